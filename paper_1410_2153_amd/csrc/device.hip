@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <climits>
 #include <cstdio>
@@ -39,6 +40,7 @@
 #include "common.hpp"
 #include "device.hpp"
 #include "host_parallel.hpp"
+#include "patch.hpp"
 #include "trace.hpp"
 
 namespace asmg {
@@ -612,8 +614,9 @@ __global__ __launch_bounds__(BS) void k_fin_spmv(const double *__restrict__ part
 
 // u += alpha p, r -= alpha q; partials of ||r||^2. The same pass runs the colour-0 Gauss-Seidel
 // pass of the next B_co application (sweep from zero) on the new r, in the precision T of B_co:
-// xf_i = r_i / a_ii on colour-0 rows (i < c0), 0 elsewhere; in FP32 r is also rounded into bf.
-template <class T>
+// xf_i = r_i / a_ii on colour-0 rows (i < c0), 0 elsewhere; in FP32 r is also rounded into bf. With
+// patches on the original grid (FIRST false) that pass is theirs.
+template <class T, bool FIRST>
 __global__ __launch_bounds__(BS) void k_cg_axpy(int n, double *__restrict__ u, double *__restrict__ r,
                                                 const double *__restrict__ p, const double *__restrict__ q,
                                                 const Ctl *ctl, double *__restrict__ partials, int c0,
@@ -626,7 +629,8 @@ __global__ __launch_bounds__(BS) void k_cg_axpy(int n, double *__restrict__ u, d
     const double ri = r[i] - alpha * q[i];
     r[i] = ri;
     v += ri * ri;
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (!FIRST) {
+    } else if constexpr (sizeof(T) == 4) {
       const float bi = (float)ri;
       bf[i] = bi;
       xf[i] = i < c0 ? bi * invd[i] : 0.0f;
@@ -983,6 +987,8 @@ struct DLevel {
   float *ng32 = nullptr, *ne32 = nullptr;
   DCsr P, PT;                 // from the next coarser level (aux levels only)
   DNb nb;                     // near-boundary correction (n = 0: none)
+  DPatch pt;                  // overlapped patches (np = 0: colour passes one by one)
+  std::vector<int> cuts;      // patch boundaries in the level's spatial order
 };
 
 struct Device {
@@ -1013,7 +1019,8 @@ struct Device {
   int restarts = 0;            // restarts from the true residual in the last solve
   int solve_iters = 0;         // PCG iterations of the last solve
   // operator refresh from a device coefficient (original grid)
-  int *rf_off_ptr = nullptr, *rf_off_el = nullptr, *rf_dg_ptr = nullptr, *rf_dg_el = nullptr, *rf_sell_map = nullptr;
+  int *rf_off_ptr = nullptr, *rf_off_el = nullptr, *rf_dg_ptr = nullptr, *rf_dg_el = nullptr, *rf_sell_map = nullptr,
+      *rf_patch_map = nullptr;
   double *rf_off_w = nullptr, *rf_dg_w = nullptr;
   int rf_nslots = 0;
   bool rf_ready = false;      // the refresh maps are built at the first device coefficient refresh
@@ -1214,10 +1221,13 @@ static SellStats sell_stats(const HCsr &H, const std::vector<int> *order) {
   return st;
 }
 
-static void stage_transfer(const HCsr &H, const std::vector<int> *order, TransferStage &X) {
+static void stage_shape(const HCsr &H, TransferStage &X) {
   X.nrows = H.nrows;
   X.ncols = H.ncols;
   X.nnz = (int64_t)H.ci.size();
+}
+
+static void stage_transfer(const HCsr &H, const std::vector<int> *order, TransferStage &X) {
   X.sell = sell_host(H, Ranges{{0, H.nrows}}, nullptr, 4, order);
   X.st = sell_stats(H, nullptr);
 }
@@ -1268,7 +1278,7 @@ static void commit_transfer(Device *dv, const TransferStage &X, DCsr &D) {
   D.nrows = X.nrows;
   D.ncols = X.ncols;
   D.nnz = X.nnz;
-  D.sell = upload_stage_sell(dv, X.sell, X.st);
+  if (!X.sell.cs.empty()) D.sell = upload_stage_sell(dv, X.sell, X.st);
   if (X.has_v) D.vsell = upload_stage_sell(dv, X.vsell, X.vst);
 }
 
@@ -1447,15 +1457,19 @@ struct LevelStage {
   std::vector<float> d32, i32;
 };
 
-static void stage_level(DLevel &L, const Csr &A, bool first_time, LevelStage &X) {
+static void stage_matrix(DLevel &L, const Csr &A, LevelStage &X) {
   X.H = permute(A, L.perm, &L.iperm, true, &X.diag);
-  const HCsr &H = X.H;
   const size_t n = X.diag.size();
   X.inv.resize(n);
   for (size_t i = 0; i < n; ++i) X.inv[i] = 1.0 / X.diag[i];
   X.d32.assign(X.diag.begin(), X.diag.end());
   X.i32.resize(n);
   for (size_t i = 0; i < n; ++i) X.i32[i] = 1.0f / (float)X.diag[i];
+}
+
+// the sliced ELL of a staged matrix
+static void stage_sell(DLevel &L, bool first_time, LevelStage &X) {
+  const HCsr &H = X.H;
   if (first_time) {
     const int G = (int)L.groups.size();
     L.cnnz.assign(G, 0);
@@ -1481,6 +1495,71 @@ static void stage_level(DLevel &L, const Csr &A, bool first_time, LevelStage &X)
         }
   }
   X.sell = sell_host(H, L.groups);
+}
+
+// Patches of the levels (index 0: the original grid, i: auxiliary level J + 1 - i), built from their
+// matrices in internal numbering. One task builds a run of kPatchRun patches.
+static constexpr int kPatchRun = 8;
+
+struct PatchJob {
+  PatchSource<HCsr> src;
+  std::vector<int> cuts;
+  std::vector<PatchHost> parts;
+  PatchHost all;
+  PatchCodes codes;
+  bool code_matrix = true;
+  std::atomic<bool> fits{true};
+};
+
+static void patch_source(PatchJob &J, const DLevel &L, const HCsr &H, const HCsr &P, const HCsr *R,
+                         const std::vector<int> &order, int nu) {
+  PatchSource<HCsr> &S = J.src;
+  S.A = &H;
+  S.n = L.n;
+  S.C = L.C;
+  S.col.resize(L.n);
+  for (int c = 0; c < L.C; ++c)
+    for (int i = L.coff[c]; i < L.coff[c + 1]; ++i) S.col[i] = (uint8_t)std::min(c, 255);
+  S.order = order;
+  S.nu = nu;
+  S.P = &P;
+  S.R = R;
+  S.prepare();
+}
+
+static int patch_runs(const PatchJob &J) {
+  return J.cuts.empty() ? 0 : ((int)J.cuts.size() - 2 + kPatchRun) / kPatchRun;
+}
+
+// run t of a job's patches, into parts[t]
+static void patch_run(PatchJob &J, int t) {
+  static thread_local PatchMarks W;
+  const int np = (int)J.cuts.size() - 1;
+  for (int p = t * kPatchRun; p < std::min(np, (t + 1) * kPatchRun) && J.fits; ++p)
+    if (!patch_range(J.src, J.cuts[p], J.cuts[p + 1], W, J.parts[t])) J.fits = false;
+}
+
+static void patch_join(PatchJob &J) {
+  if (!J.fits) {
+    J.cuts.clear();
+    J.parts.clear();
+  }
+  for (PatchHost &p : J.parts) {
+    J.all.append(p);
+    p = PatchHost();
+  }
+  J.codes = patch_code(J.all, J.code_matrix);
+}
+
+// builds the patches of every job that has cuts; a level one of whose rows alone does not fit gets none
+static void patch_build(int threads, std::vector<PatchJob> &jobs) {
+  std::vector<std::pair<int, int>> runs;
+  for (size_t j = 0; j < jobs.size(); ++j) {
+    jobs[j].parts.resize(patch_runs(jobs[j]));
+    for (int t = 0; t < patch_runs(jobs[j]); ++t) runs.push_back({(int)j, t});
+  }
+  host_parallel(threads, (int)runs.size(), [&](int i) { patch_run(jobs[runs[i].first], runs[i].second); });
+  host_parallel(threads, (int)jobs.size(), [&](int j) { patch_join(jobs[j]); });
 }
 
 // host image of a level's near-boundary solver in the level's internal numbering
@@ -1613,14 +1692,14 @@ static void commit_level(Device *dv, DLevel &L, const LevelStage &X, bool first_
       upload_csr(dv, X.H, L.A);
     else
       csr_shape(X.H, L.A);
-    sell_upload(dv, L.sell, X.sell, true);
+    if (!X.sell.cs.empty()) sell_upload(dv, L.sell, X.sell, true);
     L.dg64 = dupload(dv, X.diag);
     L.id64 = dupload(dv, X.inv);
     L.dg32 = dupload(dv, X.d32);
     L.id32 = dupload(dv, X.i32);
   } else {
     upload_values(L.A, X.H);
-    sell_upload(dv, L.sell, X.sell, false);
+    if (L.sell.sv64) sell_upload(dv, L.sell, X.sell, false);
     HIPCHECK(hipMemcpy(L.dg64, X.diag.data(), X.diag.size() * 8, hipMemcpyHostToDevice));
     HIPCHECK(hipMemcpy(L.id64, X.inv.data(), X.inv.size() * 8, hipMemcpyHostToDevice));
     HIPCHECK(hipMemcpy(L.dg32, X.d32.data(), X.d32.size() * 4, hipMemcpyHostToDevice));
@@ -1767,10 +1846,8 @@ Device *device_create(Hierarchy &h, int ordinal) {
     std::vector<NbStage> nb_st(naux);
     std::vector<TransferStage> p_st(naux), pt_st(naux);
     TransferStage pi_st, pit_st;
-    const std::vector<int> *pi_cmap = h.J > h.lc ? &dv->aux[h.J].iperm : nullptr;
     std::vector<int> forder(mrank.size());
     for (size_t i = 0; i < mrank.size(); ++i) forder[mrank[i]] = dv->fine.iperm[i];
-    // tasks: Pi and Pi^T first (the largest), then the fine operator, the levels, the prolongations
     // last colour of a level with whole-level smoothing, [first row, end) in internal numbering
     auto last_colour = [&](const DLevel &L, int l) {
       // a level with the near-boundary correction computes its residual on every row and
@@ -1778,35 +1855,67 @@ Device *device_create(Hierarchy &h, int ordinal) {
       if (L.local || L.C < 1 || (l > 0 && h.nb.count(l))) return std::make_pair(0, 0);
       return std::make_pair(L.coff[L.C - 1], L.coff[L.C]);
     };
-    const auto fl = last_colour(dv->fine, 0);
-    host_parallel(h.threads, 3 + 2 * naux, [&](int t) {
-      if (t == 0) {
-        const HCsr Pi = permute(h.Pi, dv->fine.perm, pi_cmap, false, nullptr);
-        stage_transfer(Pi, &forder, pi_st);
-        if (fl.second > fl.first) stage_prolong_v(Pi, forder, fl.first, fl.second, pi_st);
-      } else if (t == 1) {
-        const HCsr PiT = transpose(permute(h.Pi, dv->fine.perm, pi_cmap, false, nullptr));
-        stage_transfer(PiT, pi_cmap, pit_st);
-        if (fl.second > fl.first) stage_restrict_v(PiT, pi_cmap, fl.first, fl.second, pit_st);
-      } else if (t == 2) {
-        stage_level(dv->fine, h.A, true, fine_st);
-      } else if (t < 3 + naux) {
-        const int l = h.J - (t - 3);
-        stage_level(dv->aux[l], h.Al.at(l), true, aux_st[t - 3]);
-        auto it = h.nb.find(l);
-        if (it != h.nb.end()) stage_nb(it->second, dv->aux[l], aux_st[t - 3].H, nb_st[t - 3]);
+    // matrices in internal numbering: index 0 the original grid (P = Pi), i the level J + 1 - i
+    std::vector<HCsr> Pm(naux + 1), PTm(naux + 1);
+    auto stage_of = [&](int i) -> LevelStage & { return i == 0 ? fine_st : aux_st[i - 1]; };
+    auto level_of = [&](int i) -> DLevel & { return i == 0 ? dv->fine : dv->aux[h.J + 1 - i]; };
+    auto coarse_map = [&](int i) -> const std::vector<int> * {
+      return h.J - i > h.lc ? &dv->aux[h.J - i].iperm : nullptr;
+    };
+    host_parallel(h.threads, 2 * (naux + 1), [&](int t) {
+      const int i = t / 2, l = h.J + 1 - i;
+      DLevel &L = level_of(i);
+      if (t % 2 == 0) {
+        Pm[i] = permute(i == 0 ? h.Pi : h.P.at(l), L.perm, coarse_map(i), false, nullptr);
+        PTm[i] = transpose(Pm[i]);
       } else {
-        const int i = t - 3 - naux, l = h.J - i;
-        DLevel &L = dv->aux[l];
-        const std::vector<int> *cmap = l - 1 > h.lc ? &dv->aux[l - 1].iperm : nullptr;
-        HCsr P = permute(h.P.at(l), L.perm, cmap, false, nullptr);
-        const HCsr PT = transpose(P);
-        stage_transfer(P, &L.iperm, p_st[i]);
-        stage_transfer(PT, cmap, pt_st[i]);
-        const auto ll = last_colour(L, l);
-        if (ll.second > ll.first) {
-          stage_prolong_v(P, L.iperm, ll.first, ll.second, p_st[i]);
-          stage_restrict_v(PT, cmap, ll.first, ll.second, pt_st[i]);
+        stage_matrix(L, i == 0 ? h.A : h.Al.at(l), stage_of(i));
+      }
+    });
+    // Patches: whole-level smoothing without the near-boundary correction. A level whose coarser
+    // level smooths locally writes its residual instead (that level also needs a copy of its
+    // right-hand side).
+    std::vector<PatchJob> jobs(naux + 1);
+    jobs[0].code_matrix = false;  // its values may be refreshed on the device
+    host_parallel(h.threads, naux + 1, [&](int i) {
+      DLevel &L = level_of(i);
+      if (L.local || (i > 0 && h.nb.count(h.J + 1 - i))) return;
+      const bool fused = i == naux || !level_of(i + 1).local;
+      patch_source(jobs[i], L, stage_of(i).H, Pm[i], fused ? &PTm[i] : nullptr, i == 0 ? forder : L.iperm,
+                   i == 0 ? dv->nu_fine : dv->nu_aux);
+      jobs[i].cuts = patch_plan(jobs[i].src);
+    });
+    patch_build(h.threads, jobs);
+    for (int i = 0; i <= naux; ++i) level_of(i).cuts = jobs[i].cuts;
+    // sliced ELL images: the original grid's (PCG products), those of the levels without patches and
+    // their transfers, and all of them for the nested iteration
+    auto patched = [&](int i) { return !jobs[i].cuts.empty(); };
+    host_parallel(h.threads, 3 * (naux + 1), [&](int t) {
+      const int i = t / 3;
+      DLevel &L = level_of(i);
+      const auto ll = last_colour(L, i == 0 ? 0 : h.J + 1 - i);
+      const std::vector<int> &order = i == 0 ? forder : L.iperm;
+      const std::vector<int> *corder = coarse_map(i);
+      if (t % 3 == 0) {
+        if (i == 0 || !patched(i) || h.opt.nested > 0) stage_sell(L, true, stage_of(i));
+        if (i > 0) {
+          auto it = h.nb.find(h.J + 1 - i);
+          if (it != h.nb.end()) stage_nb(it->second, L, stage_of(i).H, nb_st[i - 1]);
+        }
+      } else if (t % 3 == 1) {
+        TransferStage &X = i == 0 ? pi_st : p_st[i - 1];
+        stage_shape(Pm[i], X);
+        if (!patched(i) || h.opt.nested > 0) {
+          stage_transfer(Pm[i], &order, X);
+          if (!patched(i) && ll.second > ll.first) stage_prolong_v(Pm[i], order, ll.first, ll.second, X);
+        }
+      } else {
+        TransferStage &X = i == 0 ? pit_st : pt_st[i - 1];
+        stage_shape(PTm[i], X);
+        const bool own = !patched(i) || !jobs[i].src.R;  // restricted by its own launch
+        if (own || h.opt.nested > 0) {
+          stage_transfer(PTm[i], corder, X);
+          if (own && ll.second > ll.first) stage_restrict_v(PTm[i], corder, ll.first, ll.second, X);
         }
       }
     });
@@ -1830,6 +1939,12 @@ Device *device_create(Hierarchy &h, int ordinal) {
     }
     commit_transfer(dv, pi_st, dv->Pi);
     commit_transfer(dv, pit_st, dv->PiT);
+    for (int i = 0; i <= naux; ++i) {
+      patch_commit(
+          jobs[i].all, jobs[i].codes, level_of(i).pt, jobs[i].src.R != nullptr, [&](const auto &v) { return dupload(dv, v); },
+          [&](int64_t n) { return dalloc<float>(dv, n); });
+      jobs[i].all = PatchHost();
+    }
     lap("upload");
     upload_coarse(dv, h, true);
     dv->nested = h.opt.nested;
@@ -1879,21 +1994,66 @@ Device *device_create(Hierarchy &h, int ordinal) {
   return dv;
 }
 
+// the patches of every patched level again (same cuts): new values on the same patterns
+static void rebuild_patches(Device *dv, Hierarchy &h, const std::vector<const HCsr *> &mats, std::vector<PatchJob> &jobs) {
+  const int naux = h.J - h.lc;
+  std::vector<HCsr> Pm(naux + 1), PTm(naux + 1);
+  host_parallel(h.threads, naux + 1, [&](int i) {
+    const int l = h.J + 1 - i;
+    DLevel &L = i == 0 ? dv->fine : dv->aux[l];
+    if (L.cuts.empty() || !mats[i]) return;
+    const std::vector<int> *cmap = l - 1 > h.lc ? &dv->aux[l - 1].iperm : nullptr;
+    Pm[i] = permute(i == 0 ? h.Pi : h.P.at(l), L.perm, cmap, false, nullptr);
+    std::vector<int> order = L.iperm;
+    if (i == 0) {
+      const std::vector<int> rank = morton_rank(h);
+      for (size_t k = 0; k < rank.size(); ++k) order[rank[k]] = L.iperm[k];
+    }
+    if (L.pt.fused) PTm[i] = transpose(Pm[i]);
+    patch_source(jobs[i], L, *mats[i], Pm[i], L.pt.fused ? &PTm[i] : nullptr, order, i == 0 ? dv->nu_fine : dv->nu_aux);
+    jobs[i].cuts = L.cuts;
+    jobs[i].code_matrix = i > 0;
+  });
+  patch_build(h.threads, jobs);
+}
+
 void device_update_values(Device *dv, Hierarchy &h) {
   HIPCHECK(hipSetDevice(dv->ordinal));
   const int naux = h.J - h.lc;
   std::vector<LevelStage> st(1 + naux);
   std::vector<NbStage> nst(1 + naux);
+  std::vector<PatchJob> jobs(1 + naux);
+  std::vector<const HCsr *> mats(1 + naux);
   host_parallel(h.threads, 1 + naux, [&](int t) {
-    if (t == 0) {
-      stage_level(dv->fine, h.A, false, st[0]);
-    } else {
-      const int l = h.J - (t - 1);
-      stage_level(dv->aux[l], h.Al.at(l), false, st[t]);
-      auto it = h.nb.find(l);
-      if (it != h.nb.end()) stage_nb(it->second, dv->aux[l], st[t].H, nst[t]);
-    }
+    const int l = h.J + 1 - t;
+    DLevel &L = t == 0 ? dv->fine : dv->aux[l];
+    stage_matrix(L, t == 0 ? h.A : h.Al.at(l), st[t]);
+    if (L.sell.sv64) stage_sell(L, false, st[t]);
+    mats[t] = &st[t].H;
+    if (t == 0) return;
+    auto it = h.nb.find(l);
+    if (it != h.nb.end()) stage_nb(it->second, L, st[t].H, nst[t]);
   });
+  rebuild_patches(dv, h, mats, jobs);
+  for (int i = 0; i <= naux; ++i) {
+    DPatch &D = (i == 0 ? dv->fine : dv->aux[h.J + 1 - i]).pt;
+    if (!D.np) continue;
+    if ((int64_t)jobs[i].all.pidx.size() != D.npair) throw AsmgError{ASMG_EINVAL, "matrix pattern changed"};
+    if (jobs[i].codes.matrix != D.mcode) {  // another kernel variant from here on
+      for (hipGraphExec_t &g : dv->graph) {
+        if (g) HIPCHECK(hipGraphExecDestroy(g));
+        g = nullptr;
+      }
+      patch_commit_matrix(
+          jobs[i].all, jobs[i].codes, D, [&](const auto &v) { return dupload(dv, v); },
+          [&](int64_t n) { return dalloc<float>(dv, n); });
+      continue;
+    }
+    const std::vector<double> &v = D.mcode ? jobs[i].codes.dict : jobs[i].all.pval;
+    if (D.mcode) dcopy(D.pidx, jobs[i].all.pidx);
+    dcopy(D.pval64, v);
+    patch_round((int64_t)v.size(), D.pval64, D.pval32);
+  }
   commit_level(dv, dv->fine, st[0], false, true);
   for (int l = h.J; l > h.lc; --l) {
     commit_level(dv, dv->aux[l], st[h.J - l + 1], false, false);
@@ -1987,6 +2147,19 @@ static double gs_bytes(const DLevel &L, int c, bool lower = false) {
   return nz * (sizeof(T) + 4) + 4.0 * (rows + 1) + 3.0 * sizeof(T) * rows + (double)sizeof(T) * uc;
 }
 
+// next event pair of the per-launch timing of device_time_kernel
+static void next_probe(Device *dv, double bytes, hipEvent_t &e0, hipEvent_t &e1) {
+  while (dv->probe_used + 2 > dv->probe_ev.size()) {
+    hipEvent_t p;
+    HIPCHECK(hipEventCreate(&p));
+    dv->probe_ev.push_back(p);
+  }
+  e0 = dv->probe_ev[dv->probe_used];
+  e1 = dv->probe_ev[dv->probe_used + 1];
+  dv->probe_used += 2;
+  dv->probe_bytes.push_back(bytes);
+}
+
 // One slice-kernel launch site of B_co: launch(threads, xcd, e0, e1) enqueues the kernel over
 // `nslices` slices (launch_timed: with events, they are stamped with the kernel's own start and
 // end). While tuning, the site runs the candidate shape under trial with its pair of events, so
@@ -2015,21 +2188,10 @@ static void slice_launch(Device *dv, int nslices, hipStream_t s, F &&launch, dou
     dv->tune_has.resize(std::max<size_t>(dv->tune_has.size(), site + 1), 0);
     dv->tune_has[site] = 1;
   } else if (probe_bytes >= 0.0) {
-    if (dv->probe_used + 2 > dv->probe_ev.size()) {
-      hipEvent_t p0, p1;
-      HIPCHECK(hipEventCreate(&p0));
-      HIPCHECK(hipEventCreate(&p1));
-      dv->probe_ev.push_back(p0);
-      dv->probe_ev.push_back(p1);
-    }
-    e0 = dv->probe_ev[dv->probe_used];
-    e1 = dv->probe_ev[dv->probe_used + 1];
-    dv->probe_used += 2;
-    dv->probe_bytes.push_back(probe_bytes);
+    next_probe(dv, probe_bytes, e0, e1);
   }
   launch(sh.threads, sh.xcd, sh.var, e0, e1);
 }
-
 
 template <class T>
 static void gs_pass(Device *dv, DLevel &L, int c, T *x, const T *b, hipStream_t s, bool lower = false) {
@@ -2191,8 +2353,60 @@ const float *cinv<float>(Device *dv) { return dv->cinv32; }
 // rhs / solution vectors of level l (the bottom level has its own)
 template <class T>
 static T *lvl_b(Device *dv, int l) { return l == dv->lc ? cvec_b<T>(dv) : LV<T>::b(dv->aux[l]); }
+// (patches write their result beside x, which their neighbours still read: in r)
 template <class T>
-static T *lvl_x(Device *dv, int l) { return l == dv->lc ? cvec_x<T>(dv) : LV<T>::x(dv->aux[l]); }
+static T *result(DLevel &L) { return L.pt.np ? LV<T>::r(L) : LV<T>::x(L); }
+template <class T>
+static T *lvl_x(Device *dv, int l) { return l == dv->lc ? cvec_x<T>(dv) : result<T>(dv->aux[l]); }
+
+// One patch launch. It stands for `passes` launch sites of the pass-by-pass path, whose entries in
+// the table of launch shapes it leaves at the default; timed as one launch by the pass probe.
+template <class T, class F>
+static void patch_launch(Device *dv, const DPatch &D, int passes, double bytes, F &&launch) {
+  if (dv->site >= 0) {
+    dv->site += passes;
+    if (dv->tuning) {
+      dv->tune_live = std::max(dv->tune_live, dv->site);
+      dv->tune_has.resize(std::max<size_t>(dv->tune_has.size(), dv->site), 0);
+    }
+  }
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (!dv->tuning && dv->probe_lpr != 0 && dv->probe_prec == (sizeof(T) == 4 ? 1 : 0))
+    next_probe(dv, bytes, e0, e1);
+  if (dv->count_bytes) dv->bytes += bytes;
+  launch(e0, e1);
+}
+
+// forward sweeps from zero on b, residual and restriction into bc (or the residual in r)
+template <class T, class BT>
+static void patch_down(Device *dv, DLevel &L, int nu, const BT *b, T *bc, hipStream_t s) {
+  const DPatch &D = L.pt;
+  const double sz = sizeof(T);
+  // entries once, cell numbers, b, the diagonals, x written; the restriction's entries and result
+  const double by = (double)L.A.nnz * (sz + 2) + (double)L.n * (4 + sizeof(BT) + 3 * sz) +
+                    (D.fused ? (double)D.nr * 2 * (sz + 2) + (double)D.ncoarse * (4 + sz) : (double)L.n * sz);
+  patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
+    with_codes(D, [&](auto mc, auto tc) {
+      launch_patch(k_patch_down<1, T, BT, decltype(mc)::value, decltype(tc)::value>, D, sizeof(T), sizeof(T), s, e0, e1,
+                   D.view<T>(), D.cells, L.C, nu, D.fused ? 1 : 0, b, LV<T>::dg(L), LV<T>::x(L), LV<T>::r(L), bc);
+    });
+  });
+}
+
+// x + P e, then backward sweeps on b, into result<T>(L)
+template <class T, class BT>
+static void patch_up(Device *dv, DLevel &L, int nu, const BT *b, const T *e, hipStream_t s) {
+  const DPatch &D = L.pt;
+  const double sz = sizeof(T);
+  const double by = (double)L.A.nnz * (sz + 2) + (double)L.n * (4 + sizeof(BT) + 3 * sz) + (double)D.nu * (sz + 4) +
+                    (double)D.ncoarse * sz;
+  patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
+    with_codes(D, [&](auto mc, auto tc) {
+      launch_patch(k_patch_up<1, T, BT, decltype(mc)::value, decltype(tc)::value>, D, sizeof(T), 0, s, e0, e1,
+                   D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L), (const T *)LV<T>::x(L), e, LV<T>::r(L));
+    });
+  });
+}
 
 // restriction into level l's right-hand side (with its first colour pass above the bottom)
 template <class T>
@@ -2277,7 +2491,21 @@ static void nb_correct(Device *dv, DLevel &L, T *x, const T *b, hipStream_t s) {
   }
 }
 
-// Algorithm 2: B_l applied to the level's b, result in the level's x. Above the bottom, the
+// after patch_down on a finer level: level l's right-hand side where the patches left the residual,
+// and its first colour pass where its passes run one by one
+template <class T>
+static void after_down(Device *dv, DLevel &F, const DCsr &PT, int l, hipStream_t s) {
+  if (!F.pt.fused) {
+    restrict_to<T>(dv, PT, (const T *)LV<T>::r(F), l, s);
+  } else if (l != dv->lc && !dv->aux[l].pt.np) {
+    DLevel &L = dv->aux[l];
+    hipLaunchKernelGGL((k_gs_first<T>), dim3(nblk(L.n)), dim3(BS), 0, s, L.n, L.first_rows, (const T *)LV<T>::b(L),
+                       LV<T>::id(L), LV<T>::x(L));
+    if (dv->count_bytes) dv->bytes += first_pass_bytes<T>(L);
+  }
+}
+
+// Algorithm 2: B_l applied to the level's b, result in result<T>(level). Above the bottom, the
 // colour-0 pass of the first forward sweep has been run by the restriction that wrote b. A level
 // with a near-boundary set corrects on it before and after the coarse-grid correction (the
 // symmetric form of Algorithm 3: B_l stays symmetric); its residual then covers every row.
@@ -2293,6 +2521,13 @@ static void vcycle(Device *dv, int l, hipStream_t s) {
   DLevel &L = dv->aux[l];
   T *x = LV<T>::x(L);
   T *b = LV<T>::b(L);
+  if (L.pt.np) {
+    patch_down<T>(dv, L, dv->nu_aux, (const T *)b, lvl_b<T>(dv, l - 1), s);
+    after_down<T>(dv, L, L.PT, l - 1, s);
+    vcycle<T>(dv, l - 1, s);
+    patch_up<T>(dv, L, dv->nu_aux, (const T *)b, (const T *)lvl_x<T>(dv, l - 1), s);
+    return;
+  }
   const bool nb = L.nb.n > 0;
   for (int k = 0; k < dv->nu_aux; ++k) sweep<T>(dv, L, x, b, k == 0, true, true, s);
   if (nb) nb_correct<T>(dv, L, x, b, s);
@@ -2304,7 +2539,7 @@ static void vcycle(Device *dv, int l, hipStream_t s) {
   for (int k = 0; k < dv->nu_aux; ++k) sweep<T>(dv, L, x, b, false, false, false, s);
 }
 
-// Algorithm 1 (u_0 = 0): x_fine = B_co r; r in FP64 (internal order), result in fine.x{64,32}.
+// Algorithm 1 (u_0 = 0): B_co r; r in FP64 (internal order), result in result<T>(fine).
 // `first_done`: the colour-0 pass of the fine forward sweep (and, in FP32, the rounding of r
 // into fine.b32) has already been run by the CG update that produced r.
 template <class T>
@@ -2314,6 +2549,13 @@ static void apply_Bco(Device *dv, const double *r, bool first_done, hipStream_t 
   dv->shape_pi = sizeof(T) == 4 ? 1 : 0;
   T *x = LV<T>::x(F);
   const T *b;
+  if (F.pt.np) {
+    patch_down<T>(dv, F, dv->nu_fine, r, lvl_b<T>(dv, dv->J), s);
+    after_down<T>(dv, F, dv->PiT, dv->J, s);
+    vcycle<T>(dv, dv->J, s);
+    patch_up<T>(dv, F, dv->nu_fine, r, (const T *)lvl_x<T>(dv, dv->J), s);
+    return;
+  }
   if constexpr (sizeof(T) == 8) {
     b = r;
   } else {
@@ -2377,10 +2619,11 @@ static void nested_start(Device *dv, hipStream_t s) {
     spmv<T, 0>(dv, L.P, NV<T>::e(dv, l - 1), e, s);
     for (int k = 0; k < dv->nested; ++k) {
       residual<T>(dv, L, g, e, LV<T>::b(L), s, true);
-      hipLaunchKernelGGL((k_gs_first<T>), dim3(nblk(L.n)), dim3(BS), 0, s, L.n, L.first_rows,
-                         (const T *)LV<T>::b(L), LV<T>::id(L), LV<T>::x(L));
+      if (!L.pt.np)
+        hipLaunchKernelGGL((k_gs_first<T>), dim3(nblk(L.n)), dim3(BS), 0, s, L.n, L.first_rows,
+                           (const T *)LV<T>::b(L), LV<T>::id(L), LV<T>::x(L));
       vcycle<T>(dv, l, s);
-      hipLaunchKernelGGL((k_add<T>), dim3(nblk(L.n)), dim3(BS), 0, s, L.n, (const T *)LV<T>::x(L), e);
+      hipLaunchKernelGGL((k_add<T>), dim3(nblk(L.n)), dim3(BS), 0, s, L.n, (const T *)result<T>(L), e);
     }
   }
   if constexpr (sizeof(T) == 8) {
@@ -2412,10 +2655,10 @@ static void pcg_tail(Device *dv, hipStream_t s, bool first_done) {
   const int n = dv->fine.n;
   apply_Bco<T>(dv, dv->r, first_done, s);
   const int g = red_grid(dv, n, 1);
-  hipLaunchKernelGGL((k_cg_rz<T>), dim3(g), dim3(BS), 0, s, n, dv->r, (const T *)LV<T>::x(dv->fine), dv->ctl,
+  hipLaunchKernelGGL((k_cg_rz<T>), dim3(g), dim3(BS), 0, s, n, dv->r, (const T *)result<T>(dv->fine), dv->ctl,
                      dv->partials);
   hipLaunchKernelGGL(k_fin_rz, dim3(1), dim3(BS), 0, s, dv->partials, g, dv->ctl);
-  hipLaunchKernelGGL((k_cg_p<T>), dim3(nblk(n)), dim3(BS), 0, s, n, (const T *)LV<T>::x(dv->fine), dv->p, dv->ctl);
+  hipLaunchKernelGGL((k_cg_p<T>), dim3(nblk(n)), dim3(BS), 0, s, n, (const T *)result<T>(dv->fine), dv->p, dv->ctl);
 }
 
 // Autotuner: for every candidate shape (twice), one eager B_co application on the current r with
@@ -2438,12 +2681,15 @@ static void tune(Device *dv, hipStream_t s) {
         apply_Bco<T>(dv, dv->r, false, s);
         HIPCHECK(hipStreamSynchronize(s));
         if ((int)t.size() < dv->tune_live) t.resize(dv->tune_live, std::vector<float>(K, INFINITY));
+        bool any = false;
         for (int site = 0; site < dv->tune_live; ++site) {
           if (!dv->tune_has[site]) continue;
+          any = true;
           float ms = 0;
           HIPCHECK(hipEventElapsedTime(&ms, dv->tune_ev[2 * site], dv->tune_ev[2 * site + 1]));
           t[site][k] = std::min(t[site][k], ms);
         }
+        if (!any) round = k = INT_MAX - 1;  // patches on every level: nothing to choose
       }
   } catch (...) {
     dv->tuning = false;
@@ -2467,8 +2713,12 @@ static void pcg_iteration(Device *dv, hipStream_t s) {
                      F.sell.sv64, F.dg64, dv->p, dv->q, dv->ctl, dv->partials);
   hipLaunchKernelGGL(k_fin_spmv, dim3(1), dim3(BS), 0, s, dv->partials, g, dv->ctl);
   g = red_grid(dv, n, 1);
-  hipLaunchKernelGGL((k_cg_axpy<T>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl, dv->partials,
-                     F.first_rows, LV<T>::id(F), LV<T>::b(F), LV<T>::x(F));
+  if (F.pt.np)
+    hipLaunchKernelGGL((k_cg_axpy<T, false>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl,
+                       dv->partials, 0, (const T *)nullptr, (T *)nullptr, (T *)nullptr);
+  else
+    hipLaunchKernelGGL((k_cg_axpy<T, true>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl,
+                       dv->partials, F.first_rows, LV<T>::id(F), LV<T>::b(F), LV<T>::x(F));
   hipLaunchKernelGGL(k_fin_axpy, dim3(1), dim3(BS), 0, s, dv->partials, g, dv->ctl);
   pcg_tail<T>(dv, s, true);
 }
@@ -2611,6 +2861,14 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
     std::vector<int> slots;
     build_sell(dv, F, H, false, &slots);
     build_refresh(dv, h, H, slots);
+    if (F.pt.np) {
+      std::vector<PatchJob> jobs(1 + h.J - h.lc);
+      std::vector<const HCsr *> mats(jobs.size(), nullptr);
+      mats[0] = &H;
+      jobs[0].src.want_map = true;
+      rebuild_patches(dv, h, mats, jobs);
+      dv->rf_patch_map = dupload(dv, jobs[0].all.pmap);
+    }
     dv->rf_ready = true;
   }
   hipLaunchKernelGGL(k_refresh_off, dim3(nblk(F.A.nnz)), dim3(BS), 0, s, (int)F.A.nnz, dv->rf_off_ptr, dv->rf_off_el,
@@ -2619,6 +2877,9 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
                      dv->kappa, F.dg64, F.id64, F.dg32, F.id32);
   hipLaunchKernelGGL(k_refresh_sell, dim3(nblk(dv->rf_nslots)), dim3(BS), 0, s, dv->rf_nslots, dv->rf_sell_map,
                      F.A.v64, F.sell.sv64, F.sell.sv32);
+  if (F.pt.npair > 0)
+    hipLaunchKernelGGL(k_refresh_sell, dim3(nblk(2 * F.pt.npair)), dim3(BS), 0, s, (int)(2 * F.pt.npair),
+                       dv->rf_patch_map, F.A.v64, F.pt.pval64, F.pt.pval32);
   HIPCHECK(hipGetLastError());
   HIPCHECK(hipStreamSynchronize(s));
   return ASMG_OK;
@@ -2721,11 +2982,11 @@ int device_apply_B(Device *dv, const double *d_r, double *d_z, int precision, vo
   if (precision == ASMG_PREC_MIXED) {
     apply_Bco<float>(dv, dv->f, false, s);
     hipLaunchKernelGGL((k_scatter_cvt<float>), dim3(nblk(n)), dim3(BS), 0, s, n, dv->perm_d,
-                       (const float *)dv->fine.x32, d_z);
+                       (const float *)result<float>(dv->fine), d_z);
   } else {
     apply_Bco<double>(dv, dv->f, false, s);
     hipLaunchKernelGGL((k_scatter_cvt<double>), dim3(nblk(n)), dim3(BS), 0, s, n, dv->perm_d,
-                       (const double *)dv->fine.x64, d_z);
+                       (const double *)result<double>(dv->fine), d_z);
   }
   HIPCHECK(hipGetLastError());
   HIPCHECK(hipStreamSynchronize(s));

@@ -1,0 +1,1063 @@
+// Overlapped patches: a level's Gauss-Seidel sweeps, residual and transfers as two launches.
+//
+// A level is cut into patches of consecutive rows in spatial (Morton) order. A patch also holds the
+// halo of rows that its own rows' results depend on through every colour pass of the sweeps, found by
+// walking the passes backwards: before a pass of colour c, the needed values are the ones needed
+// after it without colour c, and the neighbours of the needed rows of colour c. One block keeps the
+// patch's x in LDS and its matrix rows in registers, runs all passes with a block barrier between
+// them, and writes its own rows only; halo rows are computed redundantly (the same arithmetic in the
+// same order as their owner's, so every patch sees the same values). A row whose inputs lie outside the
+// patch computes a value that no needed row reads.
+//
+// `down` (forward sweeps from zero): b -> x on the own rows, then the residual, then the restriction of
+// the coarse rows that the patch owns (their fine rows belong to the halo as well).
+// `up` (backward sweeps): x + P e on every cell that the first pass reads, then the passes.
+//
+// Layout of a patch: its rows sorted by colour, inside a colour by row length, in slices of 64 rows
+// (one per lane); slice k belongs to wave k % 8, and cell 64 k + lane of the LDS image is its row. Cells
+// that are read but never computed follow the last slice. The cells whose value counts before the first
+// backward pass form slices of their own (start rows), by the length of their prolongation row. Matrix entries come in pairs: two values and
+// two 16-bit cell numbers, 64 lanes side by side. Matrices with few distinct values (the level matrices
+// of a constant coefficient) keep a 4-bit code above each 12-bit cell number instead of the value, and
+// so do prolongations, whose entries are 1 and 1/2 (above the column number).
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+#include <vector>
+
+#include "common.hpp"
+#include "host_parallel.hpp"
+
+namespace asmg {
+
+static constexpr int kPatchWaves = 8;
+static constexpr int kPatchThreads = 64 * kPatchWaves;
+static constexpr int kPatchSlots = 4;  // slices per wave
+static constexpr int kPatchSlices = kPatchWaves * kPatchSlots;
+static constexpr int kPatchCellSlices = 38;
+static constexpr int kPatchHeadCoarse = 16;  // coarse slices whose entry offsets are in the head
+static constexpr int kPatchPairs = 4;  // entry pairs of a row kept in registers (the cases of dot())
+static constexpr int kPatchColours = 15;
+static constexpr int kPatchHalo = 1 << 30;  // gidx: a halo row or cell (its result is not written)
+
+static constexpr int kPatchCodes = 16;
+static constexpr int kPatchCellBits = 12;      // a cell number below its code
+static_assert(64 * kPatchCellSlices <= 1 << kPatchCellBits, "cell numbers fit below the codes");
+
+struct alignas(64) PatchHead {
+  int ns, ncs;          // matrix slices, cell slices (the first ns are the matrix slices)
+  int start0, nst;      // first slice of start rows, slices
+  int coarse0, nco;     // first slice of coarse rows, slices
+  uint32_t sc[kPatchSlots];        // colour of slice 8 j + i in bits 4 i of sc[j], 15 = none
+  int poff[kPatchSlices + 1];      // first pair row of each matrix slice
+  int uoff[kPatchCellSlices + 1];  // first prolongation row of each slice of start rows
+  int roff[kPatchHeadCoarse + 1];  // first pair row of the first coarse slices
+};
+
+// host image of a level's patches
+struct PatchHost {
+  std::vector<PatchHead> head;
+  std::vector<int> gidx;            // level row per matrix lane, -1 = none; kPatchSlices slices a patch
+  std::vector<uint32_t> pidx;       // two cells per pair
+  std::vector<double> pval;         // two values
+  std::vector<int> pmap;            // matrix entry of each value, -1 = padding (on request)
+  std::vector<int> ugidx, ucell;    // start rows: level row (-1 = none), cell
+  std::vector<int> ucol;            // and prolongation row
+  std::vector<double> uval;
+  std::vector<int> roff{0}, rrow;   // coarse rows owned, and their restriction over cells
+  std::vector<uint32_t> ridx;
+  std::vector<double> rval;
+  int64_t rows = 0, own = 0;
+
+  void append(const PatchHost &b) {
+    const int c0 = (int)(ugidx.size() / 64), r0 = (int)roff.size() - 1;
+    const int p0 = (int)(pidx.size() / 64), u0 = (int)(ucol.size() / 64), q0 = roff.back();
+    for (PatchHead h : b.head) {
+      h.start0 += c0;
+      h.coarse0 += r0;
+      for (int &o : h.poff) o += p0;
+      for (int &o : h.uoff) o += u0;
+      for (int &o : h.roff) o += q0;
+      head.push_back(h);
+    }
+    auto cat = [](auto &x, const auto &y) { x.insert(x.end(), y.begin(), y.end()); };
+    auto shift = [](std::vector<int> &x, const std::vector<int> &y, int d) {
+      for (size_t i = 1; i < y.size(); ++i) x.push_back(y[i] + d);
+    };
+    cat(gidx, b.gidx);
+    cat(pidx, b.pidx);
+    cat(pval, b.pval);
+    cat(pmap, b.pmap);
+    cat(ugidx, b.ugidx);
+    cat(ucell, b.ucell);
+    cat(ucol, b.ucol);
+    cat(uval, b.uval);
+    shift(roff, b.roff, q0);
+    cat(rrow, b.rrow);
+    cat(ridx, b.ridx);
+    cat(rval, b.rval);
+    rows += b.rows;
+    own += b.own;
+  }
+};
+
+// One level's matrices in its internal numbering, as the builder reads them. M has rp, ci, v.
+template <class M>
+struct PatchSource {
+  const M *A = nullptr;       // off-diagonal part, symmetric pattern
+  int n = 0;                  // rows (all smoothed)
+  std::vector<uint8_t> col;   // colour per row
+  int C = 0;
+  std::vector<int> order;     // rows in spatial order
+  int nu = 1;                 // sweeps per side
+  const M *P = nullptr;       // prolongation: rows of this level, columns of the coarser one
+  const M *R = nullptr;       // restriction: all rows of the coarser level; null = write the residual
+  bool want_map = false;
+  // filled by prepare()
+  std::vector<int> pos;           // position of each row in the order
+  std::vector<int> cpos0, clist;  // coarse rows by the position of the row that decides their owner
+
+  void prepare() {
+    pos.resize(n);
+    for (int i = 0; i < n; ++i) pos[order[i]] = i;
+    if (!R) return;
+    const int nc = (int)R->rp.size() - 1;
+    std::vector<int> at(nc);
+    cpos0.assign((size_t)n + 1, 0);
+    for (int k = 0; k < nc; ++k) {
+      int best = -1;
+      double w = -1;
+      for (int p = R->rp[k]; p < R->rp[k + 1]; ++p) {
+        const double a = std::fabs(R->v[p]);
+        if (a > w) {
+          w = a;
+          best = R->ci[p];
+        }
+      }
+      at[k] = best >= 0 ? pos[best] : (int)((int64_t)k * n / nc);
+      cpos0[at[k] + 1]++;
+    }
+    for (int i = 0; i < n; ++i) cpos0[i + 1] += cpos0[i];
+    clist.resize(nc);
+    std::vector<int> fill(cpos0.begin(), cpos0.end() - 1);
+    for (int k = 0; k < nc; ++k) clist[fill[at[k]]++] = k;
+  }
+};
+
+// per-thread marks over a level's rows
+struct PatchMarks {
+  std::vector<int> need, uni, cell, row;
+  int epoch = 0;
+  void size(int n) {
+    if ((int)need.size() < n) {
+      need.resize(n, 0);
+      uni.resize(n, 0);
+      cell.resize(n, 0);
+      row.resize(n, 0);
+    }
+    ++epoch;
+  }
+};
+
+// Patch of the rows order[a..b): appended to out; false (nothing appended) where it does not fit.
+template <class M>
+static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, PatchHost &out) {
+  const M &A = *S.A;
+  const int C = S.C;
+  W.size(S.n);
+  const int E = W.epoch;
+  std::vector<int> need, next, uni;
+  auto add = [&](int r) {
+    if (W.need[r] != E) {
+      W.need[r] = E;
+      need.push_back(r);
+    }
+    if (W.uni[r] != E) {
+      W.uni[r] = E;
+      uni.push_back(r);
+    }
+  };
+  auto later = [&](int c, bool earlier_only, bool rows) {  // undo one pass of colour c
+    next.clear();
+    std::vector<int> cur;
+    for (int r : need)
+      if (S.col[r] == c) {
+        W.need[r] = E - 1;
+        cur.push_back(r);
+        if (rows) W.row[r] = E;
+      } else if (!(earlier_only && S.col[r] > c)) {
+        next.push_back(r);
+      } else {
+        W.need[r] = E - 1;
+      }
+    need.swap(next);
+    for (int r : cur)
+      for (int p = A.rp[r]; p < A.rp[r + 1]; ++p)
+        if (!earlier_only || S.col[A.ci[p]] < c) add(A.ci[p]);
+  };
+  // rows computed going down
+  for (int i = a; i < b; ++i) add(S.order[i]);
+  auto residual_of = [&](int r) {
+    add(r);
+    for (int p = A.rp[r]; p < A.rp[r + 1]; ++p)
+      if (S.nu > 1 || S.col[A.ci[p]] > S.col[r]) add(A.ci[p]);
+  };
+  if (S.R) {
+    for (int q = S.cpos0[a]; q < S.cpos0[b]; ++q) {
+      const int k = S.clist[q];
+      for (int p = S.R->rp[k]; p < S.R->rp[k + 1]; ++p)
+        if (S.col[S.R->ci[p]] != C - 1) residual_of(S.R->ci[p]);
+    }
+  } else {
+    for (int i = a; i < b; ++i)
+      if (S.col[S.order[i]] != C - 1) residual_of(S.order[i]);
+  }
+  for (int k = S.nu - 1; k >= 0; --k)
+    for (int c = C - 1; c >= 0; --c) later(c, k == 0, false);
+  for (int r : uni) W.row[r] = E;
+  if ((int)uni.size() > 64 * kPatchSlices) {
+    return false;
+  }
+  // rows computed and cells read going up
+  for (int r : need) W.need[r] = E - 1;
+  need.clear();
+  for (int i = a; i < b; ++i) add(S.order[i]);
+  for (int k = 0; k < S.nu; ++k)
+    for (int c = 0; c < C; ++c) later(c, false, true);
+  // now need = the cells whose value before the first pass counts (marked E in W.need)
+  std::vector<std::vector<int>> by(C);
+  std::vector<int> cells;
+  for (int i : uni)
+    if (W.row[i] == E)
+      by[S.col[i]].push_back(i);
+    else
+      cells.push_back(i);
+  int ns = 0;
+  for (auto &v : by) ns += ((int)v.size() + 63) / 64;
+  const int ncs = ns + ((int)cells.size() + 63) / 64;
+  if (ns > kPatchSlices || ncs > kPatchCellSlices) return false;
+  // spatial order inside a colour: internal numbers ascend with the spatial order there
+  PatchHead h{};
+  h.start0 = (int)(out.ugidx.size() / 64);
+  h.coarse0 = (int)out.roff.size() - 1;
+  h.ns = ns;
+  h.ncs = ncs;
+  auto kept = [&](int r) {
+    int w = 0;
+    for (int p = A.rp[r]; p < A.rp[r + 1]; ++p) w += W.uni[A.ci[p]] == E;
+    return w;
+  };
+  std::vector<int> list;  // row per cell, -1 = empty lane
+  std::vector<std::pair<int, int>> key;
+  for (uint32_t &x : h.sc) x = ~0u;
+  for (int c = 0; c < C; ++c) {
+    const int k0 = (int)list.size() / 64;
+    std::sort(by[c].begin(), by[c].end());
+    key.clear();
+    for (int r : by[c]) key.push_back({(kept(r) + 1) / 2, r});
+    std::stable_sort(key.begin(), key.end(), [](auto &x, auto &y) { return x.first > y.first; });
+    for (auto &kr : key) list.push_back(kr.second);
+    while (list.size() % 64) list.push_back(-1);
+    for (int k = k0; k < (int)list.size() / 64; ++k) {
+      h.sc[k / kPatchWaves] &= ~(15u << 4 * (k % kPatchWaves));
+      h.sc[k / kPatchWaves] |= (uint32_t)c << 4 * (k % kPatchWaves);
+    }
+  }
+  std::sort(cells.begin(), cells.end());
+  for (int r : cells) list.push_back(r);
+  while (list.size() % 64) list.push_back(-1);
+  for (size_t i = 0; i < list.size(); ++i)
+    if (list[i] >= 0) W.cell[list[i]] = (int)i;
+  // own rows: marked by position
+  std::vector<uint8_t> own(list.size(), 0);
+  for (int i = a; i < b; ++i) own[W.cell[S.order[i]]] = 1;
+  for (int i = 0; i < 64 * kPatchSlices; ++i) {
+    const int r = i < 64 * ns ? list[i] : -1;
+    out.gidx.push_back(r < 0 ? -1 : own[i] ? r : r | kPatchHalo);
+  }
+  // matrix pairs
+  for (int k = 0; k < ns; ++k) {
+    int w = 0;
+    for (int l = 0; l < 64; ++l)
+      if (list[64 * k + l] >= 0) w = std::max(w, (kept(list[64 * k + l]) + 1) / 2);
+    const size_t base = out.pidx.size();
+    h.poff[k] = (int)(base / 64);
+    out.pidx.resize(base + (size_t)w * 64, 0);
+    out.pval.resize(2 * (base + (size_t)w * 64), 0.0);
+    if (S.want_map) out.pmap.resize(2 * (base + (size_t)w * 64), -1);
+    for (int l = 0; l < 64; ++l) {
+      const int r = list[64 * k + l];
+      if (r < 0) continue;
+      int q = 0, first = 0;
+      for (int p = A.rp[r]; p < A.rp[r + 1]; ++p) {
+        if (W.uni[A.ci[p]] != E) continue;
+        const int c = W.cell[A.ci[p]];
+        if (q == 0) first = c;
+        const size_t e = base + (size_t)(q >> 1) * 64 + l;
+        out.pidx[e] |= (uint32_t)c << (q & 1 ? 16 : 0);
+        out.pval[2 * e + (q & 1)] = A.v[p];
+        if (S.want_map) out.pmap[2 * e + (q & 1)] = p;
+        ++q;
+      }
+      for (; q < 2 * w; ++q)  // padding: the row's first neighbour with value 0
+        out.pidx[base + (size_t)(q >> 1) * 64 + l] |= (uint32_t)first << (q & 1 ? 16 : 0);
+    }
+  }
+  for (int k = ns; k <= kPatchSlices; ++k) h.poff[k] = (int)(out.pidx.size() / 64);
+  // start rows: the cells that some backward pass reads as they were
+  auto plen = [&](int r) { return S.P->rp[r + 1] - S.P->rp[r]; };
+  key.clear();
+  for (int r : need)
+    if (W.need[r] == E && S.col[r] != C - 1) key.push_back({plen(r), r});
+  // in spatial order (the gathers of a slice then share lines), by length inside windows
+  std::sort(key.begin(), key.end(), [&](auto &x, auto &y) { return S.pos[x.second] < S.pos[y.second]; });
+  for (size_t k = 0; k < key.size(); k += 256)
+    std::stable_sort(key.begin() + k, key.begin() + std::min(k + 256, key.size()),
+                     [](auto &x, auto &y) { return x.first > y.first; });
+  for (size_t k = 0; k < key.size(); k += 64) {
+    const int w = key[k].first;
+    const size_t base = out.ucol.size();
+    h.uoff[h.nst++] = (int)(base / 64);
+    out.ucol.resize(base + (size_t)w * 64, 0);
+    out.uval.resize(base + (size_t)w * 64, 0.0);
+    for (size_t l = 0; l < 64; ++l) {
+      const int r = k + l < key.size() ? key[k + l].second : -1;
+      out.ugidx.push_back(r);
+      out.ucell.push_back(r < 0 ? 0 : W.cell[r]);
+      if (r < 0) continue;
+      const int m = plen(r);
+      for (int q = 0; q < w; ++q) {
+        const size_t e = base + (size_t)q * 64 + l;
+        if (q < m) {
+          out.ucol[e] = S.P->ci[S.P->rp[r] + q];
+          out.uval[e] = S.P->v[S.P->rp[r] + q];
+        } else if (m > 0) {
+          out.ucol[e] = S.P->ci[S.P->rp[r]];
+        }
+      }
+    }
+  }
+  for (int k = h.nst; k <= kPatchCellSlices; ++k) h.uoff[k] = (int)(out.ucol.size() / 64);
+  // coarse rows
+  if (S.R) {
+    key.clear();
+    auto len = [&](int k) {
+      int w = 0;
+      for (int p = S.R->rp[k]; p < S.R->rp[k + 1]; ++p) w += S.col[S.R->ci[p]] != C - 1;
+      return w;
+    };
+    for (int q = S.cpos0[a]; q < S.cpos0[b]; ++q) key.push_back({(len(S.clist[q]) + 1) / 2, S.clist[q]});
+    std::stable_sort(key.begin(), key.end(), [](auto &x, auto &y) { return x.first > y.first; });
+    for (size_t k = 0; k < key.size(); k += 64) {
+      const int w = key[k].first;
+      const size_t base = (size_t)out.roff.back() * 64;
+      out.ridx.resize(base + (size_t)w * 64, 0);
+      out.rval.resize(2 * (base + (size_t)w * 64), 0.0);
+      for (size_t l = 0; l < 64; ++l) {
+        if (k + l >= key.size()) {
+          out.rrow.push_back(-1);
+          continue;
+        }
+        const int row = key[k + l].second;
+        out.rrow.push_back(row);
+        int q = 0, first = 0;
+        for (int p = S.R->rp[row]; p < S.R->rp[row + 1]; ++p) {
+          if (S.col[S.R->ci[p]] == C - 1) continue;
+          const int c = W.cell[S.R->ci[p]];
+          if (q == 0) first = c;
+          const size_t e = base + (size_t)(q >> 1) * 64 + l;
+          out.ridx[e] |= (uint32_t)c << (q & 1 ? 16 : 0);
+          out.rval[2 * e + (q & 1)] = S.R->v[p];
+          ++q;
+        }
+        for (; q < 2 * w; ++q) out.ridx[base + (size_t)(q >> 1) * 64 + l] |= (uint32_t)first << (q & 1 ? 16 : 0);
+      }
+      out.roff.push_back(out.roff.back() + w);
+      ++h.nco;
+    }
+  }
+  for (int k = 0; k <= kPatchHeadCoarse; ++k) h.roff[k] = out.roff[h.coarse0 + std::min(k, h.nco)];
+  out.head.push_back(h);
+  out.rows += (int64_t)uni.size() - (int64_t)cells.size();
+  out.own += b - a;
+  return true;
+}
+
+template <class M>
+static bool patch_range(const PatchSource<M> &S, int a, int b, PatchMarks &W, PatchHost &out) {
+  if (a >= b) return true;
+  if (patch_one(S, a, b, W, out)) return true;
+  if (b - a < 2) return false;
+  const int m = a + (b - a) / 2;
+  return patch_range(S, a, m, W, out) && patch_range(S, m, b, W, out);
+}
+
+// own rows per patch: enough patches for the chip where that is possible, no fewer own rows than
+// kPatchOwnMin (the halo grows against them), and patches that fit
+static constexpr int kPatchOwnMin = 256;
+static constexpr int kPatchOwnMax = 1536;
+
+// Computed rows per own row above which the passes one by one are the better path.
+static constexpr double kPatchMaxRatio = 2.6;
+
+// Plan of one level's patches: the chunk boundaries in the spatial order; empty = no patches.
+template <class M>
+static std::vector<int> patch_plan(const PatchSource<M> &S) {
+  std::vector<int> cut;
+  if (S.n < 1 || S.C < 1 || S.C > kPatchColours || S.n >= 1 << 27) return cut;
+  PatchMarks W;
+  int target = std::max(kPatchOwnMin, std::min(kPatchOwnMax, (S.n + 255) / 256));
+  for (; target >= 128; target -= target / 8) {
+    const int np = (S.n + target - 1) / target;
+    const int tries = std::min(np, 8);
+    PatchHost t;
+    bool fit = true;
+    for (int i = 0; i < tries && fit; ++i) {
+      const int64_t p = tries > 1 ? (int64_t)i * (np - 1) / (tries - 1) : 0;
+      fit = patch_one(S, (int)(p * S.n / np), (int)((p + 1) * S.n / np), W, t);
+    }
+    if (!fit) continue;
+    if ((double)t.rows > kPatchMaxRatio * (double)t.own) return cut;
+    for (int p = 0; p <= np; ++p) cut.push_back((int)((int64_t)p * S.n / np));
+    return cut;
+  }
+  return cut;
+}
+
+// the distinct values of v in ascending order, at most `most` of them (else empty)
+static inline std::vector<double> patch_codes(const std::vector<double> &v, size_t most) {
+  std::vector<double> d;
+  for (double x : v) {
+    auto it = std::lower_bound(d.begin(), d.end(), x);
+    if (it != d.end() && *it == x) continue;
+    if (d.size() == most || !(x == x)) return {};
+    d.insert(it, x);
+  }
+  return d;
+}
+
+// Codes of a level: of its matrix entries (code, the index of the value in `dict`) and of its transfers
+// (tcode: 0 for the value 1, 1 for 1/2, 2 for the padding's 0).
+struct PatchCodes {
+  bool matrix = false, transfer = false;
+  std::vector<double> dict;
+};
+
+static inline PatchCodes patch_code(PatchHost &H, bool matrix) {
+  PatchCodes K;
+  K.dict.assign(kPatchCodes, 0.0);
+  auto halves = [](std::vector<uint32_t> &idx, const std::vector<double> &v, auto &&code) {
+    for (size_t e = 0; e < idx.size(); ++e)
+      idx[e] |= (uint32_t)code(v[2 * e]) << kPatchCellBits | (uint32_t)code(v[2 * e + 1]) << (16 + kPatchCellBits);
+  };
+  if (matrix) {
+    const std::vector<double> d = patch_codes(H.pval, kPatchCodes);
+    if (!d.empty()) {
+      K.matrix = true;
+      std::copy(d.begin(), d.end(), K.dict.begin());
+      halves(H.pidx, H.pval, [&](double x) { return std::lower_bound(d.begin(), d.end(), x) - d.begin(); });
+    }
+  }
+  auto simple = [](const std::vector<double> &v) {
+    for (double x : v)
+      if (x != 1.0 && x != 0.5 && x != 0.0) return false;
+    return true;
+  };
+  auto code = [](double x) { return x == 1.0 ? 0 : x == 0.5 ? 1 : 2; };
+  int most = 0;
+  for (int c : H.ucol) most = std::max(most, c);
+  if (simple(H.uval) && simple(H.rval) && most < 1 << 28) {
+    K.transfer = true;
+    for (size_t e = 0; e < H.ucol.size(); ++e) H.ucol[e] = (int)((uint32_t)H.ucol[e] | (uint32_t)code(H.uval[e]) << 28);
+    halves(H.ridx, H.rval, code);
+  }
+  return K;
+}
+
+// device arrays of a level's patches, values in precision T
+template <class T>
+struct PatchView {
+  const PatchHead *head;
+  const int *gidx;
+  const uint32_t *pidx;
+  const T *pval;  // values; the dictionary where they are coded
+  const int *ugidx, *ucell, *ucol;
+  const T *uval;
+  const int *roff, *rrow;
+  const uint32_t *ridx;
+  const T *rval;
+};
+
+struct DPatch {
+  int np = 0;
+  bool fused = false;  // `down` restricts (else it writes the residual)
+  bool mcode = false, tcode = false;  // matrix entries, transfer entries coded
+  int cells = 0;       // LDS cells of the largest patch
+  PatchHead *head = nullptr;
+  int *gidx = nullptr, *ugidx = nullptr, *ucell = nullptr, *ucol = nullptr, *roff = nullptr, *rrow = nullptr;
+  uint32_t *pidx = nullptr, *ridx = nullptr;
+  double *pval64 = nullptr, *uval64 = nullptr, *rval64 = nullptr;
+  float *pval32 = nullptr, *uval32 = nullptr, *rval32 = nullptr;
+  int64_t npair = 0, nu = 0, nr = 0, rows = 0, nstart = 0, ncoarse = 0;  // stored pairs, entries, rows
+  template <class T>
+  PatchView<T> view() const {
+    PatchView<T> v{head, gidx, pidx, nullptr, ugidx, ucell, ucol, nullptr, roff, rrow, ridx, nullptr};
+    if constexpr (sizeof(T) == 8) {
+      v.pval = pval64;
+      v.uval = uval64;
+      v.rval = rval64;
+    } else {
+      v.pval = pval32;
+      v.uval = uval32;
+      v.rval = rval32;
+    }
+    return v;
+  }
+};
+
+static __global__ __launch_bounds__(BS) void k_patch_round(int64_t n, const double *__restrict__ a,
+                                                           float *__restrict__ b) {
+  const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
+  if (i < n) b[i] = (float)a[i];
+}
+
+static inline void patch_round(int64_t n, const double *a, float *b) {
+  if (n > 0) hipLaunchKernelGGL(k_patch_round, dim3(nblk(n)), dim3(BS), 0, nullptr, n, a, b);
+}
+
+// matrix entries of a level: coded (dictionary) or plain values, in both precisions
+template <class Up, class Room>
+static void patch_commit_matrix(const PatchHost &H, const PatchCodes &K, DPatch &D, Up &&up, Room &&room32) {
+  D.mcode = K.matrix;
+  D.pidx = up(H.pidx);
+  D.npair = (int64_t)H.pidx.size();
+  const std::vector<double> &v = K.matrix ? K.dict : H.pval;
+  D.pval64 = up(v);
+  D.pval32 = room32((int64_t)v.size());
+  patch_round((int64_t)v.size(), D.pval64, D.pval32);
+}
+
+// uploads a level's patches; up(vector) -> device copy, room32(n) -> n floats
+template <class Up, class Room>
+static void patch_commit(const PatchHost &H, const PatchCodes &K, DPatch &D, bool fused, Up &&up, Room &&room32) {
+  D.np = (int)H.head.size();
+  D.fused = fused;
+  if (!D.np) return;
+  for (const PatchHead &h : H.head) D.cells = std::max(D.cells, 64 * h.ncs);
+  patch_commit_matrix(H, K, D, up, room32);
+  D.head = up(H.head);
+  D.gidx = up(H.gidx);
+  D.ugidx = up(H.ugidx);
+  D.ucell = up(H.ucell);
+  D.ucol = up(H.ucol);
+  D.nstart = (int64_t)H.ugidx.size();
+  D.roff = up(H.roff);
+  D.rrow = up(H.rrow);
+  D.ridx = up(H.ridx);
+  D.nu = (int64_t)H.ucol.size();
+  D.nr = (int64_t)H.ridx.size();
+  D.rows = H.rows;
+  D.ncoarse = (int64_t)H.rrow.size();
+  D.tcode = K.transfer;
+  if (D.tcode) return;
+  D.uval64 = up(H.uval);
+  D.rval64 = up(H.rval);
+  D.uval32 = room32(D.nu);
+  D.rval32 = room32(2 * D.nr);
+  patch_round(D.nu, D.uval64, D.uval32);
+  patch_round(2 * D.nr, D.rval64, D.rval32);
+}
+
+// ---------------------------------------------------------------------------
+// kernels
+// ---------------------------------------------------------------------------
+
+template <int NR, class T>
+struct alignas(sizeof(T) * NR) PVec {
+  T v[NR];
+};
+
+template <class T>
+struct alignas(2 * sizeof(T)) PPair {
+  T a, b;
+};
+
+// base[i], with the offset in 32 bits so that the address is a scalar base and one offset register (the
+// plan keeps every array of a level below 4 GiB)
+template <class X>
+__device__ __forceinline__ X at32(const X *base, uint32_t i) {
+  return *reinterpret_cast<const X *>(reinterpret_cast<const char *>(base) + (size_t)(uint32_t)(i * (uint32_t)sizeof(X)));
+}
+template <class X>
+__device__ __forceinline__ void put32(X *base, uint32_t i, const X &v) {
+  *reinterpret_cast<X *>(reinterpret_cast<char *>(base) + (size_t)(uint32_t)(i * (uint32_t)sizeof(X))) = v;
+}
+
+static constexpr uint32_t kCellMask = (1u << kPatchCellBits) - 1;
+
+// transfer value of a code
+template <class T>
+__device__ __forceinline__ T patch_weight(uint32_t code) {
+  return code == 0 ? T(1) : code == 1 ? T(0.5) : T(0);
+}
+
+// a0 += v.a x[first cell], a1 += v.b x[second cell]; UP: only cells above `above`
+template <bool UP, int NR, class T>
+__device__ __forceinline__ void pair_add(PVec<NR, T> &a0, PVec<NR, T> &a1, uint32_t id, PPair<T> v,
+                                         const PVec<NR, T> *xs, int above) {
+  const int i0 = (int)(id & kCellMask), i1 = (int)(id >> 16 & kCellMask);
+  if (UP) {
+    v.a = i0 > above ? v.a : T(0);
+    v.b = i1 > above ? v.b : T(0);
+  }
+  const PVec<NR, T> x0 = xs[i0], x1 = xs[i1];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    a0.v[r] += v.a * x0.v[r];
+    a1.v[r] += v.b * x1.v[r];
+  }
+}
+
+// matrix entries of a wave's slices in registers: kPatchPairs pairs of each row (longer rows read the
+// rest again in every pass), with their values unless MC (coded: looked up in `dict`, in LDS)
+template <class T, bool MC>
+struct PatchRows {
+  uint32_t id[kPatchSlots][kPatchPairs];
+  PPair<T> v[kPatchSlots][kPatchPairs];
+  int o[kPatchSlots], w[kPatchSlots];
+
+  __device__ __forceinline__ PPair<T> value(const PatchView<T> &V, uint32_t e, uint32_t c, const T *dict) const {
+    if constexpr (MC)
+      return PPair<T>{dict[c >> kPatchCellBits & 15u], dict[c >> (16 + kPatchCellBits)]};
+    else
+      return at32(reinterpret_cast<const PPair<T> *>(V.pval), e);
+  }
+
+  template <int J0, int J1>
+  __device__ __forceinline__ void load(const PatchView<T> &V, const PatchHead &h, int wv, uint32_t lane) {
+#pragma unroll
+    for (int j = J0; j < J1; ++j) {
+      const int k = j * kPatchWaves + wv;
+      o[j] = h.poff[k];
+      w[j] = h.poff[k + 1] - o[j];
+      const uint32_t *ip = V.pidx + (size_t)o[j] * 64;
+      const PPair<T> *vp = reinterpret_cast<const PPair<T> *>(V.pval) + (size_t)o[j] * 64;
+#pragma unroll
+      for (int q = 0; q < kPatchPairs; ++q)
+        if (q < w[j]) {
+          id[j][q] = at32(ip + q * 64, lane);
+          if constexpr (!MC) v[j][q] = at32(vp + q * 64, lane);
+        }
+    }
+  }
+  // values of the codes (after the dictionary is in LDS)
+  __device__ __forceinline__ void decode(const PatchView<T> &V, const T *dict) {
+    if constexpr (MC) {
+#pragma unroll
+      for (int j = 0; j < kPatchSlots; ++j)
+#pragma unroll
+        for (int q = 0; q < kPatchPairs; ++q)
+          if (q < w[j]) v[j][q] = value(V, 0, id[j][q], dict);
+    }
+  }
+
+  // the first W pairs: every LDS read before the first product
+  template <int W, bool UP, int NR>
+  __device__ __forceinline__ void add_w(PVec<NR, T> &a0, PVec<NR, T> &a1, int j, const PVec<NR, T> *xs,
+                                        int above) const {
+    PVec<NR, T> x0[W], x1[W];
+    int i0[W], i1[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+      // unpacked here, not kept unpacked across the passes (32 more registers)
+      uint32_t c = id[j][q];
+      asm volatile("" : "+v"(c));
+      i0[q] = (int)(c & kCellMask);
+      i1[q] = (int)(c >> 16 & kCellMask);
+      x0[q] = xs[i0[q]];
+      x1[q] = xs[i1[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+      PPair<T> m = v[j][q];
+      if (UP) {
+        m.a = i0[q] > above ? m.a : T(0);
+        m.b = i1[q] > above ? m.b : T(0);
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        a0.v[r] += m.a * x0[q].v[r];
+        a1.v[r] += m.b * x1[q].v[r];
+      }
+    }
+  }
+
+  template <bool UP, int NR>
+  __device__ __forceinline__ PVec<NR, T> dot(const PatchView<T> &V, int j, const PVec<NR, T> *xs, const T *dict,
+                                             uint32_t lane, int above = 0) const {
+    PVec<NR, T> a0, a1;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) a0.v[r] = a1.v[r] = T(0);
+    switch (w[j] < kPatchPairs ? w[j] : kPatchPairs) {
+      case 0: break;
+      case 1: add_w<1, UP, NR>(a0, a1, j, xs, above); break;
+      case 2: add_w<2, UP, NR>(a0, a1, j, xs, above); break;
+      case 3: add_w<3, UP, NR>(a0, a1, j, xs, above); break;
+      default: add_w<4, UP, NR>(a0, a1, j, xs, above); break;
+    }
+    for (int q = kPatchPairs; q < w[j]; ++q) {
+      const uint32_t e = (uint32_t)(o[j] + q) * 64 + lane;
+      const uint32_t c = at32(V.pidx, e);
+      pair_add<UP, NR, T>(a0, a1, c, value(V, e, c, dict), xs, above);
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) a0.v[r] += a1.v[r];
+    return a0;
+  }
+};
+
+__device__ __forceinline__ int patch_row(int g) { return g < 0 ? 0 : g & (kPatchHalo - 1); }
+__device__ __forceinline__ bool patch_owns(int g) { return g >= 0 && !(g & kPatchHalo); }
+
+// coarse slices of a wave loaded before the sweeps (coded transfers)
+template <class T>
+constexpr int kPatchCoarse = sizeof(T) == 8 ? 1 : 2;
+
+// Forward sweeps from zero on b (BT: its type; FP64 on the original grid in both precisions), x on the
+// own rows, and either the restricted residual bc on the coarse rows owned (fused) or the residual r.
+template <int NR, class T, class BT, bool MC, bool TC>
+__global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_patch_down(
+    PatchView<T> V, int cells, int C, int nu, int fused, const BT *__restrict__ b, const T *__restrict__ dg,
+    T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc) {
+  extern __shared__ __align__(32) unsigned char patch_lds[];
+  __shared__ T dict[kPatchCodes];
+  using X = PVec<NR, T>;
+  X *xs = reinterpret_cast<X *>(patch_lds);
+  const uint32_t lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int patch = xcd_block();
+  int g[kPatchSlots];
+#pragma unroll
+  for (int j = 0; j < kPatchSlots; ++j)
+    g[j] = at32(V.gidx + (size_t)(patch * kPatchSlices + j * kPatchWaves + wv) * 64, lane);
+  const PatchHead &h = V.head[patch];
+  const int ns = h.ns, nco = fused ? h.nco : 0;
+  int turn[kPatchSlots];  // colour of each slice, in scalar registers: the passes read no memory but LDS
+#pragma unroll
+  for (int j = 0; j < kPatchSlots; ++j) turn[j] = h.sc[j] >> 4 * wv & 15;
+  if (MC && threadIdx.x < kPatchCodes) dict[threadIdx.x] = V.pval[threadIdx.x];
+  PatchRows<T, MC> A;
+  A.template load<0, kPatchSlots>(V, h, wv, lane);
+  X *bs = xs + cells;
+  T *ds = reinterpret_cast<T *>(bs + 64 * kPatchSlices);
+  T iv[kPatchSlots];
+  {
+    X bv[kPatchSlots];
+    T dv[kPatchSlots];
+#pragma unroll
+    for (int j = 0; j < kPatchSlots; ++j) {
+      const int i = patch_row(g[j]);
+      const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b), i);
+#pragma unroll
+      for (int q = 0; q < NR; ++q) bv[j].v[q] = (T)t.v[q];
+      dv[j] = at32(dg, i);
+    }
+    // colour 0 of the first sweep; every other cell starts from zero
+#pragma unroll
+    for (int j = 0; j < kPatchSlots; ++j) {
+      const int k = j * kPatchWaves + wv;
+      if (k >= ns) continue;
+      iv[j] = T(1) / dv[j];
+      bs[k * 64 + lane] = bv[j];
+      ds[k * 64 + lane] = dv[j];
+      X o;
+#pragma unroll
+      for (int q = 0; q < NR; ++q) o.v[q] = turn[j] == 0 ? bv[j].v[q] * iv[j] : T(0);
+      xs[k * 64 + lane] = o;
+    }
+    for (int k = ns + wv; k < h.ncs; k += kPatchWaves) {
+      X o;
+#pragma unroll
+      for (int q = 0; q < NR; ++q) o.v[q] = T(0);
+      xs[k * 64 + lane] = o;
+    }
+  }
+  // coarse rows of the restriction: their loads are in flight during the sweeps
+  int crow[kPatchCoarse<T>], co[kPatchCoarse<T>], cw[kPatchCoarse<T>];
+  uint32_t cid[kPatchCoarse<T>][kPatchPairs];
+  if (TC) {
+#pragma unroll
+    for (int j = 0; j < kPatchCoarse<T>; ++j) {
+      const int k = j * kPatchWaves + wv;
+      co[j] = cw[j] = 0;
+      crow[j] = -1;
+      static_assert(kPatchCoarse<T> * kPatchWaves <= kPatchHeadCoarse, "offsets in the head");
+      if (k < nco) {
+        co[j] = h.roff[k];
+        cw[j] = h.roff[k + 1] - co[j];
+        crow[j] = at32(V.rrow + (size_t)(h.coarse0 + k) * 64, lane);
+      }
+#pragma unroll
+      for (int q = 0; q < kPatchPairs; ++q)
+        if (q < cw[j]) cid[j][q] = at32(V.ridx + (size_t)(co[j] + q) * 64, lane);
+    }
+  }
+  __syncthreads();
+  A.decode(V, dict);
+  for (int s = 0; s < nu; ++s)
+    for (int c = s == 0 ? 1 : 0; c < C; ++c) {
+#pragma unroll
+      for (int j = 0; j < kPatchSlots; ++j) {
+        const int k = j * kPatchWaves + wv;
+        if (turn[j] == c) {
+          X a = A.template dot<false, NR>(V, j, xs, dict, lane);
+#pragma unroll
+          for (int q = 0; q < NR; ++q) a.v[q] = (bs[k * 64 + lane].v[q] - a.v[q]) * iv[j];
+          xs[k * 64 + lane] = a;
+        }
+      }
+      __syncthreads();
+    }
+  // x out; residual in b's place (zero on the last colour: its pass came last)
+#pragma unroll
+  for (int j = 0; j < kPatchSlots; ++j) {
+    const int k = j * kPatchWaves + wv;
+    if (k >= ns) continue;
+    const X xi = xs[k * 64 + lane];
+    if (patch_owns(g[j])) put32(reinterpret_cast<X *>(x), g[j], xi);
+    X rv;
+    if (turn[j] == C - 1) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) rv.v[q] = T(0);
+    } else if (nu == 1) {  // after a single sweep from zero only the later colours' terms remain
+      rv = A.template dot<true, NR>(V, j, xs, dict, lane, k * 64 + lane);
+#pragma unroll
+      for (int q = 0; q < NR; ++q) rv.v[q] = -rv.v[q];
+    } else {
+      rv = A.template dot<false, NR>(V, j, xs, dict, lane);
+      const X bi = bs[k * 64 + lane];
+      const T d = ds[k * 64 + lane];
+#pragma unroll
+      for (int q = 0; q < NR; ++q) rv.v[q] = bi.v[q] - d * xi.v[q] - rv.v[q];
+    }
+    bs[k * 64 + lane] = rv;
+    if (!fused && patch_owns(g[j])) put32(reinterpret_cast<X *>(r), g[j], rv);
+  }
+  if (!fused) return;
+  __syncthreads();
+  auto add = [&](X &a0, X &a1, uint32_t id) {
+    const PPair<T> v{patch_weight<T>(id >> kPatchCellBits & 15u), patch_weight<T>(id >> (16 + kPatchCellBits))};
+    pair_add<false, NR, T>(a0, a1, id, v, bs, 0);
+  };
+  auto put = [&](int row, X a0, const X &a1) {
+    if (row < 0) return;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) a0.v[q] += a1.v[q];
+    put32(reinterpret_cast<X *>(bc), row, a0);
+  };
+  int k = wv;
+  if (TC) {
+#pragma unroll
+    for (int j = 0; j < kPatchCoarse<T>; ++j, k += kPatchWaves)
+      if (k < nco) {
+        X a0, a1;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) a0.v[q] = a1.v[q] = T(0);
+#pragma unroll
+        for (int q = 0; q < kPatchPairs; ++q)
+          if (q < cw[j]) add(a0, a1, cid[j][q]);
+        for (int q = kPatchPairs; q < cw[j]; ++q) add(a0, a1, at32(V.ridx + (size_t)(co[j] + q) * 64, lane));
+        put(crow[j], a0, a1);
+      }
+  }
+  for (; k < nco; k += kPatchWaves) {
+    const int row = at32(V.rrow + (size_t)(h.coarse0 + k) * 64, lane);
+    const int o = V.roff[h.coarse0 + k], w = V.roff[h.coarse0 + k + 1] - o;
+    X a0, a1;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) a0.v[q] = a1.v[q] = T(0);
+    for (int q = 0; q < w; q += 4) {
+      uint32_t ids[4];
+      PPair<T> vs[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (q + t < w) {
+          ids[t] = at32(V.ridx + (size_t)(o + q + t) * 64, lane);
+          if constexpr (!TC)
+            vs[t] = at32(reinterpret_cast<const PPair<T> *>(V.rval) + (size_t)(o + q + t) * 64, lane);
+        }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (q + t < w) {
+          if constexpr (TC)
+            add(a0, a1, ids[t]);
+          else
+            pair_add<false, NR, T>(a0, a1, ids[t], vs[t], bs, 0);
+        }
+    }
+    put(row, a0, a1);
+  }
+}
+
+// Backward sweeps on b from x + P e, result in xo on the own rows (other patches still read x).
+template <int NR, class T, class BT, bool MC, bool TC>
+__global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC) ? 2 : 4) void k_patch_up(
+    PatchView<T> V, int cells, int C, int nu, const BT *__restrict__ b, const T *__restrict__ id, const T *__restrict__ x,
+    const T *__restrict__ e, T *__restrict__ xo) {
+  extern __shared__ __align__(32) unsigned char patch_lds[];
+  __shared__ T dict[kPatchCodes];
+  using X = PVec<NR, T>;
+  X *xs = reinterpret_cast<X *>(patch_lds);
+  const uint32_t lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int patch = xcd_block();
+  int g[kPatchSlots];
+#pragma unroll
+  for (int j = 0; j < kPatchSlots; ++j)
+    g[j] = at32(V.gidx + (size_t)(patch * kPatchSlices + j * kPatchWaves + wv) * 64, lane);
+  const PatchHead &h = V.head[patch];
+  const int ns = h.ns, nst = h.nst;
+  int turn[kPatchSlots];
+#pragma unroll
+  for (int j = 0; j < kPatchSlots; ++j) turn[j] = h.sc[j] >> 4 * wv & 15;
+  if (MC && threadIdx.x < kPatchCodes) dict[threadIdx.x] = V.pval[threadIdx.x];
+  X *bs = xs + cells;
+  T iv[kPatchSlots];
+  PatchRows<T, MC> A;
+  // with 64-bit values the second half of the matrix rows is loaded after the prolongation: both at
+  // once do not fit in the registers of two blocks per CU
+  constexpr int early = sizeof(T) == 8 && TC ? kPatchSlots / 2 : kPatchSlots;
+  auto column = [](int c) { return TC ? c & 0xfffffff : c; };
+  // Start rows, UB slices of a wave at a time: all their loads, then all gathers, then the sums. Coded
+  // rows hold at most two entries; others go PW entries at a time.
+  constexpr int PW = TC ? 2 : 8, UB = TC ? 3 : 2;
+  auto start = [&](int k0, auto &&between) {
+    int ug[UB], cell[UB], o[UB], w[UB], uc[UB][PW];
+    T uv[UB][PW];
+    X a[UB], ev[UB][PW];
+#pragma unroll
+    for (int i = 0; i < UB; ++i) {
+      const int k = k0 + i * kPatchWaves;
+      ug[i] = -1;
+      o[i] = w[i] = 0;
+      if (k < nst) {
+        ug[i] = at32(V.ugidx + (size_t)(h.start0 + k) * 64, lane);
+        cell[i] = at32(V.ucell + (size_t)(h.start0 + k) * 64, lane);
+        o[i] = h.uoff[k];
+        w[i] = h.uoff[k + 1] - o[i];
+      }
+#pragma unroll
+      for (int q = 0; q < PW; ++q)
+        if (q < w[i]) {
+          uc[i][q] = at32(V.ucol + (size_t)(o[i] + q) * 64, lane);
+          if constexpr (!TC) uv[i][q] = at32(V.uval + (size_t)(o[i] + q) * 64, lane);
+        }
+    }
+    between();
+#pragma unroll
+    for (int i = 0; i < UB; ++i) {
+      if (k0 + i * kPatchWaves < nst) a[i] = at32(reinterpret_cast<const X *>(x), ug[i] < 0 ? 0 : ug[i]);
+#pragma unroll
+      for (int q = 0; q < PW; ++q)
+        if (q < w[i]) ev[i][q] = at32(reinterpret_cast<const X *>(e), column(uc[i][q]));
+    }
+#pragma unroll
+    for (int i = 0; i < UB; ++i) {
+#pragma unroll
+      for (int q = 0; q < PW; ++q)
+        if (q < w[i]) {
+          const T v = TC ? patch_weight<T>((uint32_t)uc[i][q] >> 28) : uv[i][q];
+#pragma unroll
+          for (int m = 0; m < NR; ++m) a[i].v[m] += v * ev[i][q].v[m];
+        }
+      for (int t = PW; t < w[i]; t += PW) {
+        int c[PW];
+        T v[PW];
+        X ex[PW];
+#pragma unroll
+        for (int q = 0; q < PW; ++q)
+          if (t + q < w[i]) {
+            c[q] = at32(V.ucol + (size_t)(o[i] + t + q) * 64, lane);
+            if constexpr (!TC) v[q] = at32(V.uval + (size_t)(o[i] + t + q) * 64, lane);
+          }
+#pragma unroll
+        for (int q = 0; q < PW; ++q)
+          if (t + q < w[i]) ex[q] = at32(reinterpret_cast<const X *>(e), column(c[q]));
+#pragma unroll
+        for (int q = 0; q < PW; ++q)
+          if (t + q < w[i]) {
+            const T f = TC ? patch_weight<T>((uint32_t)c[q] >> 28) : v[q];
+#pragma unroll
+            for (int m = 0; m < NR; ++m) a[i].v[m] += f * ex[q].v[m];
+          }
+      }
+      if (ug[i] >= 0) xs[cell[i]] = a[i];
+    }
+  };
+  // right-hand side and diagonal of the rows: their gathers fly with the first start rows'
+  X bv[kPatchSlots];
+  start(wv, [&] {
+#pragma unroll
+    for (int j = 0; j < kPatchSlots; ++j) {
+      const int i = patch_row(g[j]);
+      const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b), i);
+#pragma unroll
+      for (int q = 0; q < NR; ++q) bv[j].v[q] = (T)t.v[q];
+      iv[j] = at32(id, i);
+    }
+    A.template load<0, early>(V, h, wv, lane);
+  });
+#pragma unroll
+  for (int j = 0; j < kPatchSlots; ++j)
+    if (j * kPatchWaves + wv < ns) bs[(j * kPatchWaves + wv) * 64 + lane] = bv[j];
+  for (int k = wv + UB * kPatchWaves; k < nst; k += UB * kPatchWaves) start(k, [] {});
+  A.template load<early, kPatchSlots>(V, h, wv, lane);
+  __syncthreads();
+  A.decode(V, dict);
+  for (int s = 0; s < nu; ++s)
+    for (int c = C - 1; c >= 0; --c) {
+#pragma unroll
+      for (int j = 0; j < kPatchSlots; ++j) {
+        const int k = j * kPatchWaves + wv;
+        if (turn[j] == c) {
+          X y = A.template dot<false, NR>(V, j, xs, dict, lane);
+#pragma unroll
+          for (int q = 0; q < NR; ++q) y.v[q] = (bs[k * 64 + lane].v[q] - y.v[q]) * iv[j];
+          xs[k * 64 + lane] = y;
+          // the last sweep's value is final
+          if (s == nu - 1 && patch_owns(g[j])) put32(reinterpret_cast<X *>(xo), g[j], y);
+        }
+      }
+      __syncthreads();
+    }
+}
+
+// launch of a patch kernel, one block per patch; LDS: x on the cells, b (then the residual) and the
+// diagonal on the rows, `vec` and `scalar` bytes each
+template <class K, class... A>
+static void launch_patch(K kernel, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
+                         hipEvent_t e1, A... args) {
+  const size_t lds = (size_t)D.cells * vec + 64 * kPatchSlices * (vec + scalar);
+  if (e0) {
+    hipExtLaunchKernelGGL(kernel, dim3(D.np), dim3(kPatchThreads), lds, s, e0, e1, 0, args...);
+    HIPCHECK(hipGetLastError());
+  } else {
+    hipLaunchKernelGGL(kernel, dim3(D.np), dim3(kPatchThreads), lds, s, args...);
+  }
+}
+
+// calls f(matrix coded, transfers coded) with the level's variant as compile-time constants
+template <class F>
+static void with_codes(const DPatch &D, F &&f) {
+  if (D.mcode && D.tcode)
+    f(std::true_type(), std::true_type());
+  else if (D.tcode)
+    f(std::false_type(), std::true_type());
+  else if (D.mcode)
+    f(std::true_type(), std::false_type());
+  else
+    f(std::false_type(), std::false_type());
+}
+
+}  // namespace asmg
