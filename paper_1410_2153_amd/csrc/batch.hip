@@ -26,6 +26,7 @@
 #include "batch.hpp"
 #include "common.hpp"
 #include "host_parallel.hpp"
+#include "patch.hpp"
 #include "trace.hpp"
 
 namespace asmg {
@@ -527,7 +528,8 @@ __global__ __launch_bounds__(BS) void kb_fin_spmv(const int *__restrict__ m_b0, 
 // u += alpha p, r -= alpha q per system; partials of ||r||^2. The same pass runs the first
 // colour pass of the next B_co on the new r in precision T: xf = r * id0 on colour 0 (the other
 // rows of xf are written by the sweep's later passes), and in FP32 also bf = (float) r.
-template <int NR, class T>
+// FIRST false: patches on the original grids, that pass is theirs.
+template <int NR, class T, bool FIRST>
 __global__ __launch_bounds__(BS) void kb_cg_axpy(const int *__restrict__ ew_m, const int *__restrict__ ew_r0,
                                                  const int *__restrict__ ew_r1, double *__restrict__ u,
                                                  double *__restrict__ r, const double *__restrict__ p,
@@ -544,7 +546,7 @@ __global__ __launch_bounds__(BS) void kb_cg_axpy(const int *__restrict__ ew_m, c
   if (act) {
     const V al = reinterpret_cast<const V *>(c.alpha)[m];
     const VecR<NR, int> dn = reinterpret_cast<const VecR<NR, int> *>(c.dn)[m];
-    const T d = id0[row];
+    const T d = FIRST ? id0[row] : T(0);
     V uv = reinterpret_cast<const V *>(u)[row];
     V rv = reinterpret_cast<const V *>(r)[row];
     const V pv = reinterpret_cast<const V *>(p)[row];
@@ -562,8 +564,8 @@ __global__ __launch_bounds__(BS) void kb_cg_axpy(const int *__restrict__ ew_m, c
     }
     reinterpret_cast<V *>(u)[row] = uv;
     reinterpret_cast<V *>(r)[row] = rv;
-    if constexpr (sizeof(T) == 4) reinterpret_cast<VecR<NR, T> *>(bf)[row] = bo;
-    if (d != T(0)) reinterpret_cast<VecR<NR, T> *>(xf)[row] = xo;  // colour 0 only, as kb_first
+    if constexpr (FIRST && sizeof(T) == 4) reinterpret_cast<VecR<NR, T> *>(bf)[row] = bo;
+    if (FIRST && d != T(0)) reinterpret_cast<VecR<NR, T> *>(xf)[row] = xo;  // colour 0 only, as kb_first
   }
   bwrite<NR>(v, partials);
 }
@@ -787,6 +789,9 @@ struct BLevel {
   int64_t *bt_moff = nullptr;
   double *inv64 = nullptr;
   float *inv32 = nullptr;
+  DPatch pt;             // overlapped patches of the smoothing rows (np = 0: colour passes one by one)
+  int C = 0;             // colours
+  int64_t nnz = 0;       // off-diagonal entries of the smoothing rows (byte model)
   int bottom_waves = 0;
   double bt_entries = 0, bt_rows = 0;  // byte model: inverse entries, rows of the bottom meshes
 };
@@ -1364,10 +1369,90 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         if (Cm == Cf) zero[r] = 1;
       }
     }
-    // tasks: 0-2 the original grids' smoothing, product and residual images, 3-4 Pi and Pi^T,
-    // 5..K+5 the auxiliary levels, then the prolongations
+    // ---- matrices of the auxiliary levels and prolongations (level k+1 -> k for the smoothing meshes
+    // of level k), and the transposes
+    std::vector<HMat> Pm(K), PTm(K);
+    HMat PiT;
+    std::vector<std::vector<uint8_t>> colour(K);  // colour per smoothing row
+    host_parallel(0, 2 * K + 1, [&](int t) {
+      if (t == 2 * K) {
+        PiT = htranspose(Pi);
+      } else if (t < K) {
+        const int k = t;
+        BLevel &L = dv->aux[k];
+        LevelImage &X = aux_img[k];
+        for (size_t i = 0; i < smooth_m[k].size(); ++i) {
+          const int m = smooth_m[k][i];
+          const int l = H[m]->J - k;
+          append_rows(X.A, H[m]->Al.at(l), lev[m][k].perm, &lev[m][k].iperm, L.off[i], true, &X.diag);
+          const auto &co = lev[m][k].coff;
+          L.C = std::max(L.C, (int)co.size() - 1);
+          for (size_t c = 0; c + 1 < co.size(); ++c)
+            colour[k].insert(colour[k].end(), co[c + 1] - co[c], (uint8_t)std::min<size_t>(c, 255));
+          const int nl = (int)H[m]->Al.at(l).nrows;
+          for (int r = 0; r < nl; ++r) X.c0flag.push_back(r < co[1]);
+        }
+        X.A.ncols = L.nsmooth;
+        L.nnz = (int64_t)X.A.ci.size();
+      } else {
+        const int k = t - K;
+        BLevel &Lc = dv->aux[k + 1];
+        HMat &P = Pm[k];
+        for (int m : smooth_m[k]) {
+          const int D = H[m]->J - H[m]->lc;
+          const int l = H[m]->J - k;
+          const size_t j = std::find(Lc.mesh.begin(), Lc.mesh.end(), m) - Lc.mesh.begin();
+          const std::vector<int> *cmap = (D > k + 1) ? &lev[m][k + 1].iperm : nullptr;
+          append_rows(P, H[m]->P.at(l), lev[m][k].perm, cmap, Lc.off[j], false, nullptr);
+        }
+        P.ncols = Lc.nrows;
+        PTm[k] = htranspose(P);
+      }
+    });
+    F.C = Cf;
+    F.nnz = (int64_t)fine_img.A.ci.size();
+    // the level's smoothing rows (the first P.nrows of the merged level) in each mesh's own numbering
+    auto smooth_order = [&](int k) {
+      std::vector<int> nat = natural_rows(dv->aux[k], k);
+      nat.erase(std::remove_if(nat.begin(), nat.end(), [&](int r) { return r >= dv->aux[k].nsmooth; }), nat.end());
+      return nat;
+    };
+    // ---- patches: job 0 the original grids, job k + 1 the auxiliary level k. The meshes are blocks of
+    // the merged matrix, so a patch may hold rows of several small meshes.
+    std::vector<PatchJob<HMat>> jobs(K + 1);
+    host_parallel(0, K + 1, [&](int i) {
+      PatchSource<HMat> &S = jobs[i].src;
+      BLevel &L = i == 0 ? F : dv->aux[i - 1];
+      S.A = i == 0 ? &fine_img.A : &aux_img[i - 1].A;
+      S.n = L.nsmooth;
+      S.C = L.C;
+      S.nu = i == 0 ? dv->nu_fine : dv->nu_aux;
+      S.P = i == 0 ? &Pi : &Pm[i - 1];
+      S.R = i == 0 ? &PiT : &PTm[i - 1];
+      S.ncoarse = dv->aux[i].nrows;
+      if (i == 0) {
+        S.order = mo;
+        for (int m = 0; m < nm; ++m) {
+          const auto &co = fine[m].coff;
+          for (size_t c = 0; c + 1 < co.size(); ++c)
+            S.col.insert(S.col.end(), co[c + 1] - co[c], (uint8_t)std::min<size_t>(c, 255));
+        }
+      } else {
+        S.order = smooth_order(i - 1);
+        S.col = colour[i - 1];
+      }
+      S.prepare();
+      jobs[i].cuts = patch_plan(S);
+    });
+    jobs[0].code_matrix = false;  // values of the mesh's own geometry
+    patch_build(0, jobs);
+    auto patched = [&](int i) { return !jobs[i].cuts.empty(); };
+    // ---- sliced ELL images: the product of the original grids, and what has no patches. Tasks: 0-2 the
+    // original grids' smoothing, product and residual images, 3-4 Pi and Pi^T, 5..K+4 the auxiliary
+    // levels, K+5 the bottom inverses, then the prolongations
     host_parallel(0, 2 * K + 6, [&](int t) {
       if (t == 0) {
+        if (patched(0)) return;
         LevelImage &X = fine_img;
         // Gauss-Seidel passes: group c = colour c of every mesh
         Groups groups(Cf);
@@ -1387,6 +1472,7 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         for (int m = 0; m < nm; ++m) mg[m].push_back({r0[m], r1[m]});
         bsell_host(X.A, mg, true, X.cg, &mo);
       } else if (t == 2) {
+        if (patched(0)) return;
         // residual after a single forward sweep from zero: r = U x with U the later colours' entries
         // of each row (columns above the row: each mesh numbers its rows colour by colour), negated;
         // the rows that have such entries, in Morton order. The other rows' r stays zero.
@@ -1414,36 +1500,30 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         X.up.nrows = (int)uo.size();  // byte model: rows written, distinct x entries gathered
         X.up.ncols = ucols;
       } else if (t == 3) {
+        if (patched(0)) return;
         const std::vector<int> oPi = keep_rows(mo, last);
         bsell_host(Pi, {{{0, (int)oPi.size()}}}, false, pi_img, &oPi);
         transfer_stats(Pi, oPi, pi_img);
       } else if (t == 4) {
-        const HMat PiT = drop_cols(htranspose(Pi), zero);
+        if (patched(0)) return;
+        const HMat R = drop_cols(PiT, zero);
         const std::vector<int> oPiT = natural_rows(L0, 0);
-        bsell_host(PiT, {{{0, PiT.nrows}}}, false, pit_img, &oPiT);
-        transfer_stats(PiT, oPiT, pit_img);
+        bsell_host(R, {{{0, R.nrows}}}, false, pit_img, &oPiT);
+        transfer_stats(R, oPiT, pit_img);
       } else if (t < K + 6) {
         const int k = t - 5;
         BLevel &L = dv->aux[k];
         LevelImage &X = aux_img[k];
-        int C = 0;
-        for (size_t i = 0; i < smooth_m[k].size(); ++i) {
-          const int m = smooth_m[k][i];
-          const int l = H[m]->J - k;
-          append_rows(X.A, H[m]->Al.at(l), lev[m][k].perm, &lev[m][k].iperm, L.off[i], true, &X.diag);
-          C = std::max(C, (int)lev[m][k].coff.size() - 1);
-          const int nl = (int)H[m]->Al.at(l).nrows;
-          for (int r = 0; r < nl; ++r) X.c0flag.push_back(r < lev[m][k].coff[1]);
+        if (k < K && !patched(k + 1)) {
+          Groups groups(L.C);
+          for (int c = 0; c < L.C; ++c)
+            for (size_t i = 0; i < smooth_m[k].size(); ++i) {
+              const auto &co = lev[smooth_m[k][i]][k].coff;
+              if (c + 1 < (int)co.size()) groups[c].push_back({L.off[i] + co[c], L.off[i] + co[c + 1]});
+            }
+          bsell_host(X.A, groups, false, X.gs);
+          group_counts(X.A, groups, X.counts);
         }
-        X.A.ncols = L.nsmooth;
-        Groups groups(C);
-        for (int c = 0; c < C; ++c)
-          for (size_t i = 0; i < smooth_m[k].size(); ++i) {
-            const auto &co = lev[smooth_m[k][i]][k].coff;
-            if (c + 1 < (int)co.size()) groups[c].push_back({L.off[i] + co[c], L.off[i] + co[c + 1]});
-          }
-        bsell_host(X.A, groups, false, X.gs);
-        group_counts(X.A, groups, X.counts);
         for (size_t i = 0; i < bottom_m[k].size(); ++i) {
           const int m = bottom_m[k][i];
           const int nc = (int)H[m]->nc;
@@ -1457,38 +1537,24 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         }
         X.inv32.assign(X.inv.begin(), X.inv.end());
       } else {
-        // prolongation P (level k+1 -> k) for the smoothing meshes of level k
         const int k = t - (K + 6);
+        if (patched(k + 1)) return;
         BLevel &L = dv->aux[k], &Lc = dv->aux[k + 1];
-        HMat P;
-        for (int m : smooth_m[k]) {
-          const int D = H[m]->J - H[m]->lc;
-          const int l = H[m]->J - k;
-          const size_t j = std::find(Lc.mesh.begin(), Lc.mesh.end(), m) - Lc.mesh.begin();
-          const std::vector<int> *cmap = (D > k + 1) ? &lev[m][k + 1].iperm : nullptr;
-          append_rows(P, H[m]->P.at(l), lev[m][k].perm, cmap, Lc.off[j], false, nullptr);
-        }
-        P.ncols = Lc.nrows;
+        const HMat &P = Pm[k];
         std::vector<uint8_t> last(P.nrows, 0), zero(P.nrows, 0);
-        int C = 0;
-        for (int m : smooth_m[k]) C = std::max(C, (int)lev[m][k].coff.size() - 1);
         for (size_t i = 0; i < smooth_m[k].size(); ++i) {
           const auto &co = lev[smooth_m[k][i]][k].coff;
           const int Cm = (int)co.size() - 1;
           if (Cm < 1) continue;
           for (int r = L.off[i] + co[Cm - 1]; r < L.off[i] + co[Cm]; ++r) {
             last[r] = 1;
-            if (Cm == C) zero[r] = 1;
+            if (Cm == L.C) zero[r] = 1;
           }
         }
-        // the level's rows in each mesh's own numbering; P has the smoothing meshes' rows only
-        // (the first P.nrows of the merged level), not those of meshes whose bottom it is
-        std::vector<int> nat = natural_rows(L, k);
-        nat.erase(std::remove_if(nat.begin(), nat.end(), [&](int r) { return r >= P.nrows; }), nat.end());
-        const std::vector<int> oP = keep_rows(nat, last), oPT = natural_rows(Lc, k + 1);
+        const std::vector<int> oP = keep_rows(smooth_order(k), last), oPT = natural_rows(Lc, k + 1);
         bsell_host(P, {{{0, (int)oP.size()}}}, false, p_img[k], &oP);
         transfer_stats(P, oP, p_img[k]);
-        const HMat PT = drop_cols(htranspose(P), zero);
+        const HMat PT = drop_cols(PTm[k], zero);
         bsell_host(PT, {{{0, PT.nrows}}}, false, pt_img[k], &oPT);
         transfer_stats(PT, oPT, pt_img[k]);
       }
@@ -1548,6 +1614,12 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
     }
     bsell_upload(dv, pi_img, dv->Pi);
     bsell_upload(dv, pit_img, dv->PiT);
+    for (int i = 0; i <= K; ++i) {
+      patch_commit(
+          jobs[i].all, jobs[i].codes, (i == 0 ? dv->fine : dv->aux[i - 1]).pt, true,
+          [&](const auto &v) { return bupload(dv, v); }, [&](int64_t n) { return balloc<float>(dv, n); });
+      jobs[i].all = PatchHost();
+    }
     // ---- gather/scatter maps: internal fine row -> user offset of (mesh, rhs 0, dof), stride n_m
     {
       const int n = dv->fine.nrows;
@@ -1671,6 +1743,19 @@ const double *bid0<double>(const BLevel &L) { return L.id0_64; }
 template <>
 const float *bid0<float>(const BLevel &L) { return L.id0_32; }
 
+// next event pair of the per-launch timing
+static void next_probe(BatchDevice *dv, double bytes, hipEvent_t &e0, hipEvent_t &e1) {
+  while (dv->probe_used + 2 > dv->probe_ev.size()) {
+    hipEvent_t p;
+    HIPCHECK(hipEventCreate(&p));
+    dv->probe_ev.push_back(p);
+  }
+  e0 = dv->probe_ev[dv->probe_used];
+  e1 = dv->probe_ev[dv->probe_used + 1];
+  dv->probe_used += 2;
+  dv->probe_bytes.push_back(bytes);
+}
+
 // One slice-kernel launch site of B_co: launch(threads, xcd, e0, e1) enqueues the kernel over
 // `nslices` slices (launch_timed: with events, they are stamped with the kernel's own start and
 // end). While tuning, the site runs the candidate shape under trial with its pair of events, so
@@ -1687,17 +1772,7 @@ static void slice_launch(BatchDevice *dv, int nslices, hipStream_t s, F &&launch
   auto sh = site < (int)tab.size() ? tab[site] : kShapes[0];
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (dv->probe && probe_bytes >= 0.0) {
-    if (dv->probe_used + 2 > dv->probe_ev.size()) {
-      hipEvent_t p0, p1;
-      HIPCHECK(hipEventCreate(&p0));
-      HIPCHECK(hipEventCreate(&p1));
-      dv->probe_ev.push_back(p0);
-      dv->probe_ev.push_back(p1);
-    }
-    e0 = dv->probe_ev[dv->probe_used];
-    e1 = dv->probe_ev[dv->probe_used + 1];
-    dv->probe_used += 2;
-    dv->probe_bytes.push_back(probe_bytes);
+    next_probe(dv, probe_bytes, e0, e1);
   } else if (dv->tuning) {
     while ((int)dv->tune_ev.size() < 2 * (site + 1)) {
       hipEvent_t e;
@@ -1714,6 +1789,61 @@ static void slice_launch(BatchDevice *dv, int nslices, hipStream_t s, F &&launch
   launch(sh.threads, sh.xcd, sh.var, e0, e1);
 }
 
+
+// V-cycle result of a level: patches write it beside x, which their neighbours still read, in r
+template <class T>
+static T *b_result(BLevel &L) { return L.pt.np ? BV<T>::r(L) : BV<T>::x(L); }
+
+// One patch launch; it stands for `passes` launch sites of the pass-by-pass path, whose entries in the
+// table of launch shapes it leaves at the default.
+template <class F>
+static void patch_launch(BatchDevice *dv, int passes, double bytes, F &&launch) {
+  dv->site += passes;
+  if (dv->tuning) {
+    dv->tune_live = std::max(dv->tune_live, dv->site);
+    dv->tune_has.resize(std::max<size_t>(dv->tune_has.size(), dv->site), 0);
+  }
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (dv->probe) next_probe(dv, bytes, e0, e1);
+  if (dv->count_bytes) dv->bytes += bytes;
+  launch(e0, e1);
+}
+
+// forward sweeps from zero on b, residual, restriction into the right-hand side of Lc, and the first
+// colour pass there where the passes of Lc run one by one
+template <int NR, class T, class BT>
+static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &Lc, hipStream_t s) {
+  const DPatch &D = L.pt;
+  const double sz = sizeof(T), n = L.nsmooth;
+  const double by = (double)L.nnz * (sz + 2) + n * (4 + NR * sizeof(BT) + sz + NR * sz) + (double)D.nr * 2 * (sz + 2) +
+                    (double)D.ncoarse * (4 + NR * sz);
+  patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
+    with_codes(D, [&](auto mc, auto tc) {
+      launch_patch(k_patch_down<NR, T, BT, decltype(mc)::value, decltype(tc)::value>, D, NR * sizeof(T), sizeof(T), s,
+                   e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, 1, b, BV<T>::dg(L), BV<T>::x(L), (T *)nullptr,
+                   BV<T>::b(Lc), (const int *)nullptr);
+    });
+  });
+  if (!Lc.pt.np && Lc.nsmooth > 0)
+    hipLaunchKernelGGL((kb_first<NR, T>), dim3(nblk(Lc.nsmooth)), dim3(BS), 0, s, Lc.nsmooth,
+                       (const T *)BV<T>::b(Lc), bid0<T>(Lc), BV<T>::x(Lc));
+}
+
+// x + P e with the result e of Lc, then backward sweeps on b, into b_result(L)
+template <int NR, class T, class BT>
+static void patch_up(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &Lc, hipStream_t s) {
+  const DPatch &D = L.pt;
+  const double sz = sizeof(T), n = L.nsmooth;
+  const double by = (double)L.nnz * (sz + 2) + n * (4 + NR * sizeof(BT) + sz + 2 * NR * sz) +
+                    (double)D.nu * (sz + 4) + (double)D.ncoarse * NR * sz;
+  patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
+    with_codes(D, [&](auto mc, auto tc) {
+      launch_patch(k_patch_up<NR, T, BT, decltype(mc)::value, decltype(tc)::value>, D, NR * sizeof(T), 0, s, e0, e1,
+                   D.view<T>(), D.cells, L.C, nu, b, BV<T>::id(L), (const T *)BV<T>::x(L),
+                   (const T *)b_result<T>(Lc), BV<T>::r(L), (double *)nullptr, (const int *)nullptr);
+    });
+  });
+}
 
 // Gauss-Seidel sweep over the colour groups of L. `first_done`: the sweep starts from zero and
 // its colour-0 pass was run by the kernel that produced b.
@@ -1838,21 +1968,27 @@ static void b_vcycle(BatchDevice *dv, int k, hipStream_t s) {
   const T *b = BV<T>::b(L);
   if (L.nbottom > 0 && L.bottom_waves > 0) {
     hipLaunchKernelGGL((kb_gemv<NR, T>), dim3(nblk((int64_t)L.bottom_waves * 64)), dim3(BS), 0, s, L.bt_wavepref,
-                       L.nbottom, L.bt_nc, L.bt_moff, L.bt_voff, BV<T>::inv(L), b, BV<T>::x(L));
+                       L.nbottom, L.bt_nc, L.bt_moff, L.bt_voff, BV<T>::inv(L), b, b_result<T>(L));
     // the bottom inverses, g read and y written
     if (dv->count_bytes) dv->bytes += L.bt_entries * sizeof(T) + 2.0 * NR * sizeof(T) * L.bt_rows;
   }
   if (L.nsmooth == 0) return;
+  BLevel &Lc = dv->aux[k + 1];
+  if (L.pt.np) {
+    patch_down<NR, T>(dv, L, dv->nu_aux, b, Lc, s);
+    b_vcycle<NR, T>(dv, k + 1, s);
+    patch_up<NR, T>(dv, L, dv->nu_aux, b, Lc, s);
+    return;
+  }
   for (int it = 0; it < dv->nu_aux; ++it) b_sweep<NR, T>(dv, L, b, it == 0, true, true, s);
   b_residual<NR, T>(dv, L, b, s, UPPER_RESIDUAL && dv->nu_aux == 1);
-  BLevel &Lc = dv->aux[k + 1];
   b_spmv<NR, 0, 1, T>(dv, L.PT, BV<T>::r(L), BV<T>::b(Lc), &Lc, s);
   b_vcycle<NR, T>(dv, k + 1, s);
-  b_spmv<NR, 1, 0, T>(dv, L.P, BV<T>::x(Lc), BV<T>::x(L), nullptr, s);
+  b_spmv<NR, 1, 0, T>(dv, L.P, b_result<T>(Lc), BV<T>::x(L), nullptr, s);
   for (int it = 0; it < dv->nu_aux; ++it) b_sweep<NR, T>(dv, L, b, false, false, false, s);
 }
 
-// z = B_co r for every system; r (FP64, internal) -> fine.x (precision T). `first_done`: the CG
+// z = B_co r for every system; r (FP64, internal) -> b_result(fine) (precision T). `first_done`: the CG
 // update already ran the first colour pass on the original grids (and the FP32 rounding of r).
 template <int NR, class T>
 static void b_apply(BatchDevice *dv, const double *r, bool first_done, hipStream_t s) {
@@ -1860,6 +1996,12 @@ static void b_apply(BatchDevice *dv, const double *r, bool first_done, hipStream
   dv->site = 0;
   dv->shape_pi = sizeof(T) == 4 ? 1 : 0;
   dv->shape_nr = NR;
+  if (F.pt.np) {
+    patch_down<NR, T>(dv, F, dv->nu_fine, r, dv->aux[0], s);
+    b_vcycle<NR, T>(dv, 0, s);
+    patch_up<NR, T>(dv, F, dv->nu_fine, r, dv->aux[0], s);
+    return;
+  }
   const T *b;
   if constexpr (sizeof(T) == 8) {
     b = r;
@@ -1877,14 +2019,14 @@ static void b_apply(BatchDevice *dv, const double *r, bool first_done, hipStream
     b_residual<NR, T>(dv, F, b, s, false);
   b_spmv<NR, 0, 1, T>(dv, dv->PiT, BV<T>::r(F), BV<T>::b(dv->aux[0]), &dv->aux[0], s);
   b_vcycle<NR, T>(dv, 0, s);
-  b_spmv<NR, 1, 0, T>(dv, dv->Pi, BV<T>::x(dv->aux[0]), BV<T>::x(F), nullptr, s);
+  b_spmv<NR, 1, 0, T>(dv, dv->Pi, b_result<T>(dv->aux[0]), BV<T>::x(F), nullptr, s);
   for (int it = 0; it < dv->nu_fine; ++it) b_sweep<NR, T>(dv, F, b, false, false, false, s);
 }
 
 template <int NR, class T>
 static void b_tail(BatchDevice *dv, hipStream_t s, bool first_done) {
   b_apply<NR, T>(dv, dv->r, first_done, s);
-  const T *z = BV<T>::x(dv->fine);
+  const T *z = b_result<T>(dv->fine);
   hipLaunchKernelGGL((kb_cg_rz<NR, T>), dim3(dv->ew_blocks), dim3(BS), 0, s, dv->ew_r0, dv->ew_r1, dv->r, z, dv->ctl,
                      dv->partials);
   hipLaunchKernelGGL((kb_fin_rz<NR>), dim3(dv->nm), dim3(BS), 0, s, dv->ew_b0, dv->partials, dv->ctl);
@@ -1899,8 +2041,14 @@ static void b_iteration(BatchDevice *dv, hipStream_t s) {
   hipLaunchKernelGGL((kb_cg_spmv<NR>), dim3(Q.nslices / (BS / 64)), dim3(BS), 0, s, Q.srow, Q.soff, Q.scol, Q.sv64,
                      F.dg64, dv->p, dv->q, dv->ctl, dv->partials);
   hipLaunchKernelGGL((kb_fin_spmv<NR>), dim3(dv->nm), dim3(BS), 0, s, dv->cg_b0, dv->partials, dv->ctl);
-  hipLaunchKernelGGL((kb_cg_axpy<NR, T>), dim3(dv->ew_blocks), dim3(BS), 0, s, dv->ew_m, dv->ew_r0, dv->ew_r1, dv->u,
-                     dv->r, dv->p, dv->q, dv->ctl, dv->partials, bid0<T>(F), BV<T>::b(F), BV<T>::x(F));
+  auto axpy = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(dv->ew_blocks), dim3(BS), 0, s, dv->ew_m, dv->ew_r0, dv->ew_r1, dv->u, dv->r, dv->p,
+                       dv->q, dv->ctl, dv->partials, bid0<T>(F), BV<T>::b(F), BV<T>::x(F));
+  };
+  if (F.pt.np)
+    axpy(kb_cg_axpy<NR, T, false>);
+  else
+    axpy(kb_cg_axpy<NR, T, true>);
   hipLaunchKernelGGL((kb_fin_axpy<NR>), dim3(dv->nm), dim3(BS), 0, s, dv->ew_b0, dv->partials, dv->ctl);
   b_tail<NR, T>(dv, s, true);
 }
@@ -1925,12 +2073,15 @@ static void b_tune(BatchDevice *dv, hipStream_t s) {
         b_apply<NR, T>(dv, dv->r, false, s);
         HIPCHECK(hipStreamSynchronize(s));
         if ((int)t.size() < dv->tune_live) t.resize(dv->tune_live, std::vector<float>(K, INFINITY));
+        bool any = false;
         for (int site = 0; site < dv->tune_live; ++site) {
           if (!dv->tune_has[site]) continue;
+          any = true;
           float ms = 0;
           HIPCHECK(hipEventElapsedTime(&ms, dv->tune_ev[2 * site], dv->tune_ev[2 * site + 1]));
           t[site][k] = std::min(t[site][k], ms);
         }
+        if (!any) round = k = INT_MAX - 1;  // patches on every level: nothing to choose
       }
   } catch (...) {
     dv->tuning = false;

@@ -23,7 +23,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <climits>
 #include <cstdio>
@@ -1497,21 +1496,8 @@ static void stage_sell(DLevel &L, bool first_time, LevelStage &X) {
   X.sell = sell_host(H, L.groups);
 }
 
-// Patches of the levels (index 0: the original grid, i: auxiliary level J + 1 - i), built from their
-// matrices in internal numbering. One task builds a run of kPatchRun patches.
-static constexpr int kPatchRun = 8;
-
-struct PatchJob {
-  PatchSource<HCsr> src;
-  std::vector<int> cuts;
-  std::vector<PatchHost> parts;
-  PatchHost all;
-  PatchCodes codes;
-  bool code_matrix = true;
-  std::atomic<bool> fits{true};
-};
-
-static void patch_source(PatchJob &J, const DLevel &L, const HCsr &H, const HCsr &P, const HCsr *R,
+// what the patch builder reads of a level in internal numbering
+static void patch_source(PatchJob<HCsr> &J, const DLevel &L, const HCsr &H, const HCsr &P, const HCsr *R,
                          const std::vector<int> &order, int nu) {
   PatchSource<HCsr> &S = J.src;
   S.A = &H;
@@ -1523,43 +1509,9 @@ static void patch_source(PatchJob &J, const DLevel &L, const HCsr &H, const HCsr
   S.order = order;
   S.nu = nu;
   S.P = &P;
+  S.ncoarse = P.ncols;
   S.R = R;
   S.prepare();
-}
-
-static int patch_runs(const PatchJob &J) {
-  return J.cuts.empty() ? 0 : ((int)J.cuts.size() - 2 + kPatchRun) / kPatchRun;
-}
-
-// run t of a job's patches, into parts[t]
-static void patch_run(PatchJob &J, int t) {
-  static thread_local PatchMarks W;
-  const int np = (int)J.cuts.size() - 1;
-  for (int p = t * kPatchRun; p < std::min(np, (t + 1) * kPatchRun) && J.fits; ++p)
-    if (!patch_range(J.src, J.cuts[p], J.cuts[p + 1], W, J.parts[t])) J.fits = false;
-}
-
-static void patch_join(PatchJob &J) {
-  if (!J.fits) {
-    J.cuts.clear();
-    J.parts.clear();
-  }
-  for (PatchHost &p : J.parts) {
-    J.all.append(p);
-    p = PatchHost();
-  }
-  J.codes = patch_code(J.all, J.code_matrix);
-}
-
-// builds the patches of every job that has cuts; a level one of whose rows alone does not fit gets none
-static void patch_build(int threads, std::vector<PatchJob> &jobs) {
-  std::vector<std::pair<int, int>> runs;
-  for (size_t j = 0; j < jobs.size(); ++j) {
-    jobs[j].parts.resize(patch_runs(jobs[j]));
-    for (int t = 0; t < patch_runs(jobs[j]); ++t) runs.push_back({(int)j, t});
-  }
-  host_parallel(threads, (int)runs.size(), [&](int i) { patch_run(jobs[runs[i].first], runs[i].second); });
-  host_parallel(threads, (int)jobs.size(), [&](int j) { patch_join(jobs[j]); });
 }
 
 // host image of a level's near-boundary solver in the level's internal numbering
@@ -1875,7 +1827,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
     // Patches: whole-level smoothing without the near-boundary correction. A level whose coarser
     // level smooths locally writes its residual instead (that level also needs a copy of its
     // right-hand side).
-    std::vector<PatchJob> jobs(naux + 1);
+    std::vector<PatchJob<HCsr>> jobs(naux + 1);
     jobs[0].code_matrix = false;  // its values may be refreshed on the device
     host_parallel(h.threads, naux + 1, [&](int i) {
       DLevel &L = level_of(i);
@@ -1995,7 +1947,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
 }
 
 // the patches of every patched level again (same cuts): new values on the same patterns
-static void rebuild_patches(Device *dv, Hierarchy &h, const std::vector<const HCsr *> &mats, std::vector<PatchJob> &jobs) {
+static void rebuild_patches(Device *dv, Hierarchy &h, const std::vector<const HCsr *> &mats, std::vector<PatchJob<HCsr>> &jobs) {
   const int naux = h.J - h.lc;
   std::vector<HCsr> Pm(naux + 1), PTm(naux + 1);
   host_parallel(h.threads, naux + 1, [&](int i) {
@@ -2022,7 +1974,7 @@ void device_update_values(Device *dv, Hierarchy &h) {
   const int naux = h.J - h.lc;
   std::vector<LevelStage> st(1 + naux);
   std::vector<NbStage> nst(1 + naux);
-  std::vector<PatchJob> jobs(1 + naux);
+  std::vector<PatchJob<HCsr>> jobs(1 + naux);
   std::vector<const HCsr *> mats(1 + naux);
   host_parallel(h.threads, 1 + naux, [&](int t) {
     const int l = h.J + 1 - t;
@@ -2388,7 +2340,8 @@ static void patch_down(Device *dv, DLevel &L, int nu, const BT *b, T *bc, hipStr
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes(D, [&](auto mc, auto tc) {
       launch_patch(k_patch_down<1, T, BT, decltype(mc)::value, decltype(tc)::value>, D, sizeof(T), sizeof(T), s, e0, e1,
-                   D.view<T>(), D.cells, L.C, nu, D.fused ? 1 : 0, b, LV<T>::dg(L), LV<T>::x(L), LV<T>::r(L), bc);
+                   D.view<T>(), D.cells, D.lrows, L.C, nu, D.fused ? 1 : 0, b, LV<T>::dg(L), LV<T>::x(L), LV<T>::r(L), bc,
+                   (const int *)nullptr);
     });
   });
 }
@@ -2403,7 +2356,7 @@ static void patch_up(Device *dv, DLevel &L, int nu, const BT *b, const T *e, hip
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes(D, [&](auto mc, auto tc) {
       launch_patch(k_patch_up<1, T, BT, decltype(mc)::value, decltype(tc)::value>, D, sizeof(T), 0, s, e0, e1,
-                   D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L), (const T *)LV<T>::x(L), e, LV<T>::r(L));
+                   D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L), (const T *)LV<T>::x(L), e, LV<T>::r(L), (double *)nullptr, (const int *)nullptr);
     });
   });
 }
@@ -2862,7 +2815,7 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
     build_sell(dv, F, H, false, &slots);
     build_refresh(dv, h, H, slots);
     if (F.pt.np) {
-      std::vector<PatchJob> jobs(1 + h.J - h.lc);
+      std::vector<PatchJob<HCsr>> jobs(1 + h.J - h.lc);
       std::vector<const HCsr *> mats(jobs.size(), nullptr);
       mats[0] = &H;
       jobs[0].src.want_map = true;

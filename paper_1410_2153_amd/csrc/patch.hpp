@@ -23,6 +23,8 @@
 #pragma once
 
 #include <algorithm>
+#include <atomic>
+#include <cmath>
 #include <cstdint>
 #include <vector>
 
@@ -112,6 +114,7 @@ struct PatchSource {
   std::vector<int> order;     // rows in spatial order
   int nu = 1;                 // sweeps per side
   const M *P = nullptr;       // prolongation: rows of this level, columns of the coarser one
+  int ncoarse = 0;            // rows of the coarser level
   const M *R = nullptr;       // restriction: all rows of the coarser level; null = write the residual
   bool want_map = false;
   // filled by prepare()
@@ -406,6 +409,7 @@ template <class M>
 static std::vector<int> patch_plan(const PatchSource<M> &S) {
   std::vector<int> cut;
   if (S.n < 1 || S.C < 1 || S.C > kPatchColours || S.n >= 1 << 27) return cut;
+  if (S.ncoarse >= 1 << 27) return cut;
   PatchMarks W;
   int target = std::max(kPatchOwnMin, std::min(kPatchOwnMax, (S.n + 255) / 256));
   for (; target >= 128; target -= target / 8) {
@@ -475,6 +479,50 @@ static inline PatchCodes patch_code(PatchHost &H, bool matrix) {
   return K;
 }
 
+// A level's patches under construction; one task builds a run of kPatchRun patches.
+static constexpr int kPatchRun = 8;
+
+template <class M>
+struct PatchJob {
+  PatchSource<M> src;
+  std::vector<int> cuts;  // patch boundaries in the spatial order; empty: none
+  std::vector<PatchHost> parts;
+  PatchHost all;
+  PatchCodes codes;
+  bool code_matrix = true;
+  std::atomic<bool> fits{true};
+  int runs() const { return cuts.empty() ? 0 : ((int)cuts.size() - 2 + kPatchRun) / kPatchRun; }
+};
+
+// builds the patches of every job that has cuts; a level one of whose rows alone does not fit gets none
+template <class M>
+static void patch_build(int threads, std::vector<PatchJob<M>> &jobs) {
+  std::vector<std::pair<int, int>> runs;
+  for (size_t j = 0; j < jobs.size(); ++j) {
+    jobs[j].parts.resize(jobs[j].runs());
+    for (int t = 0; t < jobs[j].runs(); ++t) runs.push_back({(int)j, t});
+  }
+  host_parallel(threads, (int)runs.size(), [&](int i) {
+    static thread_local PatchMarks W;
+    PatchJob<M> &J = jobs[runs[i].first];
+    const int t = runs[i].second, np = (int)J.cuts.size() - 1;
+    for (int p = t * kPatchRun; p < std::min(np, (t + 1) * kPatchRun) && J.fits; ++p)
+      if (!patch_range(J.src, J.cuts[p], J.cuts[p + 1], W, J.parts[t])) J.fits = false;
+  });
+  host_parallel(threads, (int)jobs.size(), [&](int j) {
+    PatchJob<M> &J = jobs[j];
+    if (!J.fits) {
+      J.cuts.clear();
+      J.parts.clear();
+    }
+    for (PatchHost &p : J.parts) {
+      J.all.append(p);
+      p = PatchHost();
+    }
+    J.codes = patch_code(J.all, J.code_matrix);
+  });
+}
+
 // device arrays of a level's patches, values in precision T
 template <class T>
 struct PatchView {
@@ -493,7 +541,7 @@ struct DPatch {
   int np = 0;
   bool fused = false;  // `down` restricts (else it writes the residual)
   bool mcode = false, tcode = false;  // matrix entries, transfer entries coded
-  int cells = 0;       // LDS cells of the largest patch
+  int cells = 0, lrows = 0;  // LDS cells and matrix lanes of the largest patch
   PatchHead *head = nullptr;
   int *gidx = nullptr, *ugidx = nullptr, *ucell = nullptr, *ucol = nullptr, *roff = nullptr, *rrow = nullptr;
   uint32_t *pidx = nullptr, *ridx = nullptr;
@@ -544,7 +592,10 @@ static void patch_commit(const PatchHost &H, const PatchCodes &K, DPatch &D, boo
   D.np = (int)H.head.size();
   D.fused = fused;
   if (!D.np) return;
-  for (const PatchHead &h : H.head) D.cells = std::max(D.cells, 64 * h.ncs);
+  for (const PatchHead &h : H.head) {
+    D.cells = std::max(D.cells, 64 * h.ncs);
+    D.lrows = std::max(D.lrows, 64 * h.ns);
+  }
   patch_commit_matrix(H, K, D, up, room32);
   D.head = up(H.head);
   D.gidx = up(H.gidx);
@@ -583,8 +634,8 @@ struct alignas(2 * sizeof(T)) PPair {
   T a, b;
 };
 
-// base[i], with the offset in 32 bits so that the address is a scalar base and one offset register (the
-// plan keeps every array of a level below 4 GiB)
+// base[i], with the offset in 32 bits so that the address is a scalar base and one offset register (a
+// level with patches has fewer than 2^27 rows, and so has the coarser one: 4 GiB of four FP64 values)
 template <class X>
 __device__ __forceinline__ X at32(const X *base, uint32_t i) {
   return *reinterpret_cast<const X *>(reinterpret_cast<const char *>(base) + (size_t)(uint32_t)(i * (uint32_t)sizeof(X)));
@@ -627,11 +678,13 @@ struct PatchRows {
   PPair<T> v[kPatchSlots][kPatchPairs];
   int o[kPatchSlots], w[kPatchSlots];
 
-  __device__ __forceinline__ PPair<T> value(const PatchView<T> &V, uint32_t e, uint32_t c, const T *dict) const {
+  // values of pair row `row` (one lane's) with code word c
+  __device__ __forceinline__ PPair<T> value(const PatchView<T> &V, int row, uint32_t lane, uint32_t c,
+                                            const T *dict) const {
     if constexpr (MC)
       return PPair<T>{dict[c >> kPatchCellBits & 15u], dict[c >> (16 + kPatchCellBits)]};
     else
-      return at32(reinterpret_cast<const PPair<T> *>(V.pval), e);
+      return at32(reinterpret_cast<const PPair<T> *>(V.pval) + (size_t)row * 64, lane);
   }
 
   template <int J0, int J1>
@@ -658,7 +711,7 @@ struct PatchRows {
       for (int j = 0; j < kPatchSlots; ++j)
 #pragma unroll
         for (int q = 0; q < kPatchPairs; ++q)
-          if (q < w[j]) v[j][q] = value(V, 0, id[j][q], dict);
+          if (q < w[j]) v[j][q] = value(V, 0, 0, id[j][q], dict);
     }
   }
 
@@ -707,9 +760,8 @@ struct PatchRows {
       default: add_w<4, UP, NR>(a0, a1, j, xs, above); break;
     }
     for (int q = kPatchPairs; q < w[j]; ++q) {
-      const uint32_t e = (uint32_t)(o[j] + q) * 64 + lane;
-      const uint32_t c = at32(V.pidx, e);
-      pair_add<UP, NR, T>(a0, a1, c, value(V, e, c, dict), xs, above);
+      const uint32_t c = at32(V.pidx + (size_t)(o[j] + q) * 64, lane);
+      pair_add<UP, NR, T>(a0, a1, c, value(V, o[j] + q, lane, c, dict), xs, above);
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) a0.v[r] += a1.v[r];
@@ -728,8 +780,8 @@ constexpr int kPatchCoarse = sizeof(T) == 8 ? 1 : 2;
 // own rows, and either the restricted residual bc on the coarse rows owned (fused) or the residual r.
 template <int NR, class T, class BT, bool MC, bool TC>
 __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_patch_down(
-    PatchView<T> V, int cells, int C, int nu, int fused, const BT *__restrict__ b, const T *__restrict__ dg,
-    T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc) {
+    PatchView<T> V, int cells, int rows, int C, int nu, int fused, const BT *__restrict__ b, const T *__restrict__ dg,
+    T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
   __shared__ T dict[kPatchCodes];
   using X = PVec<NR, T>;
@@ -743,6 +795,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_p
     g[j] = at32(V.gidx + (size_t)(patch * kPatchSlices + j * kPatchWaves + wv) * 64, lane);
   const PatchHead &h = V.head[patch];
   const int ns = h.ns, nco = fused ? h.nco : 0;
+  const int stop = done ? *done : 0;  // the solve has ended: nothing is written
   int turn[kPatchSlots];  // colour of each slice, in scalar registers: the passes read no memory but LDS
 #pragma unroll
   for (int j = 0; j < kPatchSlots; ++j) turn[j] = h.sc[j] >> 4 * wv & 15;
@@ -750,7 +803,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_p
   PatchRows<T, MC> A;
   A.template load<0, kPatchSlots>(V, h, wv, lane);
   X *bs = xs + cells;
-  T *ds = reinterpret_cast<T *>(bs + 64 * kPatchSlices);
+  T *ds = reinterpret_cast<T *>(bs + rows);
   T iv[kPatchSlots];
   {
     X bv[kPatchSlots];
@@ -763,6 +816,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_p
       for (int q = 0; q < NR; ++q) bv[j].v[q] = (T)t.v[q];
       dv[j] = at32(dg, i);
     }
+    if (stop) return;
     // colour 0 of the first sweep; every other cell starts from zero
 #pragma unroll
     for (int j = 0; j < kPatchSlots; ++j) {
@@ -900,11 +954,12 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_p
   }
 }
 
-// Backward sweeps on b from x + P e, result in xo on the own rows (other patches still read x).
+// Backward sweeps on b from x + P e, result in xo on the own rows (other patches still read x); with
+// `part` also each patch's share of b.xo.
 template <int NR, class T, class BT, bool MC, bool TC>
 __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC) ? 2 : 4) void k_patch_up(
-    PatchView<T> V, int cells, int C, int nu, const BT *__restrict__ b, const T *__restrict__ id, const T *__restrict__ x,
-    const T *__restrict__ e, T *__restrict__ xo) {
+    PatchView<T> V, int cells, int C, int nu, const BT *__restrict__ b, const T *__restrict__ id,
+    const T *__restrict__ x, const T *__restrict__ e, T *__restrict__ xo, double *__restrict__ part, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
   __shared__ T dict[kPatchCodes];
   using X = PVec<NR, T>;
@@ -918,6 +973,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
     g[j] = at32(V.gidx + (size_t)(patch * kPatchSlices + j * kPatchWaves + wv) * 64, lane);
   const PatchHead &h = V.head[patch];
   const int ns = h.ns, nst = h.nst;
+  const int stop = done ? *done : 0;
   int turn[kPatchSlots];
 #pragma unroll
   for (int j = 0; j < kPatchSlots; ++j) turn[j] = h.sc[j] >> 4 * wv & 15;
@@ -1008,6 +1064,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
     }
     A.template load<0, early>(V, h, wv, lane);
   });
+  if (stop) return;
 #pragma unroll
   for (int j = 0; j < kPatchSlots; ++j)
     if (j * kPatchWaves + wv < ns) bs[(j * kPatchWaves + wv) * 64 + lane] = bv[j];
@@ -1031,6 +1088,23 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
       }
       __syncthreads();
     }
+  // partial sum of b.x over the own rows (FP64 b: the residual of the original grid)
+  if constexpr (NR == 1 && sizeof(BT) == 8)
+    if (part) {
+      double v = 0;
+#pragma unroll
+      for (int j = 0; j < kPatchSlots; ++j)
+        if (patch_owns(g[j])) v += at32(b, g[j]) * (double)xs[(j * kPatchWaves + wv) * 64 + lane].v[0];
+      __shared__ double sm[kPatchWaves];
+      v = group_sum<64>(v);
+      if (lane == 0) sm[wv] = v;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        v = 0;
+        for (int i = 0; i < kPatchWaves; ++i) v += sm[i];
+        part[patch] = v;
+      }
+    }
 }
 
 // launch of a patch kernel, one block per patch; LDS: x on the cells, b (then the residual) and the
@@ -1038,7 +1112,10 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
 template <class K, class... A>
 static void launch_patch(K kernel, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1, A... args) {
-  const size_t lds = (size_t)D.cells * vec + 64 * kPatchSlices * (vec + scalar);
+  const size_t lds = (size_t)D.cells * vec + (size_t)D.lrows * (vec + scalar);
+  if (lds > 64 * 1024)
+    HIPCHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)lds));
   if (e0) {
     hipExtLaunchKernelGGL(kernel, dim3(D.np), dim3(kPatchThreads), lds, s, e0, e1, 0, args...);
     HIPCHECK(hipGetLastError());
