@@ -196,7 +196,7 @@ int asmg_solve_device(asmg_handle h, const double *d_f, double tol, double *d_u,
  * As asmg_solve_device, for callers that cannot allocate (serving loops, harnesses that forbid
  * allocation): the call allocates nothing, host or device, and calls no allocating routine.
  * The PCG control block and the reduction partials live in a static per-GPU scratch array of
- * 16640 bytes (256 for the control block, 8 per reduction block up to 2048) held by the library
+ * 24832 bytes (256 for the control block, three times 8 per reduction block up to 1024) held by the library
  * until the process ends; every handle's reduction grid fits it (a larger one would be rejected
  * with ASMG_EINVAL). The iteration runs as eager kernel launches (no graph is built) and the
  * launch-shape autotuner never runs here: the shapes tuned by earlier asmg_solve_device calls on

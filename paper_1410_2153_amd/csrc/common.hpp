@@ -64,6 +64,26 @@ __device__ __forceinline__ double block_sum(double v) {
   return a[0];
 }
 
+// Sums of NV values over a 256-thread block, in every thread; the shared array may be reused at once.
+template <int NV>
+__device__ __forceinline__ void block_sum_all(double v[NV]) {
+  __shared__ double sm[NV][BS / 64];
+  const int w = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    v[q] = group_sum<64>(v[q]);
+    if ((threadIdx.x & 63) == 0) sm[q][w] = v[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    v[q] = 0.0;
+#pragma unroll
+    for (int i = 0; i < BS / 64; ++i) v[q] += sm[q][i];
+  }
+  __syncthreads();
+}
+
 // XCD-aware block index. Workgroups are dealt to the 8 XCDs round-robin (block b to XCD b % 8),
 // and each XCD has its own L2. This bijection of [0, gridDim.x) gives XCD x a contiguous run of
 // logical blocks, so rows that are neighbours in the numbering (and gather the same entries of

@@ -55,10 +55,18 @@ namespace asmg {
 // device control block for PCG
 // ---------------------------------------------------------------------------
 
+// The scalars that change from step to step are held twice: the direction update (k_cg_p) reads `a` and
+// writes `b`, the solution update (k_cg_axpy) reads `b` and writes `a`. Every block of a kernel derives
+// them for itself from the partial sums of the kernel before, and one block writes them down; no block
+// reads what another one of its kernel writes.
+struct CtlStep {
+  double rho;
+  int iter, done, status, first;
+};
 struct Ctl {
-  double rho, pq, rr, alpha, beta, fnorm2, tol2, rz, tr, mean;
-  int iter, done, status, maxit, first, pad;
-  unsigned ticket;
+  double pq, rr, alpha, beta, fnorm2, tol2, rz, tr, mean;
+  int maxit, pad;
+  CtlStep a, b;
 };
 
 enum { ST_OK = 0, ST_NOTSPD = 1, ST_NAN = 2, ST_NOCONV = 3 };
@@ -344,15 +352,16 @@ __global__ __launch_bounds__(BS) void k_scatter_cvt(int n, const int *__restrict
 // the handle's smaller cap) and writes one partial per block; a one-block finalize kernel
 // reduces the partials in a fixed order and updates the PCG scalars. No atomics, reproducible
 // results.
-static constexpr int RED_BLOCKS = 2048;
+static constexpr int RED_BLOCKS = 1024;
 
-// r = f, u = 0, p = 0; partials of ||f||^2
-__global__ __launch_bounds__(BS) void k_cg_init(int n, const double *__restrict__ f, double *__restrict__ r,
-                                                double *__restrict__ u, double *__restrict__ p,
-                                                double *__restrict__ partials) {
+// f gathered into internal order (perm; null: in place), r = f, u = 0, p = 0; partials of ||f||^2
+__global__ __launch_bounds__(BS) void k_cg_init(int n, const int *__restrict__ perm, const double *src, double *f,
+                                                double *__restrict__ r, double *__restrict__ u,
+                                                double *__restrict__ p, double *__restrict__ partials) {
   double v = 0.0;
   for (int i = blockIdx.x * BS + threadIdx.x; i < n; i += gridDim.x * BS) {
-    const double fi = f[i];
+    const double fi = perm ? src[perm[i]] : f[i];
+    if (perm) f[i] = fi;
     r[i] = fi;
     u[i] = 0.0;
     p[i] = 0.0;
@@ -374,11 +383,9 @@ __global__ __launch_bounds__(BS) void k_fin_init(const double *__restrict__ part
   if (threadIdx.x == 0) {
     ctl->fnorm2 = t;
     ctl->tol2 = tol * tol * t;
-    ctl->iter = 0;
-    ctl->status = ST_OK;
-    ctl->done = (t == 0.0) ? 1 : 0;
-    ctl->first = 1;
     ctl->maxit = maxit;
+    ctl->a = CtlStep{0.0, 0, (t == 0.0) ? 1 : 0, ST_OK, 1};
+    ctl->b = ctl->a;
   }
 }
 
@@ -397,8 +404,8 @@ __global__ __launch_bounds__(BS) void k_cg_restart(int n, const int *__restrict_
     p[row] = 0.0;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctl->done = 0;
-    ctl->first = 1;
+    ctl->a.done = ctl->b.done = 0;
+    ctl->a.first = 1;
   }
 }
 
@@ -424,9 +431,13 @@ __global__ __launch_bounds__(BS) void k_true_res(int n, const int *__restrict__ 
   if (threadIdx.x == 0) partials[blockIdx.x] = v;
 }
 
-__global__ __launch_bounds__(BS) void k_fin_tr(const double *__restrict__ partials, int nb, Ctl *ctl) {
+// the true residual, and a copy of the control block in the host's pinned memory
+__global__ __launch_bounds__(BS) void k_fin_tr(const double *__restrict__ partials, int nb, Ctl *ctl, Ctl *host) {
   const double t = sum_partials(partials, nb);
-  if (threadIdx.x == 0) ctl->tr = t;
+  if (threadIdx.x == 0) {
+    ctl->tr = t;
+    *host = *ctl;
+  }
 }
 
 // PCG start from a guess u: r = f - A u, p = 0, partials of ||r||^2 (grid-stride over row groups)
@@ -457,7 +468,7 @@ __global__ __launch_bounds__(BS) void k_cg_guess(int n, const int *__restrict__ 
 // a guess that already meets the stopping rule ends the solve before its first iteration
 __global__ __launch_bounds__(BS) void k_fin_guess(const double *__restrict__ partials, int nb, Ctl *ctl) {
   const double t = sum_partials(partials, nb);
-  if (threadIdx.x == 0 && t <= ctl->tol2) ctl->done = 1;
+  if (threadIdx.x == 0 && t <= ctl->tol2) ctl->a.done = ctl->b.done = 1;
 }
 
 // e += x
@@ -480,7 +491,7 @@ __global__ __launch_bounds__(BS) void k_cg_spmv(int ns, const int *__restrict__ 
                                                 const double *__restrict__ dg, const double *__restrict__ p,
                                                 double *__restrict__ q, const Ctl *ctl,
                                                 double *__restrict__ partials) {
-  if (ctl->done) return;
+  if (ctl->b.done) return;
   const int lane = threadIdx.x & 63;
   double v = 0.0;
   for (int s = wave_slice(0); s < ns; s += gridDim.x * (BS / 64)) {
@@ -595,33 +606,34 @@ __global__ __launch_bounds__(BS) void k_cg_spmv_lds(int ntiles, int ns, const in
   if (threadIdx.x == 0) partials[blockIdx.x] = v;
 }
 
-// alpha = rho / p.q, iteration count
-__global__ __launch_bounds__(BS) void k_fin_spmv(const double *__restrict__ partials, int nb, Ctl *ctl) {
-  if (ctl->done) return;
-  const double pq = sum_partials(partials, nb);
-  if (threadIdx.x == 0) {
-    ctl->pq = pq;
-    ctl->iter += 1;
-    if (!(pq > 0.0) || !isfinite(pq)) {
-      ctl->status = isfinite(pq) ? ST_NOTSPD : ST_NAN;
-      ctl->done = 1;
-    } else {
-      ctl->alpha = ctl->rho / pq;
-    }
-  }
-}
-
 // u += alpha p, r -= alpha q; partials of ||r||^2. The same pass runs the colour-0 Gauss-Seidel
 // pass of the next B_co application (sweep from zero) on the new r, in the precision T of B_co:
 // xf_i = r_i / a_ii on colour-0 rows (i < c0), 0 elsewhere; in FP32 r is also rounded into bf. With
-// patches on the original grid (FIRST false) that pass is theirs.
+// patches on the original grid (FIRST false) that pass is theirs. Every block first sums the `npq`
+// partials of p.q: alpha = rho / p.q and the iteration count.
 template <class T, bool FIRST>
 __global__ __launch_bounds__(BS) void k_cg_axpy(int n, double *__restrict__ u, double *__restrict__ r,
-                                                const double *__restrict__ p, const double *__restrict__ q,
-                                                const Ctl *ctl, double *__restrict__ partials, int c0,
-                                                const T *__restrict__ invd, T *__restrict__ bf, T *__restrict__ xf) {
-  if (ctl->done) return;
-  const double alpha = ctl->alpha;
+                                                const double *__restrict__ p, const double *__restrict__ q, Ctl *ctl,
+                                                const double *__restrict__ pqpart, int npq,
+                                                double *__restrict__ partials, int c0, const T *__restrict__ invd,
+                                                T *__restrict__ bf, T *__restrict__ xf) {
+  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  double pq[1] = {0.0};
+  for (int i = threadIdx.x; i < npq; i += BS) pq[0] += pqpart[i];
+  const CtlStep st = ctl->b;
+  if (st.done) {
+    if (lead) ctl->a = st;
+    return;
+  }
+  block_sum_all<1>(pq);
+  const bool bad = !(pq[0] > 0.0) || !isfinite(pq[0]);
+  const double alpha = st.rho / pq[0];
+  if (lead) {
+    ctl->pq = pq[0];
+    ctl->alpha = alpha;
+    ctl->a = CtlStep{st.rho, st.iter + 1, bad ? 1 : 0, !bad ? st.status : isfinite(pq[0]) ? ST_NOTSPD : ST_NAN, st.first};
+  }
+  if (bad) return;
   double v = 0.0;
   for (int i = blockIdx.x * BS + threadIdx.x; i < n; i += gridDim.x * BS) {
     u[i] += alpha * p[i];
@@ -641,62 +653,66 @@ __global__ __launch_bounds__(BS) void k_cg_axpy(int n, double *__restrict__ u, d
   if (threadIdx.x == 0) partials[blockIdx.x] = v;
 }
 
-// convergence test on ||r||^2
-__global__ __launch_bounds__(BS) void k_fin_axpy(const double *__restrict__ partials, int nb, Ctl *ctl) {
-  if (ctl->done) return;
-  const double rr = sum_partials(partials, nb);
-  if (threadIdx.x == 0) {
-    ctl->rr = rr;
-    if (!isfinite(rr)) {
-      ctl->status = ST_NAN;
-      ctl->done = 1;
-    } else if (rr <= ctl->tol2) {
-      ctl->done = 1;
-    } else if (ctl->iter >= ctl->maxit) {
-      ctl->status = ST_NOCONV;
-      ctl->done = 1;
-    }
-  }
-}
-
 // partials of r.z (z = B_co r in precision T)
 template <class T>
 __global__ __launch_bounds__(BS) void k_cg_rz(int n, const double *__restrict__ r, const T *__restrict__ z,
                                               const Ctl *ctl, double *__restrict__ partials) {
-  if (ctl->done) return;
+  if (ctl->a.done) return;
   double v = 0.0;
   for (int i = blockIdx.x * BS + threadIdx.x; i < n; i += gridDim.x * BS) v += r[i] * (double)z[i];
   v = block_sum(v);
   if (threadIdx.x == 0) partials[blockIdx.x] = v;
 }
 
-// rho' = r.z -> beta
-__global__ __launch_bounds__(BS) void k_fin_rz(const double *__restrict__ partials, int nb, Ctl *ctl) {
-  if (ctl->done) return;
-  const double rz = sum_partials(partials, nb);
-  if (threadIdx.x == 0) {
-    ctl->rz = rz;
-    if (!(rz > 0.0) || !isfinite(rz)) {
-      ctl->status = isfinite(rz) ? ST_NOTSPD : ST_NAN;
-      ctl->done = 1;
-    } else if (ctl->first) {
-      ctl->beta = 0.0;
-      ctl->rho = rz;
-      ctl->first = 0;
-    } else {
-      ctl->beta = rz / ctl->rho;
-      ctl->rho = rz;
+// Convergence test on the `nrr` partials of ||r||^2 (not before the first step), rho' = r.z from `nrz`
+// partials and beta in every block, then p = z + beta p.
+template <class T>
+__global__ __launch_bounds__(BS) void k_cg_p(int n, const T *__restrict__ z, double *__restrict__ p, Ctl *ctl,
+                                             const double *__restrict__ rrpart, int nrr,
+                                             const double *__restrict__ rzpart, int nrz) {
+  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  double s[2] = {0.0, 0.0};
+  for (int i = threadIdx.x; i < nrr; i += BS) s[0] += rrpart[i];
+  for (int i = threadIdx.x; i < nrz; i += BS) s[1] += rzpart[i];
+  CtlStep st = ctl->a;
+  const double tol2 = ctl->tol2;
+  const int maxit = ctl->maxit;
+  if (st.done) {
+    if (lead) ctl->b = st;
+    return;
+  }
+  block_sum_all<2>(s);
+  const double rr = s[0], rz = s[1];
+  if (!st.first) {
+    if (!isfinite(rr)) {
+      st.status = ST_NAN;
+      st.done = 1;
+    } else if (rr <= tol2) {
+      st.done = 1;
+    } else if (st.iter >= maxit) {
+      st.status = ST_NOCONV;
+      st.done = 1;
     }
   }
-}
-
-// p = z + beta p
-template <class T>
-__global__ __launch_bounds__(BS) void k_cg_p(int n, const T *__restrict__ z, double *__restrict__ p, const Ctl *ctl) {
-  if (ctl->done) return;
-  const double beta = ctl->beta;
-  const int i = blockIdx.x * BS + threadIdx.x;
-  if (i < n) p[i] = (double)z[i] + beta * p[i];
+  double beta = 0.0;
+  if (!st.done) {
+    if (!(rz > 0.0) || !isfinite(rz)) {
+      st.status = isfinite(rz) ? ST_NOTSPD : ST_NAN;
+      st.done = 1;
+    } else {
+      beta = st.first ? 0.0 : rz / st.rho;
+      st.rho = rz;
+      st.first = 0;
+    }
+  }
+  if (lead) {
+    ctl->rr = rr;
+    ctl->rz = rz;
+    ctl->beta = beta;
+    ctl->b = st;
+  }
+  if (st.done) return;
+  for (int i = blockIdx.x * BS + threadIdx.x; i < n; i += gridDim.x * BS) p[i] = (double)z[i] + beta * p[i];
 }
 
 // Operator refresh from a new per-element coefficient: every matrix entry is a fixed list of
@@ -1013,7 +1029,7 @@ struct Device {
   double *io_in = nullptr, *io_out = nullptr;   // staging for host-pointer calls
   Ctl *ctl = nullptr;
   Ctl *ctl_host = nullptr;    // pinned
-  double *partials = nullptr;
+  double *partials = nullptr;  // three buffers of RED_BLOCKS: p.q (and others), ||r||^2, r.z
   int max_blocks = 1;          // cap of the reduction grids (grid-stride loops beyond it)
   int restarts = 0;            // restarts from the true residual in the last solve
   int solve_iters = 0;         // PCG iterations of the last solve
@@ -1030,8 +1046,8 @@ struct Device {
   // execution: an internal stream carries the PCG loop (joined to the caller's stream with
   // events); one PCG iteration is captured per precision as a HIP graph
   hipStream_t stream = nullptr;
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
+  hipEvent_t ev_in = nullptr;
+  hipGraphExec_t graph[4] = {nullptr, nullptr, nullptr, nullptr};  // one iteration, then kGraphRun
   // launch shapes of the V-cycle slice kernels per precision and launch site (the k-th slice
   // launch of one B_co application), chosen by the autotuner at the first solve
   std::vector<Shape> shape[2];  // (threads per block, xcd order, kernel variant)
@@ -1045,6 +1061,10 @@ struct Device {
   std::vector<uint8_t> tune_has;       // site launched something
   int last_iters[2] = {0, 0};
   bool use_graph = true;
+  // inside the PCG loop: the flag that ends the patch kernels early, and where the last one leaves the
+  // patches' shares of r.z (null elsewhere)
+  const int *stop = nullptr;
+  double *rz_part = nullptr;
   bool no_alloc = false;      // inside asmg_solve_device_noalloc: no autotuning, no graph
   // byte model accumulation, and per-launch HIP event timing of one GS kernel instance
   bool count_bytes = false;
@@ -1926,9 +1946,8 @@ Device *device_create(Hierarchy &h, int ordinal) {
     HIPCHECK(hipHostMalloc((void **)&dv->ctl_host, sizeof(Ctl), hipHostMallocDefault));
     HIPCHECK(hipStreamCreateWithFlags(&dv->stream, hipStreamNonBlocking));
     HIPCHECK(hipEventCreateWithFlags(&dv->ev_in, hipEventDisableTiming));
-    HIPCHECK(hipEventCreateWithFlags(&dv->ev_out, hipEventDisableTiming));
     dv->max_blocks = h.opt.red_blocks > 0 ? std::min(h.opt.red_blocks, RED_BLOCKS) : RED_BLOCKS;
-    dv->partials = dalloc<double>(dv, RED_BLOCKS);
+    dv->partials = dalloc<double>(dv, 3 * RED_BLOCKS);
     // element data for the gradient kernel
     dv->ne = h.ne;
     dv->nv = h.nv;
@@ -2022,12 +2041,11 @@ void device_destroy(Device *dv) {
   if (!dv) return;
   (void)hipSetDevice(dv->ordinal);
   if (dv->stream) (void)hipStreamSynchronize(dv->stream);
-  for (int k = 0; k < 2; ++k)
-    if (dv->graph[k]) (void)hipGraphExecDestroy(dv->graph[k]);
+  for (hipGraphExec_t g : dv->graph)
+    if (g) (void)hipGraphExecDestroy(g);
   for (hipEvent_t e : dv->tune_ev) (void)hipEventDestroy(e);
   for (hipEvent_t e : dv->probe_ev) (void)hipEventDestroy(e);
   if (dv->ev_in) (void)hipEventDestroy(dv->ev_in);
-  if (dv->ev_out) (void)hipEventDestroy(dv->ev_out);
   if (dv->stream) (void)hipStreamDestroy(dv->stream);
   for (void *p : dv->allocs) (void)hipFree(p);
   if (dv->ctl_host) (void)hipHostFree(dv->ctl_host);
@@ -2341,22 +2359,29 @@ static void patch_down(Device *dv, DLevel &L, int nu, const BT *b, T *bc, hipStr
     with_codes(D, [&](auto mc, auto tc) {
       launch_patch(k_patch_down<1, T, BT, decltype(mc)::value, decltype(tc)::value>, D, sizeof(T), sizeof(T), s, e0, e1,
                    D.view<T>(), D.cells, D.lrows, L.C, nu, D.fused ? 1 : 0, b, LV<T>::dg(L), LV<T>::x(L), LV<T>::r(L), bc,
-                   (const int *)nullptr);
+                   dv->stop);
     });
   });
 }
 
-// x + P e, then backward sweeps on b, into result<T>(L)
+// x + P e, then backward sweeps on b, into result<T>(L); with `part` the patches' shares of b.x
 template <class T, class BT>
-static void patch_up(Device *dv, DLevel &L, int nu, const BT *b, const T *e, hipStream_t s) {
+static void patch_up(Device *dv, DLevel &L, int nu, const BT *b, const T *e, double *part, hipStream_t s) {
   const DPatch &D = L.pt;
   const double sz = sizeof(T);
   const double by = (double)L.A.nnz * (sz + 2) + (double)L.n * (4 + sizeof(BT) + 3 * sz) + (double)D.nu * (sz + 4) +
                     (double)D.ncoarse * sz;
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes(D, [&](auto mc, auto tc) {
-      launch_patch(k_patch_up<1, T, BT, decltype(mc)::value, decltype(tc)::value>, D, sizeof(T), 0, s, e0, e1,
-                   D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L), (const T *)LV<T>::x(L), e, LV<T>::r(L), (double *)nullptr, (const int *)nullptr);
+      constexpr bool MC = decltype(mc)::value, TC = decltype(tc)::value;
+      auto go = [&](auto kernel) {
+        launch_patch(kernel, D, sizeof(T), 0, s, e0, e1, D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L),
+                     (const T *)LV<T>::x(L), e, LV<T>::r(L), part, dv->stop);
+      };
+      if constexpr (sizeof(BT) == 8) {
+        if (part) return go(k_patch_up<1, T, BT, MC, TC, true>);
+      }
+      go(k_patch_up<1, T, BT, MC, TC, false>);
     });
   });
 }
@@ -2478,7 +2503,7 @@ static void vcycle(Device *dv, int l, hipStream_t s) {
     patch_down<T>(dv, L, dv->nu_aux, (const T *)b, lvl_b<T>(dv, l - 1), s);
     after_down<T>(dv, L, L.PT, l - 1, s);
     vcycle<T>(dv, l - 1, s);
-    patch_up<T>(dv, L, dv->nu_aux, (const T *)b, (const T *)lvl_x<T>(dv, l - 1), s);
+    patch_up<T>(dv, L, dv->nu_aux, (const T *)b, (const T *)lvl_x<T>(dv, l - 1), nullptr, s);
     return;
   }
   const bool nb = L.nb.n > 0;
@@ -2506,7 +2531,7 @@ static void apply_Bco(Device *dv, const double *r, bool first_done, hipStream_t 
     patch_down<T>(dv, F, dv->nu_fine, r, lvl_b<T>(dv, dv->J), s);
     after_down<T>(dv, F, dv->PiT, dv->J, s);
     vcycle<T>(dv, dv->J, s);
-    patch_up<T>(dv, F, dv->nu_fine, r, (const T *)lvl_x<T>(dv, dv->J), s);
+    patch_up<T>(dv, F, dv->nu_fine, r, (const T *)lvl_x<T>(dv, dv->J), dv->rz_part, s);
     return;
   }
   if constexpr (sizeof(T) == 8) {
@@ -2601,17 +2626,23 @@ static void nested_start(Device *dv, hipStream_t s) {
 // PCG driver
 // ---------------------------------------------------------------------------
 
-// z = B_co r, rho/beta, p = z + beta p (`first_done`: the CG update already ran the first
-// colour pass of B_co on r)
+// z = B_co r, convergence test and rho/beta, p = z + beta p (`first_done`: the CG update already ran the
+// first colour pass of B_co on r). r.z comes from the last patch launch where its partials fit.
 template <class T>
 static void pcg_tail(Device *dv, hipStream_t s, bool first_done) {
-  const int n = dv->fine.n;
+  const int n = dv->fine.n, np = dv->fine.pt.np;
+  double *rz = dv->partials + 2 * RED_BLOCKS;
+  const bool fused = np > 0 && np <= RED_BLOCKS;
+  dv->stop = &dv->ctl->a.done;
+  dv->rz_part = fused ? rz : nullptr;
   apply_Bco<T>(dv, dv->r, first_done, s);
+  dv->stop = nullptr;
+  dv->rz_part = nullptr;
   const int g = red_grid(dv, n, 1);
-  hipLaunchKernelGGL((k_cg_rz<T>), dim3(g), dim3(BS), 0, s, n, dv->r, (const T *)result<T>(dv->fine), dv->ctl,
-                     dv->partials);
-  hipLaunchKernelGGL(k_fin_rz, dim3(1), dim3(BS), 0, s, dv->partials, g, dv->ctl);
-  hipLaunchKernelGGL((k_cg_p<T>), dim3(nblk(n)), dim3(BS), 0, s, n, (const T *)result<T>(dv->fine), dv->p, dv->ctl);
+  if (!fused)
+    hipLaunchKernelGGL((k_cg_rz<T>), dim3(g), dim3(BS), 0, s, n, dv->r, (const T *)result<T>(dv->fine), dv->ctl, rz);
+  hipLaunchKernelGGL((k_cg_p<T>), dim3(g), dim3(BS), 0, s, n, (const T *)result<T>(dv->fine), dv->p, dv->ctl,
+                     (const double *)dv->partials + RED_BLOCKS, g, (const double *)rz, fused ? np : g);
 }
 
 // Autotuner: for every candidate shape (twice), one eager B_co application on the current r with
@@ -2664,40 +2695,50 @@ static void pcg_iteration(Device *dv, hipStream_t s) {
   int g = std::min<int>(dv->max_blocks, nblk((int64_t)F.sell.nslices * 64));
   hipLaunchKernelGGL(k_cg_spmv, dim3(g), dim3(BS), 0, s, F.sell.nslices, F.sell.srow, F.sell.soff, F.sell.scol,
                      F.sell.sv64, F.dg64, dv->p, dv->q, dv->ctl, dv->partials);
-  hipLaunchKernelGGL(k_fin_spmv, dim3(1), dim3(BS), 0, s, dv->partials, g, dv->ctl);
+  const double *pq = dv->partials;
+  const int npq = g;
+  double *rr = dv->partials + RED_BLOCKS;
   g = red_grid(dv, n, 1);
   if (F.pt.np)
-    hipLaunchKernelGGL((k_cg_axpy<T, false>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl,
-                       dv->partials, 0, (const T *)nullptr, (T *)nullptr, (T *)nullptr);
+    hipLaunchKernelGGL((k_cg_axpy<T, false>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl, pq, npq,
+                       rr, 0, (const T *)nullptr, (T *)nullptr, (T *)nullptr);
   else
-    hipLaunchKernelGGL((k_cg_axpy<T, true>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl,
-                       dv->partials, F.first_rows, LV<T>::id(F), LV<T>::b(F), LV<T>::x(F));
-  hipLaunchKernelGGL(k_fin_axpy, dim3(1), dim3(BS), 0, s, dv->partials, g, dv->ctl);
+    hipLaunchKernelGGL((k_cg_axpy<T, true>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl, pq, npq,
+                       rr, F.first_rows, LV<T>::id(F), LV<T>::b(F), LV<T>::x(F));
   pcg_tail<T>(dv, s, true);
 }
 
-static void read_ctl(Device *dv, hipStream_t s) {
-  HIPCHECK(hipMemcpyAsync(dv->ctl_host, dv->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
+// graph of k PCG iterations
+template <class T>
+static hipGraphExec_t iteration_graph(Device *dv, int k, hipStream_t s) {
+  hipGraph_t g;
+  hipGraphExec_t e;
+  HIPCHECK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+  for (int i = 0; i < k; ++i) pcg_iteration<T>(dv, s);
+  HIPCHECK(hipStreamEndCapture(s, &g));
+  HIPCHECK(hipGraphInstantiate(&e, g, nullptr, nullptr, 0));
+  HIPCHECK(hipGraphDestroy(g));
+  return e;
 }
+
+// A graph launch costs about 10 us beside its kernels (1.75 us each where they do nothing): handles that
+// solve again replay kGraphRun iterations at once.
+static constexpr int kGraphRun = 4;
 
 template <class T>
 static void launch_iterations(Device *dv, int k, hipStream_t s) {
   const int pi = sizeof(T) == 4 ? 1 : 0;
-  if (dv->use_graph && !dv->graph[pi]) {
-    hipGraph_t g;
-    HIPCHECK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    pcg_iteration<T>(dv, s);
-    HIPCHECK(hipStreamEndCapture(s, &g));
-    HIPCHECK(hipGraphInstantiate(&dv->graph[pi], g, nullptr, nullptr, 0));
-    HIPCHECK(hipGraphDestroy(g));
+  if (!dv->use_graph) {
+    for (int i = 0; i < k; ++i) pcg_iteration<T>(dv, s);
+    return;
   }
-  for (int i = 0; i < k; ++i) {
-    if (dv->use_graph)
-      HIPCHECK(hipGraphLaunch(dv->graph[pi], s));
-    else
-      pcg_iteration<T>(dv, s);
+  if (k >= kGraphRun && dv->last_iters[pi] > 0) {
+    hipGraphExec_t &run = dv->graph[2 + pi];
+    if (!run) run = iteration_graph<T>(dv, kGraphRun, s);
+    for (; k >= kGraphRun; k -= kGraphRun) HIPCHECK(hipGraphLaunch(run, s));
   }
+  if (k > 0 && !dv->graph[pi]) dv->graph[pi] = iteration_graph<T>(dv, 1, s);
+  for (int i = 0; i < k; ++i) HIPCHECK(hipGraphLaunch(dv->graph[pi], s));
 }
 
 // x -= mean(x) over the fine unknowns (pure Neumann problems: the constants span the kernel of A)
@@ -2710,49 +2751,56 @@ static void project_mean(Device *dv, double *x, hipStream_t s) {
 }
 
 template <class T>
-static int pcg(Device *dv, double tol, int *iters, double *true_rel, hipStream_t s) {
+static int pcg(Device *dv, const double *d_f, double tol, double *d_u, int *iters, double *true_rel, hipStream_t s) {
   TraceRange tr_pcg(sizeof(T) == 4 ? "asmg::pcg(mixed)" : "asmg::pcg(fp64)");
   const int n = dv->fine.n;
   const int pi = sizeof(T) == 4 ? 1 : 0;
   DLevel &F = dv->fine;
   const int gi = red_grid(dv, n, 1);
-  if (dv->pure_neumann) project_mean(dv, dv->f, s);  // the part of f in the range of A
-  hipLaunchKernelGGL(k_cg_init, dim3(gi), dim3(BS), 0, s, n, dv->f, dv->r, dv->u, dv->p, dv->partials);
+  const int *perm = dv->perm_d;
+  if (dv->pure_neumann) {  // the part of f in the range of A
+    hipLaunchKernelGGL(k_gather, dim3(nblk(n)), dim3(BS), 0, s, n, perm, d_f, dv->f);
+    project_mean(dv, dv->f, s);
+    perm = nullptr;
+  }
+  hipLaunchKernelGGL(k_cg_init, dim3(gi), dim3(BS), 0, s, n, perm, d_f, dv->f, dv->r, dv->u, dv->p, dv->partials);
   hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(BS), 0, s, dv->partials, gi, tol, dv->maxit, dv->ctl);
   if (dv->nested > 0) nested_start<T>(dv, s);  // u = u_0, r = f - A u_0
   tune<T>(dv, s);  // first solve in this precision: pick the launch shapes
   pcg_tail<T>(dv, s, false);
-  // host checks of the device flag: first after (previous count - 1) iterations, then every
-  // iteration; with no history, every `check_every` (default 4) iterations
-  int first = dv->last_iters[pi] > 1 ? dv->last_iters[pi] - 1 : 0;
+  // The host looks at the device flag after the previous solve's iteration count (iterations beyond
+  // convergence return at once; one less where B_co has launches that do not), then after every
+  // iteration; with no history, every `check_every` (default 4) iterations. The true residual in FP64 and
+  // u in the caller's order follow each run, so that the look at the flag is the solve's only wait.
+  bool all = F.pt.np > 0;
+  for (int l = dv->lc + 1; l <= dv->J; ++l) all = all && dv->aux[l].pt.np > 0;
+  int run = dv->last_iters[pi] - (all ? 0 : 1);
   const int K = dv->check_every > 0 ? dv->check_every : (dv->last_iters[pi] > 0 ? 1 : 4);
   int restarts = 0;
-  if (first > 0) {
-    launch_iterations<T>(dv, std::min(first, dv->maxit), s);
-  }
   while (true) {
-    read_ctl(dv, s);
-    if (!dv->ctl_host->done) {
-      launch_iterations<T>(dv, K, s);
-      continue;
-    }
-    // converged, broke down or hit max_iter: true residual in FP64
+    if (run > 0) launch_iterations<T>(dv, std::min(run, dv->maxit), s);
+    run = K;
     const int gt = red_grid(dv, n, F.A.lpr);
     with_lpr(F.A.lpr, [&](auto c) {
       constexpr int LP = decltype(c)::value;
       hipLaunchKernelGGL((k_true_res<LP>), dim3(gt), dim3(BS), 0, s, n, F.A.rp, F.A.ci, F.A.v64, F.dg64, dv->f,
                          dv->u, dv->partials);
     });
-    hipLaunchKernelGGL(k_fin_tr, dim3(1), dim3(BS), 0, s, dv->partials, gt, dv->ctl);
-    read_ctl(dv, s);
+    hipLaunchKernelGGL(k_fin_tr, dim3(1), dim3(BS), 0, s, dv->partials, gt, dv->ctl, dv->ctl_host);
+    if (!dv->pure_neumann)
+      hipLaunchKernelGGL(k_scatter, dim3(nblk(n)), dim3(BS), 0, s, n, dv->perm_d, dv->u, d_u);
+    HIPCHECK(hipGetLastError());
+    HIPCHECK(hipStreamSynchronize(s));
     const Ctl &c = *dv->ctl_host;
+    const CtlStep &at = c.b;
+    if (!at.done) continue;
     const double rel = c.fnorm2 > 0 ? std::sqrt(c.tr / c.fnorm2) : 0.0;
     // Converged on the recursively updated residual but the true residual is above tol: CG
     // restarts from the true residual (at most 3 times), as the oracle does. With the iteration
     // budget already spent the restart cannot take a step, and the solve ends unconverged.
-    int status = c.status;
+    int status = at.status;
     if (status == ST_OK && rel > tol && restarts < 3) {
-      if (c.iter >= dv->maxit) {
+      if (at.iter >= dv->maxit) {
         status = ST_NOCONV;
       } else {
         ++restarts;
@@ -2762,14 +2810,21 @@ static int pcg(Device *dv, double tol, int *iters, double *true_rel, hipStream_t
                              F.A.v64, F.dg64, dv->f, dv->u, dv->r, dv->p, dv->ctl);
         });
         pcg_tail<T>(dv, s, false);
+        run = 0;
         continue;
       }
     }
+    if (dv->pure_neumann) {  // the solution with zero mean
+      project_mean(dv, dv->u, s);
+      hipLaunchKernelGGL(k_scatter, dim3(nblk(n)), dim3(BS), 0, s, n, dv->perm_d, dv->u, d_u);
+      HIPCHECK(hipGetLastError());
+      HIPCHECK(hipStreamSynchronize(s));
+    }
     dv->restarts = restarts;
-    dv->solve_iters = c.iter;
-    if (iters) *iters = c.iter;
+    dv->solve_iters = at.iter;
+    if (iters) *iters = at.iter;
     if (true_rel) *true_rel = rel;
-    if (status == ST_OK) dv->last_iters[pi] = c.iter;
+    if (status == ST_OK) dv->last_iters[pi] = at.iter;
     switch (status) {
       case ST_OK: return ASMG_OK;
       case ST_NOTSPD: return ASMG_ENOTSPD;
@@ -2791,16 +2846,9 @@ int device_solve(Device *dv, const double *d_f, double tol, double *d_u, int *it
   }
   HIPCHECK(hipEventRecord(dv->ev_in, cs));
   HIPCHECK(hipStreamWaitEvent(s, dv->ev_in, 0));
-  hipLaunchKernelGGL(k_gather, dim3(nblk(n)), dim3(BS), 0, s, n, dv->perm_d, d_f, dv->f);
-  const int rc = dv->precision == ASMG_PREC_MIXED ? pcg<float>(dv, tol, iters, true_rel, s)
-                                                   : pcg<double>(dv, tol, iters, true_rel, s);
-  if (dv->pure_neumann) project_mean(dv, dv->u, s);  // the solution with zero mean
-  hipLaunchKernelGGL(k_scatter, dim3(nblk(n)), dim3(BS), 0, s, n, dv->perm_d, dv->u, d_u);
-  HIPCHECK(hipGetLastError());
-  HIPCHECK(hipEventRecord(dv->ev_out, s));
-  HIPCHECK(hipStreamWaitEvent(cs, dv->ev_out, 0));
-  HIPCHECK(hipStreamSynchronize(s));
-  return rc;
+  // the solve ends with a wait for `s`: what the caller enqueues next sees u
+  return dv->precision == ASMG_PREC_MIXED ? pcg<float>(dv, d_f, tol, d_u, iters, true_rel, s)
+                                          : pcg<double>(dv, d_f, tol, d_u, iters, true_rel, s);
 }
 
 // Operator refresh from dv->kappa (already written on `s`)
@@ -2843,11 +2891,11 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
 // ---------------------------------------------------------------------------
 
 // Scratch of device_solve_noalloc: the PCG control block at offset 0, the reduction partials
-// (at most RED_BLOCKS doubles) from offset kScratchPartials. One copy per GPU, held until the
+// (three buffers of RED_BLOCKS doubles) from offset kScratchPartials. One copy per GPU, held until the
 // process ends. In host code `scratch` names a host-side stand-in: only the address that
 // hipGetSymbolAddress returns for the current device may reach a kernel or a copy.
 static constexpr size_t kScratchPartials = 256;
-static constexpr size_t kScratchBytes = kScratchPartials + sizeof(double) * RED_BLOCKS;
+static constexpr size_t kScratchBytes = kScratchPartials + 3 * sizeof(double) * RED_BLOCKS;
 static_assert(sizeof(Ctl) <= kScratchPartials, "control block larger than its scratch slot");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -2873,9 +2921,6 @@ static void *scratch_address(int ordinal) {
 int device_solve_noalloc(Device *dv, const double *d_f, double tol, double *d_u, int *iters, double *true_rel,
                          void *stream) {
   HIPCHECK(hipSetDevice(dv->ordinal));
-  if (kScratchPartials + sizeof(double) * (size_t)dv->max_blocks > kScratchBytes)
-    throw AsmgError{ASMG_EINVAL, "reduction grid of this handle exceeds the solver scratch (" +
-                                     std::to_string(kScratchBytes) + " bytes)"};
   unsigned char *base = (unsigned char *)scratch_address(dv->ordinal);
   // the handle's own control block and partials are swapped for the scratch for this call; the
   // iteration runs as eager launches (a captured graph holds the handle's own pointers) and

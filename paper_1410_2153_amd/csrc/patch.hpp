@@ -39,7 +39,7 @@ static constexpr int kPatchSlots = 4;  // slices per wave
 static constexpr int kPatchSlices = kPatchWaves * kPatchSlots;
 static constexpr int kPatchCellSlices = 38;
 static constexpr int kPatchHeadCoarse = 16;  // coarse slices whose entry offsets are in the head
-static constexpr int kPatchPairs = 4;  // entry pairs of a row kept in registers (the cases of dot())
+static constexpr int kPatchPairs = 4;  // entry pairs of a row kept in registers, at most (cases of dot())
 static constexpr int kPatchColours = 15;
 static constexpr int kPatchHalo = 1 << 30;  // gidx: a halo row or cell (its result is not written)
 
@@ -670,12 +670,13 @@ __device__ __forceinline__ void pair_add(PVec<NR, T> &a0, PVec<NR, T> &a1, uint3
   }
 }
 
-// matrix entries of a wave's slices in registers: kPatchPairs pairs of each row (longer rows read the
-// rest again in every pass), with their values unless MC (coded: looked up in `dict`, in LDS)
-template <class T, bool MC>
+// matrix entries of a wave's slices in registers: N pairs of each row (longer rows read the rest again
+// in every pass), with their values unless MC (coded: looked up in `dict`, in LDS). Rows of the 2-D
+// auxiliary levels hold at most 6 entries: N = 3 there leaves registers for two FP64 blocks per CU.
+template <class T, bool MC, int N>
 struct PatchRows {
-  uint32_t id[kPatchSlots][kPatchPairs];
-  PPair<T> v[kPatchSlots][kPatchPairs];
+  uint32_t id[kPatchSlots][N];
+  PPair<T> v[kPatchSlots][N];
   int o[kPatchSlots], w[kPatchSlots];
 
   // values of pair row `row` (one lane's) with code word c
@@ -697,7 +698,7 @@ struct PatchRows {
       const uint32_t *ip = V.pidx + (size_t)o[j] * 64;
       const PPair<T> *vp = reinterpret_cast<const PPair<T> *>(V.pval) + (size_t)o[j] * 64;
 #pragma unroll
-      for (int q = 0; q < kPatchPairs; ++q)
+      for (int q = 0; q < N; ++q)
         if (q < w[j]) {
           id[j][q] = at32(ip + q * 64, lane);
           if constexpr (!MC) v[j][q] = at32(vp + q * 64, lane);
@@ -710,7 +711,7 @@ struct PatchRows {
 #pragma unroll
       for (int j = 0; j < kPatchSlots; ++j)
 #pragma unroll
-        for (int q = 0; q < kPatchPairs; ++q)
+        for (int q = 0; q < N; ++q)
           if (q < w[j]) v[j][q] = value(V, 0, 0, id[j][q], dict);
     }
   }
@@ -752,14 +753,16 @@ struct PatchRows {
     PVec<NR, T> a0, a1;
 #pragma unroll
     for (int r = 0; r < NR; ++r) a0.v[r] = a1.v[r] = T(0);
-    switch (w[j] < kPatchPairs ? w[j] : kPatchPairs) {
+    switch (w[j] < N ? w[j] : N) {
       case 0: break;
       case 1: add_w<1, UP, NR>(a0, a1, j, xs, above); break;
       case 2: add_w<2, UP, NR>(a0, a1, j, xs, above); break;
       case 3: add_w<3, UP, NR>(a0, a1, j, xs, above); break;
-      default: add_w<4, UP, NR>(a0, a1, j, xs, above); break;
+      default:
+        if constexpr (N > 3) add_w<N, UP, NR>(a0, a1, j, xs, above);
+        break;
     }
-    for (int q = kPatchPairs; q < w[j]; ++q) {
+    for (int q = N; q < w[j]; ++q) {
       const uint32_t c = at32(V.pidx + (size_t)(o[j] + q) * 64, lane);
       pair_add<UP, NR, T>(a0, a1, c, value(V, o[j] + q, lane, c, dict), xs, above);
     }
@@ -779,7 +782,7 @@ constexpr int kPatchCoarse = sizeof(T) == 8 ? 1 : 2;
 // Forward sweeps from zero on b (BT: its type; FP64 on the original grid in both precisions), x on the
 // own rows, and either the restricted residual bc on the coarse rows owned (fused) or the residual r.
 template <int NR, class T, class BT, bool MC, bool TC>
-__global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_patch_down(
+__global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC) ? 2 : 4) void k_patch_down(
     PatchView<T> V, int cells, int rows, int C, int nu, int fused, const BT *__restrict__ b, const T *__restrict__ dg,
     T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
@@ -800,8 +803,10 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_p
 #pragma unroll
   for (int j = 0; j < kPatchSlots; ++j) turn[j] = h.sc[j] >> 4 * wv & 15;
   if (MC && threadIdx.x < kPatchCodes) dict[threadIdx.x] = V.pval[threadIdx.x];
-  PatchRows<T, MC> A;
-  A.template load<0, kPatchSlots>(V, h, wv, lane);
+  PatchRows<T, MC, TC ? 3 : kPatchPairs> A;
+  // the last slot's 64-bit values wait until b and the diagonal are out of their registers
+  constexpr int early = sizeof(T) == 8 ? kPatchSlots - 1 : kPatchSlots;
+  A.template load<0, early>(V, h, wv, lane);
   X *bs = xs + cells;
   T *ds = reinterpret_cast<T *>(bs + rows);
   T iv[kPatchSlots];
@@ -857,6 +862,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_p
         if (q < cw[j]) cid[j][q] = at32(V.ridx + (size_t)(co[j] + q) * 64, lane);
     }
   }
+  A.template load<early, kPatchSlots>(V, h, wv, lane);
   __syncthreads();
   A.decode(V, dict);
   for (int s = 0; s < nu; ++s)
@@ -956,7 +962,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 ? 2 : 4) void k_p
 
 // Backward sweeps on b from x + P e, result in xo on the own rows (other patches still read x); with
 // `part` also each patch's share of b.xo.
-template <int NR, class T, class BT, bool MC, bool TC>
+template <int NR, class T, class BT, bool MC, bool TC, bool DOT = false>
 __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC) ? 2 : 4) void k_patch_up(
     PatchView<T> V, int cells, int C, int nu, const BT *__restrict__ b, const T *__restrict__ id,
     const T *__restrict__ x, const T *__restrict__ e, T *__restrict__ xo, double *__restrict__ part, const int *__restrict__ done) {
@@ -980,14 +986,14 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   if (MC && threadIdx.x < kPatchCodes) dict[threadIdx.x] = V.pval[threadIdx.x];
   X *bs = xs + cells;
   T iv[kPatchSlots];
-  PatchRows<T, MC> A;
+  PatchRows<T, MC, TC ? 3 : kPatchPairs> A;
   // with 64-bit values the second half of the matrix rows is loaded after the prolongation: both at
   // once do not fit in the registers of two blocks per CU
   constexpr int early = sizeof(T) == 8 && TC ? kPatchSlots / 2 : kPatchSlots;
   auto column = [](int c) { return TC ? c & 0xfffffff : c; };
   // Start rows, UB slices of a wave at a time: all their loads, then all gathers, then the sums. Coded
   // rows hold at most two entries; others go PW entries at a time.
-  constexpr int PW = TC ? 2 : 8, UB = TC ? 3 : 2;
+  constexpr int PW = TC ? 2 : NR * sizeof(T) > 16 ? 4 : 8, UB = TC ? 3 : NR == 1 ? 2 : 1;
   auto start = [&](int k0, auto &&between) {
     int ug[UB], cell[UB], o[UB], w[UB], uc[UB][PW];
     T uv[UB][PW];
@@ -1089,22 +1095,21 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
       __syncthreads();
     }
   // partial sum of b.x over the own rows (FP64 b: the residual of the original grid)
-  if constexpr (NR == 1 && sizeof(BT) == 8)
-    if (part) {
-      double v = 0;
+  if constexpr (DOT) {
+    double v = 0;
 #pragma unroll
-      for (int j = 0; j < kPatchSlots; ++j)
-        if (patch_owns(g[j])) v += at32(b, g[j]) * (double)xs[(j * kPatchWaves + wv) * 64 + lane].v[0];
-      __shared__ double sm[kPatchWaves];
-      v = group_sum<64>(v);
-      if (lane == 0) sm[wv] = v;
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        v = 0;
-        for (int i = 0; i < kPatchWaves; ++i) v += sm[i];
-        part[patch] = v;
-      }
+    for (int j = 0; j < kPatchSlots; ++j)
+      if (patch_owns(g[j])) v += at32(b, g[j]) * (double)xs[(j * kPatchWaves + wv) * 64 + lane].v[0];
+    __shared__ double sm[kPatchWaves];
+    v = group_sum<64>(v);
+    if (lane == 0) sm[wv] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      v = 0;
+      for (int i = 0; i < kPatchWaves; ++i) v += sm[i];
+      part[patch] = v;
     }
+  }
 }
 
 // launch of a patch kernel, one block per patch; LDS: x on the cells, b (then the residual) and the
