@@ -318,7 +318,9 @@ __global__ __launch_bounds__(BS) void kb_first_cvt(int n, const double *__restri
   if (d != 0.0f) reinterpret_cast<VecR<NR, float> *>(x)[i] = o;
 }
 
-// bottom solves of the meshes whose V-cycle ends on this level: y = M_m g. A wave computes
+// Bottom solves y = M_m g of every mesh, whatever merged level its V-cycle ends on: nothing reads a
+// bottom result before the way up, so one launch at the deepest point serves all levels (one launch per
+// level took 14-28 us each for a few meshes, half of it without enough rows in flight). A wave computes
 // kGemvRows consecutive rows of one mesh, so that each gathered g entry (NR values) serves all of
 // them: per row the wave streams n entries of M from HBM and n / kGemvRows entries of g from L2
 // (one row per wave read g once per row, four times the bytes of M with four right-hand sides).
@@ -327,7 +329,8 @@ constexpr int kGemvRows = 4;
 template <int NR, class T>
 __global__ __launch_bounds__(BS) void kb_gemv(const int *__restrict__ wavepref, int nb, const int *__restrict__ nc,
                                               const int64_t *__restrict__ moff, const int *__restrict__ voff,
-                                              const T *__restrict__ M, const T *__restrict__ g, T *__restrict__ y) {
+                                              const int *__restrict__ lev, const T *__restrict__ M,
+                                              const T *const *__restrict__ gs, T *const *__restrict__ ys) {
   const int w = blockIdx.x * (BS / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (w >= wavepref[nb]) return;  // whole wave leaves together
@@ -336,7 +339,7 @@ __global__ __launch_bounds__(BS) void kb_gemv(const int *__restrict__ wavepref, 
   const int i0 = (w - wavepref[s]) * kGemvRows;
   const int nr = min(kGemvRows, n - i0);
   const T *m = M + moff[s] + (int64_t)i0 * n;
-  const VecR<NR, T> *G = reinterpret_cast<const VecR<NR, T> *>(g) + voff[s];
+  const VecR<NR, T> *G = reinterpret_cast<const VecR<NR, T> *>(gs[lev[s]]) + voff[s];
   T acc[kGemvRows][NR];
 #pragma unroll
   for (int k = 0; k < kGemvRows; ++k)
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(BS) void kb_gemv(const int *__restrict__ wavepref, 
       if (k == lane)
 #pragma unroll
         for (int r = 0; r < NR; ++r) o.v[r] = acc[k][r];
-    reinterpret_cast<VecR<NR, T> *>(y)[voff[s] + i0 + lane] = o;
+    reinterpret_cast<VecR<NR, T> *>(ys[lev[s]])[voff[s] + i0 + lane] = o;
   }
 }
 
@@ -783,17 +786,9 @@ struct BLevel {
   BSell P, PT;           // P: rows = smoothing rows, cols = rows of level k+1 (as used in B_co:
                          // P without each mesh's last colour rows, P^T without the zero-residual
                          // columns of the last colour group)
-  // bottom meshes
-  int nbottom = 0;
-  int *bt_wavepref = nullptr, *bt_nc = nullptr, *bt_voff = nullptr;  // waves of kb_gemv per mesh (prefix)
-  int64_t *bt_moff = nullptr;
-  double *inv64 = nullptr;
-  float *inv32 = nullptr;
   DPatch pt;             // overlapped patches of the smoothing rows (np = 0: colour passes one by one)
   int C = 0;             // colours
   int64_t nnz = 0;       // off-diagonal entries of the smoothing rows (byte model)
-  int bottom_waves = 0;
-  double bt_entries = 0, bt_rows = 0;  // byte model: inverse entries, rows of the bottom meshes
 };
 
 struct BatchDevice {
@@ -815,6 +810,14 @@ struct BatchDevice {
   int *row_stride = nullptr;      // gather/scatter
   int64_t *row_src0[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};  // per NR (index NR)
   std::vector<BLevel> aux;        // merged level k = 0..K
+  // bottom solves of all meshes: waves of kb_gemv (prefix), size, offsets, merged level; the levels'
+  // right-hand sides and results
+  int nbottom = 0, bottom_waves = 0;
+  int *bt_wavepref = nullptr, *bt_nc = nullptr, *bt_voff = nullptr, *bt_lev = nullptr;
+  int64_t *bt_moff = nullptr;
+  double *inv64 = nullptr, **bt_g64 = nullptr, **bt_y64 = nullptr;
+  float *inv32 = nullptr, **bt_g32 = nullptr, **bt_y32 = nullptr;
+  double bt_entries = 0, bt_rows = 0;  // byte model: inverse entries, rows
   // CG
   double *f = nullptr, *u = nullptr, *r = nullptr, *p = nullptr, *q = nullptr;
   double *partials = nullptr;
@@ -1287,7 +1290,6 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         off += (int)H[m]->nc;
       }
       L.nrows = off;
-      L.nbottom = (int)bottom_m[k].size();
     }
     // rows of merged level k in each mesh's own (Morton) numbering: smoothing meshes through their
     // colour permutation, bottom meshes as they are
@@ -1312,12 +1314,6 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
       std::vector<uint8_t> c0flag;
       BSellHost gs, cg, up;
       GroupCounts counts;  // byte-model counts of every colour group
-      // bottom meshes
-      std::vector<int> pref{0}, ncs, voff;
-      double bt_entries = 0, bt_rows = 0;
-      std::vector<int64_t> moff;
-      std::vector<double> inv;
-      std::vector<float> inv32;
     };
     LevelImage fine_img;
     std::vector<LevelImage> aux_img(K + 1);
@@ -1524,18 +1520,6 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
           bsell_host(X.A, groups, false, X.gs);
           group_counts(X.A, groups, X.counts);
         }
-        for (size_t i = 0; i < bottom_m[k].size(); ++i) {
-          const int m = bottom_m[k][i];
-          const int nc = (int)H[m]->nc;
-          X.ncs.push_back(nc);
-          X.voff.push_back(L.off[smooth_m[k].size() + i]);
-          X.moff.push_back((int64_t)X.inv.size());
-          X.inv.insert(X.inv.end(), H[m]->coarse_inv.begin(), H[m]->coarse_inv.end());
-          X.pref.push_back(X.pref.back() + (nc + kGemvRows - 1) / kGemvRows);  // waves of kb_gemv
-          X.bt_entries += (double)nc * nc;
-          X.bt_rows += nc;
-        }
-        X.inv32.assign(X.inv.begin(), X.inv.end());
       } else {
         const int k = t - (K + 6);
         if (patched(k + 1)) return;
@@ -1596,15 +1580,6 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
       bsell_upload(dv, X.gs, L.sell);
       set_counts(L, std::move(X.counts));
       upload_diag(dv, L, X.diag, X.c0flag);
-      L.bottom_waves = X.pref.back();
-      L.bt_entries = X.bt_entries;
-      L.bt_rows = X.bt_rows;
-      L.bt_wavepref = bupload(dv, X.pref);
-      L.bt_nc = bupload(dv, X.ncs);
-      L.bt_voff = bupload(dv, X.voff);
-      L.bt_moff = bupload(dv, X.moff);
-      L.inv64 = bupload(dv, X.inv);
-      L.inv32 = bupload(dv, X.inv32);
       alloc_level_vectors(dv, L);
       X = LevelImage();
     }
@@ -1619,6 +1594,53 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
           jobs[i].all, jobs[i].codes, (i == 0 ? dv->fine : dv->aux[i - 1]).pt, true,
           [&](const auto &v) { return bupload(dv, v); }, [&](int64_t n) { return balloc<float>(dv, n); });
       jobs[i].all = PatchHost();
+    }
+    // ---- bottom solves of all levels
+    {
+      std::vector<int> pref{0}, ncs, voff, lv;
+      std::vector<int64_t> moff;
+      int64_t len = 0;
+      for (int k = 0; k <= K; ++k)
+        for (size_t i = 0; i < bottom_m[k].size(); ++i) {
+          const int64_t nc = H[bottom_m[k][i]]->nc;
+          ncs.push_back((int)nc);
+          voff.push_back(dv->aux[k].off[smooth_m[k].size() + i]);
+          lv.push_back(k);
+          moff.push_back(len);
+          len += nc * nc;
+          pref.push_back(pref.back() + (int)((nc + kGemvRows - 1) / kGemvRows));
+          dv->bt_rows += (double)nc;
+        }
+      dv->bt_entries = (double)len;
+      dv->nbottom = (int)ncs.size();
+      dv->bottom_waves = pref.back();
+      dv->bt_wavepref = bupload(dv, pref);
+      dv->bt_nc = bupload(dv, ncs);
+      dv->bt_voff = bupload(dv, voff);
+      dv->bt_lev = bupload(dv, lv);
+      dv->bt_moff = bupload(dv, moff);
+      dv->inv64 = balloc<double>(dv, len);
+      dv->inv32 = balloc<float>(dv, len);
+      int at = 0;
+      for (int k = 0; k <= K; ++k)
+        for (int m : bottom_m[k]) {
+          const std::vector<double> &v = H[m]->coarse_inv;
+          if (!v.empty()) HIPCHECK(hipMemcpy(dv->inv64 + moff[at], v.data(), v.size() * 8, hipMemcpyHostToDevice));
+          ++at;
+        }
+      patch_round(len, dv->inv64, dv->inv32);
+      std::vector<double *> g64, y64;
+      std::vector<float *> g32, y32;
+      for (BLevel &L : dv->aux) {
+        g64.push_back(L.b64);
+        g32.push_back(L.b32);
+        y64.push_back(L.pt.np ? L.r64 : L.x64);
+        y32.push_back(L.pt.np ? L.r32 : L.x32);
+      }
+      dv->bt_g64 = bupload(dv, g64);
+      dv->bt_g32 = bupload(dv, g32);
+      dv->bt_y64 = bupload(dv, y64);
+      dv->bt_y32 = bupload(dv, y32);
     }
     // ---- gather/scatter maps: internal fine row -> user offset of (mesh, rhs 0, dof), stride n_m
     {
@@ -1714,7 +1736,6 @@ struct BV<double> {
   static const double *dg(BLevel &L) { return L.dg64; }
   static const double *id(BLevel &L) { return L.id64; }
   static const double *v(const BCsr &A) { return A.v64; }
-  static const double *inv(BLevel &L) { return L.inv64; }
 };
 template <>
 struct BV<float> {
@@ -1724,7 +1745,6 @@ struct BV<float> {
   static const float *dg(BLevel &L) { return L.dg32; }
   static const float *id(BLevel &L) { return L.id32; }
   static const float *v(const BCsr &A) { return A.v32; }
-  static const float *inv(BLevel &L) { return L.inv32; }
 };
 
 static inline double bsell_bytes(const BSell &A, int s) { return (double)A.nnz * (s + 4) + 4.0 * (A.nrows + 1); }
@@ -1966,13 +1986,19 @@ template <int NR, class T>
 static void b_vcycle(BatchDevice *dv, int k, hipStream_t s) {
   BLevel &L = dv->aux[k];
   const T *b = BV<T>::b(L);
-  if (L.nbottom > 0 && L.bottom_waves > 0) {
-    hipLaunchKernelGGL((kb_gemv<NR, T>), dim3(nblk((int64_t)L.bottom_waves * 64)), dim3(BS), 0, s, L.bt_wavepref,
-                       L.nbottom, L.bt_nc, L.bt_moff, L.bt_voff, BV<T>::inv(L), b, b_result<T>(L));
+  if (L.nsmooth == 0) {  // the deepest level: the bottom solves of every level
+    if (dv->bottom_waves == 0) return;
+    const dim3 grid(nblk((int64_t)dv->bottom_waves * 64));
+    if constexpr (sizeof(T) == 8)
+      hipLaunchKernelGGL((kb_gemv<NR, T>), grid, dim3(BS), 0, s, dv->bt_wavepref, dv->nbottom, dv->bt_nc, dv->bt_moff,
+                         dv->bt_voff, dv->bt_lev, dv->inv64, dv->bt_g64, dv->bt_y64);
+    else
+      hipLaunchKernelGGL((kb_gemv<NR, T>), grid, dim3(BS), 0, s, dv->bt_wavepref, dv->nbottom, dv->bt_nc, dv->bt_moff,
+                         dv->bt_voff, dv->bt_lev, dv->inv32, dv->bt_g32, dv->bt_y32);
     // the bottom inverses, g read and y written
-    if (dv->count_bytes) dv->bytes += L.bt_entries * sizeof(T) + 2.0 * NR * sizeof(T) * L.bt_rows;
+    if (dv->count_bytes) dv->bytes += dv->bt_entries * sizeof(T) + 2.0 * NR * sizeof(T) * dv->bt_rows;
+    return;
   }
-  if (L.nsmooth == 0) return;
   BLevel &Lc = dv->aux[k + 1];
   if (L.pt.np) {
     patch_down<NR, T>(dv, L, dv->nu_aux, b, Lc, s);
