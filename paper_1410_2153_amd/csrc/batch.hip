@@ -1438,7 +1438,7 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         S.col = colour[i - 1];
       }
       S.prepare();
-      jobs[i].cuts = patch_plan(S);
+      jobs[i].cuts = patch_plan(S, false);
     });
     jobs[0].code_matrix = false;  // values of the mesh's own geometry
     patch_build(0, jobs);
@@ -1838,8 +1838,9 @@ static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &
   const double by = (double)L.nnz * (sz + 2) + n * (4 + NR * sizeof(BT) + sz + NR * sz) + (double)D.nr * 2 * (sz + 2) +
                     (double)D.ncoarse * (4 + NR * sz);
   patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
-    with_codes(D, [&](auto mc, auto tc) {
-      launch_patch(k_patch_down<NR, T, BT, decltype(mc)::value, decltype(tc)::value>, D, NR * sizeof(T), sizeof(T), s,
+    with_codes<false>(D, [&](auto geom, auto mc, auto tc) {
+      using G = decltype(geom);
+      launch_patch(k_patch_down<G, NR, T, BT, decltype(mc)::value, decltype(tc)::value>, G::threads, D, NR * sizeof(T), sizeof(T), s,
                    e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, 1, b, BV<T>::dg(L), BV<T>::x(L), (T *)nullptr,
                    BV<T>::b(Lc), (const int *)nullptr);
     });
@@ -1857,8 +1858,9 @@ static void patch_up(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &Lc
   const double by = (double)L.nnz * (sz + 2) + n * (4 + NR * sizeof(BT) + sz + 2 * NR * sz) +
                     (double)D.nu * (sz + 4) + (double)D.ncoarse * NR * sz;
   patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
-    with_codes(D, [&](auto mc, auto tc) {
-      launch_patch(k_patch_up<NR, T, BT, decltype(mc)::value, decltype(tc)::value>, D, NR * sizeof(T), 0, s, e0, e1,
+    with_codes<false>(D, [&](auto geom, auto mc, auto tc) {
+      using G = decltype(geom);
+      launch_patch(k_patch_up<G, NR, T, BT, decltype(mc)::value, decltype(tc)::value>, G::threads, D, NR * sizeof(T), 0, s, e0, e1,
                    D.view<T>(), D.cells, L.C, nu, b, BV<T>::id(L), (const T *)BV<T>::x(L),
                    (const T *)b_result<T>(Lc), BV<T>::r(L), (double *)nullptr, (const int *)nullptr);
     });

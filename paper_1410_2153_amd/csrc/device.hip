@@ -1855,7 +1855,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
       const bool fused = i == naux || !level_of(i + 1).local;
       patch_source(jobs[i], L, stage_of(i).H, Pm[i], fused ? &PTm[i] : nullptr, i == 0 ? forder : L.iperm,
                    i == 0 ? dv->nu_fine : dv->nu_aux);
-      jobs[i].cuts = patch_plan(jobs[i].src);
+      jobs[i].cuts = patch_plan(jobs[i].src, i > 0);
     });
     patch_build(h.threads, jobs);
     for (int i = 0; i <= naux; ++i) level_of(i).cuts = jobs[i].cuts;
@@ -1912,6 +1912,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
     commit_transfer(dv, pi_st, dv->Pi);
     commit_transfer(dv, pit_st, dv->PiT);
     for (int i = 0; i <= naux; ++i) {
+      level_of(i).pt.big = jobs[i].src.shape.waves == kPatchBig.waves;
       patch_commit(
           jobs[i].all, jobs[i].codes, level_of(i).pt, jobs[i].src.R != nullptr, [&](const auto &v) { return dupload(dv, v); },
           [&](int64_t n) { return dalloc<float>(dv, n); });
@@ -1983,6 +1984,7 @@ static void rebuild_patches(Device *dv, Hierarchy &h, const std::vector<const HC
     if (L.pt.fused) PTm[i] = transpose(Pm[i]);
     patch_source(jobs[i], L, *mats[i], Pm[i], L.pt.fused ? &PTm[i] : nullptr, order, i == 0 ? dv->nu_fine : dv->nu_aux);
     jobs[i].cuts = L.cuts;
+    jobs[i].src.shape = L.pt.big ? kPatchBig : kPatchSmall;
     jobs[i].code_matrix = i > 0;
   });
   patch_build(h.threads, jobs);
@@ -2356,10 +2358,11 @@ static void patch_down(Device *dv, DLevel &L, int nu, const BT *b, T *bc, hipStr
   const double by = (double)L.A.nnz * (sz + 2) + (double)L.n * (4 + sizeof(BT) + 3 * sz) +
                     (D.fused ? (double)D.nr * 2 * (sz + 2) + (double)D.ncoarse * (4 + sz) : (double)L.n * sz);
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
-    with_codes(D, [&](auto mc, auto tc) {
-      launch_patch(k_patch_down<1, T, BT, decltype(mc)::value, decltype(tc)::value>, D, sizeof(T), sizeof(T), s, e0, e1,
-                   D.view<T>(), D.cells, D.lrows, L.C, nu, D.fused ? 1 : 0, b, LV<T>::dg(L), LV<T>::x(L), LV<T>::r(L), bc,
-                   dv->stop);
+    with_codes<std::is_same<T, BT>::value>(D, [&](auto geom, auto mc, auto tc) {
+      using G = decltype(geom);
+      launch_patch(k_patch_down<G, 1, T, BT, decltype(mc)::value, decltype(tc)::value>, G::threads, D, sizeof(T),
+                   sizeof(T), s, e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, D.fused ? 1 : 0, b, LV<T>::dg(L),
+                   LV<T>::x(L), LV<T>::r(L), bc, dv->stop);
     });
   });
 }
@@ -2372,16 +2375,17 @@ static void patch_up(Device *dv, DLevel &L, int nu, const BT *b, const T *e, dou
   const double by = (double)L.A.nnz * (sz + 2) + (double)L.n * (4 + sizeof(BT) + 3 * sz) + (double)D.nu * (sz + 4) +
                     (double)D.ncoarse * sz;
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
-    with_codes(D, [&](auto mc, auto tc) {
+    with_codes<std::is_same<T, BT>::value>(D, [&](auto geom, auto mc, auto tc) {
+      using G = decltype(geom);
       constexpr bool MC = decltype(mc)::value, TC = decltype(tc)::value;
       auto go = [&](auto kernel) {
-        launch_patch(kernel, D, sizeof(T), 0, s, e0, e1, D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L),
+        launch_patch(kernel, G::threads, D, sizeof(T), 0, s, e0, e1, D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L),
                      (const T *)LV<T>::x(L), e, LV<T>::r(L), part, dv->stop);
       };
-      if constexpr (sizeof(BT) == 8) {
-        if (part) return go(k_patch_up<1, T, BT, MC, TC, true>);
+      if constexpr (sizeof(BT) == 8 && !MC) {
+        if (part) return go(k_patch_up<G, 1, T, BT, MC, TC, true>);
       }
-      go(k_patch_up<1, T, BT, MC, TC, false>);
+      go(k_patch_up<G, 1, T, BT, MC, TC, false>);
     });
   });
 }

@@ -14,7 +14,7 @@
 // `up` (backward sweeps): x + P e on every cell that the first pass reads, then the passes.
 //
 // Layout of a patch: its rows sorted by colour, inside a colour by row length, in slices of 64 rows
-// (one per lane); slice k belongs to wave k % 8, and cell 64 k + lane of the LDS image is its row. Cells
+// (one per lane), dealt to the waves in turn, and cell 64 k + lane of the LDS image is its row. Cells
 // that are read but never computed follow the last slice. The cells whose value counts before the first
 // backward pass form slices of their own (start rows), by the length of their prolongation row. Matrix entries come in pairs: two values and
 // two 16-bit cell numbers, 64 lanes side by side. Matrices with few distinct values (the level matrices
@@ -33,34 +33,48 @@
 
 namespace asmg {
 
-static constexpr int kPatchWaves = 8;
-static constexpr int kPatchThreads = 64 * kPatchWaves;
-static constexpr int kPatchSlots = 4;  // slices per wave
-static constexpr int kPatchSlices = kPatchWaves * kPatchSlots;
-static constexpr int kPatchCellSlices = 38;
-static constexpr int kPatchHeadCoarse = 16;  // coarse slices whose entry offsets are in the head
-static constexpr int kPatchPairs = 4;  // entry pairs of a row kept in registers, at most (cases of dot())
-static constexpr int kPatchColours = 15;
-static constexpr int kPatchHalo = 1 << 30;  // gidx: a halo row or cell (its result is not written)
+// Geometry of the patch kernels: waves of a block, slices per wave, entry pairs of a row kept in registers
+// (FP64, FP32), bits of a cell number in 16 (a code sits above it).
+//   PatchSmall: up to 2048 rows, two blocks per CU; the 2-D levels.
+//   PatchBig: up to 6144 rows, the whole register file and LDS of a CU; 3-D levels of many colours, whose
+//   halo through all passes is several times the own rows.
+template <int Waves, int Slots, int Pairs64, int Pairs32, int Bits>
+struct PatchGeom {
+  static constexpr int waves = Waves, slots = Slots, bits = Bits;
+  static constexpr int threads = 64 * Waves, slices = Waves * Slots;
+  template <class T>
+  static constexpr int pairs = sizeof(T) == 8 ? Pairs64 : Pairs32;
+};
+using PatchSmall = PatchGeom<8, 4, 4, 4, 12>;
+using PatchBig = PatchGeom<16, 6, 2, 4, 13>;
 
-static constexpr int kPatchCodes = 16;
-static constexpr int kPatchCellBits = 12;      // a cell number below its code
-static_assert(64 * kPatchCellSlices <= 1 << kPatchCellBits, "cell numbers fit below the codes");
+struct PatchShape {
+  int waves, slices, cell_slices, bits;
+};
+static constexpr PatchShape kPatchSmall{PatchSmall::waves, PatchSmall::slices, 38, PatchSmall::bits};
+static constexpr PatchShape kPatchBig{PatchBig::waves, PatchBig::slices, 104, PatchBig::bits};
+static_assert(64 * kPatchSmall.cell_slices <= 1 << PatchSmall::bits, "cell numbers fit below the codes");
+static_assert(64 * kPatchBig.cell_slices <= 1 << PatchBig::bits, "cell numbers fit below the codes");
+
+static constexpr int kPatchHeadCoarse = 16;  // coarse slices whose entry offsets are in the head
+static constexpr int kPatchColours = 15;
+static constexpr int kPatchHalo = 1 << 30;   // gidx: a halo row or cell (its result is not written)
+static constexpr int kPatchCodes = 16;       // matrix codes (PatchSmall)
 
 struct alignas(64) PatchHead {
   int ns, ncs;          // matrix slices, cell slices (the first ns are the matrix slices)
   int start0, nst;      // first slice of start rows, slices
   int coarse0, nco;     // first slice of coarse rows, slices
-  uint32_t sc[kPatchSlots];        // colour of slice 8 j + i in bits 4 i of sc[j], 15 = none
-  int poff[kPatchSlices + 1];      // first pair row of each matrix slice
-  int uoff[kPatchCellSlices + 1];  // first prolongation row of each slice of start rows
-  int roff[kPatchHeadCoarse + 1];  // first pair row of the first coarse slices
+  uint64_t sc[PatchBig::slots];         // colour of slice (waves j + i) in bits 4 i of sc[j], 15 = none
+  int poff[kPatchBig.slices + 1];       // first pair row of each matrix slice
+  int uoff[kPatchBig.cell_slices + 1];  // first prolongation row of each slice of start rows
+  int roff[kPatchHeadCoarse + 1];       // first pair row of the first coarse slices
 };
 
 // host image of a level's patches
 struct PatchHost {
   std::vector<PatchHead> head;
-  std::vector<int> gidx;            // level row per matrix lane, -1 = none; kPatchSlices slices a patch
+  std::vector<int> gidx;            // level row per matrix lane, -1 = none; as many slices a patch as fit
   std::vector<uint32_t> pidx;       // two cells per pair
   std::vector<double> pval;         // two values
   std::vector<int> pmap;            // matrix entry of each value, -1 = padding (on request)
@@ -117,6 +131,7 @@ struct PatchSource {
   int ncoarse = 0;            // rows of the coarser level
   const M *R = nullptr;       // restriction: all rows of the coarser level; null = write the residual
   bool want_map = false;
+  PatchShape shape = kPatchSmall;
   // filled by prepare()
   std::vector<int> pos;           // position of each row in the order
   std::vector<int> cpos0, clist;  // coarse rows by the position of the row that decides their owner
@@ -151,6 +166,7 @@ struct PatchSource {
 // per-thread marks over a level's rows
 struct PatchMarks {
   std::vector<int> need, uni, cell, row;
+  std::vector<int> list[2];
   int epoch = 0;
   void size(int n) {
     if ((int)need.size() < n) {
@@ -163,14 +179,18 @@ struct PatchMarks {
   }
 };
 
-// Patch of the rows order[a..b): appended to out; false (nothing appended) where it does not fit.
+// Rows and cells of the patch of order[a..b): `uni` all of them (W.row marks the computed ones), `need` the
+// cells whose value before the first backward pass counts; false where they cannot fit.
 template <class M>
-static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, PatchHost &out) {
+static bool patch_closure(const PatchSource<M> &S, int a, int b, PatchMarks &W, std::vector<int> &need,
+                          std::vector<int> &uni) {
   const M &A = *S.A;
   const int C = S.C;
   W.size(S.n);
   const int E = W.epoch;
-  std::vector<int> need, next, uni;
+  std::vector<int> next, cur;
+  need.clear();
+  uni.clear();
   auto add = [&](int r) {
     if (W.need[r] != E) {
       W.need[r] = E;
@@ -183,7 +203,7 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   };
   auto later = [&](int c, bool earlier_only, bool rows) {  // undo one pass of colour c
     next.clear();
-    std::vector<int> cur;
+    cur.clear();
     for (int r : need)
       if (S.col[r] == c) {
         W.need[r] = E - 1;
@@ -219,16 +239,41 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   for (int k = S.nu - 1; k >= 0; --k)
     for (int c = C - 1; c >= 0; --c) later(c, k == 0, false);
   for (int r : uni) W.row[r] = E;
-  if ((int)uni.size() > 64 * kPatchSlices) {
-    return false;
-  }
+  if ((int)uni.size() > 64 * S.shape.slices) return false;
   // rows computed and cells read going up
   for (int r : need) W.need[r] = E - 1;
   need.clear();
   for (int i = a; i < b; ++i) add(S.order[i]);
   for (int k = 0; k < S.nu; ++k)
     for (int c = 0; c < C; ++c) later(c, false, true);
-  // now need = the cells whose value before the first pass counts (marked E in W.need)
+  return true;
+}
+
+// computed rows of a patch, 0 where it does not fit
+template <class M>
+static int patch_rows(const PatchSource<M> &S, int a, int b, PatchMarks &W, std::vector<int> &need,
+                      std::vector<int> &uni) {
+  if (!patch_closure(S, a, b, W, need, uni)) return 0;
+  std::vector<int> count(S.C + 1, 0);
+  int rows = 0;
+  for (int r : uni) {
+    const bool row = W.row[r] == W.epoch;
+    count[row ? S.col[r] : S.C]++;
+    rows += row;
+  }
+  int ns = 0;
+  for (int c = 0; c < S.C; ++c) ns += (count[c] + 63) / 64;
+  return ns > S.shape.slices || ns + (count[S.C] + 63) / 64 > S.shape.cell_slices ? 0 : rows;
+}
+
+// Patch of the rows order[a..b): appended to out; false (nothing appended) where it does not fit.
+template <class M>
+static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, PatchHost &out) {
+  const M &A = *S.A;
+  const int C = S.C;
+  std::vector<int> &need = W.list[0], &uni = W.list[1];
+  if (!patch_closure(S, a, b, W, need, uni)) return false;
+  const int E = W.epoch;
   std::vector<std::vector<int>> by(C);
   std::vector<int> cells;
   for (int i : uni)
@@ -239,7 +284,7 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   int ns = 0;
   for (auto &v : by) ns += ((int)v.size() + 63) / 64;
   const int ncs = ns + ((int)cells.size() + 63) / 64;
-  if (ns > kPatchSlices || ncs > kPatchCellSlices) return false;
+  if (ns > S.shape.slices || ncs > S.shape.cell_slices) return false;
   // spatial order inside a colour: internal numbers ascend with the spatial order there
   PatchHead h{};
   h.start0 = (int)(out.ugidx.size() / 64);
@@ -253,7 +298,7 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   };
   std::vector<int> list;  // row per cell, -1 = empty lane
   std::vector<std::pair<int, int>> key;
-  for (uint32_t &x : h.sc) x = ~0u;
+  for (uint64_t &x : h.sc) x = ~0ull;
   for (int c = 0; c < C; ++c) {
     const int k0 = (int)list.size() / 64;
     std::sort(by[c].begin(), by[c].end());
@@ -263,8 +308,8 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
     for (auto &kr : key) list.push_back(kr.second);
     while (list.size() % 64) list.push_back(-1);
     for (int k = k0; k < (int)list.size() / 64; ++k) {
-      h.sc[k / kPatchWaves] &= ~(15u << 4 * (k % kPatchWaves));
-      h.sc[k / kPatchWaves] |= (uint32_t)c << 4 * (k % kPatchWaves);
+      const int bit = 4 * (k % S.shape.waves);
+      h.sc[k / S.shape.waves] = (h.sc[k / S.shape.waves] & ~(15ull << bit)) | (uint64_t)c << bit;
     }
   }
   std::sort(cells.begin(), cells.end());
@@ -275,7 +320,7 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   // own rows: marked by position
   std::vector<uint8_t> own(list.size(), 0);
   for (int i = a; i < b; ++i) own[W.cell[S.order[i]]] = 1;
-  for (int i = 0; i < 64 * kPatchSlices; ++i) {
+  for (int i = 0; i < 64 * S.shape.slices; ++i) {
     const int r = i < 64 * ns ? list[i] : -1;
     out.gidx.push_back(r < 0 ? -1 : own[i] ? r : r | kPatchHalo);
   }
@@ -307,7 +352,7 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
         out.pidx[base + (size_t)(q >> 1) * 64 + l] |= (uint32_t)first << (q & 1 ? 16 : 0);
     }
   }
-  for (int k = ns; k <= kPatchSlices; ++k) h.poff[k] = (int)(out.pidx.size() / 64);
+  for (int k = ns; k <= kPatchBig.slices; ++k) h.poff[k] = (int)(out.pidx.size() / 64);
   // start rows: the cells that some backward pass reads as they were
   auto plen = [&](int r) { return S.P->rp[r + 1] - S.P->rp[r]; };
   key.clear();
@@ -341,7 +386,7 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
       }
     }
   }
-  for (int k = h.nst; k <= kPatchCellSlices; ++k) h.uoff[k] = (int)(out.ucol.size() / 64);
+  for (int k = h.nst; k <= kPatchBig.cell_slices; ++k) h.uoff[k] = (int)(out.ucol.size() / 64);
   // coarse rows
   if (S.R) {
     key.clear();
@@ -396,36 +441,80 @@ static bool patch_range(const PatchSource<M> &S, int a, int b, PatchMarks &W, Pa
   return patch_range(S, a, m, W, out) && patch_range(S, m, b, W, out);
 }
 
-// own rows per patch: enough patches for the chip where that is possible, no fewer own rows than
-// kPatchOwnMin (the halo grows against them), and patches that fit
+// Own rows per patch: enough patches for the chip where that is possible, no fewer own rows than
+// kPatchOwnMin (the halo grows against them: measured flat from 256 to 1024 within 4 %), no more than
+// kPatchOwnMax; where the halo outweighs the own rows (3-D levels), as many as fit.
 static constexpr int kPatchOwnMin = 256;
 static constexpr int kPatchOwnMax = 1536;
 
-// Computed rows per own row above which the passes one by one are the better path.
-static constexpr double kPatchMaxRatio = 2.6;
+// Estimated us of a level's two patch launches, from measured ones: 5 us each, and beyond that 4 us for
+// every 512 patches of PatchSmall (two per CU at a time), for every 256 of PatchBig 14 and 1.2 for each
+// pass, or its rows (own and halo) at 4 TB/s and some 70 bytes; and the prolongation's gathers, 1.6 us for
+// each entry of a row beyond two (the original grid: 2-D 6 entries, up 15 us; 3-D 12, 29 us).
+static inline double patch_cost(bool big, int np, double rows, int passes, double pw) {
+  const double one = big ? (14 + 1.2 * passes) * ((np + 255) / 256) : 4.0 * ((np + 511) / 512);
+  return 2 * (5 + std::max(one, 1.75e-5 * rows)) + 1.6 * std::max(0.0, pw - 2);
+}
 
-// Plan of one level's patches: the chunk boundaries in the spatial order; empty = no patches.
+// and of its passes one by one: one per colour, sweep and direction, the residual and the transfers, 3 us
+// each and 18 more per million rows of their colour (measured in a graph: 2.9 us at 2000 rows, 4.75 at
+// 125,000, 12.5 at 540,000).
+static inline double pass_cost(int n, int C, int nu) { return (2 * nu * C + 3) * (3.0 + 1.8e-5 * n / C); }
+
+// Plan of one level's patches: the chunk boundaries in the spatial order, and the shape in S; empty = the
+// passes are faster. `big`: the larger shape may be used.
 template <class M>
-static std::vector<int> patch_plan(const PatchSource<M> &S) {
+static std::vector<int> patch_plan(PatchSource<M> &S, bool big) {
   std::vector<int> cut;
   if (S.n < 1 || S.C < 1 || S.C > kPatchColours || S.n >= 1 << 27) return cut;
   if (S.ncoarse >= 1 << 27) return cut;
   PatchMarks W;
-  int target = std::max(kPatchOwnMin, std::min(kPatchOwnMax, (S.n + 255) / 256));
-  for (; target >= 128; target -= target / 8) {
-    const int np = (S.n + target - 1) / target;
-    const int tries = std::min(np, 8);
-    PatchHost t;
-    bool fit = true;
-    for (int i = 0; i < tries && fit; ++i) {
+  const double pw = (double)S.P->ci.size() / S.n, passes = pass_cost(S.n, S.C, S.nu);
+  double best = passes;
+  int best_np = 0;
+  PatchShape shape = kPatchSmall;
+  // computed rows per own row of `np` patches, from up to 5 of them; 0 where one does not fit
+  auto try_plan = [&](int np) {
+    const int tries = std::min(np, 5);
+    double rows = 0, own = 0;
+    for (int i = 0; i < tries; ++i) {
       const int64_t p = tries > 1 ? (int64_t)i * (np - 1) / (tries - 1) : 0;
-      fit = patch_one(S, (int)(p * S.n / np), (int)((p + 1) * S.n / np), W, t);
+      const int a = (int)(p * S.n / np), b = (int)((p + 1) * S.n / np);
+      const int r = patch_rows(S, a, b, W, W.list[0], W.list[1]);
+      if (r == 0) return 0.0;
+      rows += r;
+      own += b - a;
     }
-    if (!fit) continue;
-    if ((double)t.rows > kPatchMaxRatio * (double)t.own) return cut;
-    for (int p = 0; p <= np; ++p) cut.push_back((int)((int64_t)p * S.n / np));
-    return cut;
+    return rows / own;
+  };
+  for (int k = 0; k < (big ? 2 : 1); ++k) {
+    S.shape = k ? kPatchBig : kPatchSmall;
+    int target = std::max(kPatchOwnMin, std::min(k ? 2 * kPatchOwnMax : kPatchOwnMax, (S.n + 255) / 256));
+    int np = 0;
+    double ratio = 0;
+    for (; target >= 128 && ratio == 0; target -= target / 5) {
+      np = (S.n + target - 1) / target;
+      ratio = try_plan(np);
+    }
+    if (ratio == 0) continue;
+    while (ratio > 2 && np > 1) {  // fewer, larger patches while they fit
+      const int fewer = np - std::max(1, np / 5);
+      const double r = try_plan(fewer);
+      if (r == 0) break;
+      np = fewer;
+      ratio = r;
+    }
+    // the larger shape has to be clearly better: its patches take longer to lay out
+    const double cost = patch_cost(k == 1, np, ratio * S.n, S.nu * S.C, pw) * (k ? 1.25 : 1.0);
+    if (cost < best) {
+      best = cost;
+      best_np = np;
+      shape = S.shape;
+    }
+    if (ratio <= 2) break;
   }
+  S.shape = shape;
+  for (int p = 0; p <= best_np && best_np > 0; ++p) cut.push_back((int)((int64_t)p * S.n / best_np));
   return cut;
 }
 
@@ -448,12 +537,12 @@ struct PatchCodes {
   std::vector<double> dict;
 };
 
-static inline PatchCodes patch_code(PatchHost &H, bool matrix) {
+static inline PatchCodes patch_code(PatchHost &H, bool matrix, int bits) {
   PatchCodes K;
   K.dict.assign(kPatchCodes, 0.0);
-  auto halves = [](std::vector<uint32_t> &idx, const std::vector<double> &v, auto &&code) {
+  auto halves = [bits](std::vector<uint32_t> &idx, const std::vector<double> &v, auto &&code) {
     for (size_t e = 0; e < idx.size(); ++e)
-      idx[e] |= (uint32_t)code(v[2 * e]) << kPatchCellBits | (uint32_t)code(v[2 * e + 1]) << (16 + kPatchCellBits);
+      idx[e] |= (uint32_t)code(v[2 * e]) << bits | (uint32_t)code(v[2 * e + 1]) << (16 + bits);
   };
   if (matrix) {
     const std::vector<double> d = patch_codes(H.pval, kPatchCodes);
@@ -519,7 +608,7 @@ static void patch_build(int threads, std::vector<PatchJob<M>> &jobs) {
       J.all.append(p);
       p = PatchHost();
     }
-    J.codes = patch_code(J.all, J.code_matrix);
+    J.codes = patch_code(J.all, J.code_matrix && J.src.shape.bits == kPatchSmall.bits, J.src.shape.bits);
   });
 }
 
@@ -539,6 +628,7 @@ struct PatchView {
 
 struct DPatch {
   int np = 0;
+  bool big = false;    // PatchBig
   bool fused = false;  // `down` restricts (else it writes the residual)
   bool mcode = false, tcode = false;  // matrix entries, transfer entries coded
   int cells = 0, lrows = 0;  // LDS cells and matrix lanes of the largest patch
@@ -645,8 +735,6 @@ __device__ __forceinline__ void put32(X *base, uint32_t i, const X &v) {
   *reinterpret_cast<X *>(reinterpret_cast<char *>(base) + (size_t)(uint32_t)(i * (uint32_t)sizeof(X))) = v;
 }
 
-static constexpr uint32_t kCellMask = (1u << kPatchCellBits) - 1;
-
 // transfer value of a code
 template <class T>
 __device__ __forceinline__ T patch_weight(uint32_t code) {
@@ -654,10 +742,11 @@ __device__ __forceinline__ T patch_weight(uint32_t code) {
 }
 
 // a0 += v.a x[first cell], a1 += v.b x[second cell]; UP: only cells above `above`
-template <bool UP, int NR, class T>
+template <int BITS, bool UP, int NR, class T>
 __device__ __forceinline__ void pair_add(PVec<NR, T> &a0, PVec<NR, T> &a1, uint32_t id, PPair<T> v,
                                          const PVec<NR, T> *xs, int above) {
-  const int i0 = (int)(id & kCellMask), i1 = (int)(id >> 16 & kCellMask);
+  constexpr uint32_t mask = (1u << BITS) - 1;
+  const int i0 = (int)(id & mask), i1 = (int)(id >> 16 & mask);
   if (UP) {
     v.a = i0 > above ? v.a : T(0);
     v.b = i1 > above ? v.b : T(0);
@@ -673,26 +762,21 @@ __device__ __forceinline__ void pair_add(PVec<NR, T> &a0, PVec<NR, T> &a1, uint3
 // matrix entries of a wave's slices in registers: N pairs of each row (longer rows read the rest again
 // in every pass), with their values unless MC (coded: looked up in `dict`, in LDS). Rows of the 2-D
 // auxiliary levels hold at most 6 entries: N = 3 there leaves registers for two FP64 blocks per CU.
-template <class T, bool MC, int N>
+template <class G, class T, bool MC, int N>
 struct PatchRows {
-  uint32_t id[kPatchSlots][N];
-  PPair<T> v[kPatchSlots][N];
-  int o[kPatchSlots], w[kPatchSlots];
+  uint32_t id[G::slots][N];
+  PPair<T> v[G::slots][N];
+  int o[G::slots], w[G::slots];
 
-  // values of pair row `row` (one lane's) with code word c
-  __device__ __forceinline__ PPair<T> value(const PatchView<T> &V, int row, uint32_t lane, uint32_t c,
-                                            const T *dict) const {
-    if constexpr (MC)
-      return PPair<T>{dict[c >> kPatchCellBits & 15u], dict[c >> (16 + kPatchCellBits)]};
-    else
-      return at32(reinterpret_cast<const PPair<T> *>(V.pval) + (size_t)row * 64, lane);
+  __device__ __forceinline__ PPair<T> value(uint32_t c, const T *dict) const {
+    return PPair<T>{dict[c >> G::bits & 15u], dict[c >> (16 + G::bits)]};
   }
 
   template <int J0, int J1>
   __device__ __forceinline__ void load(const PatchView<T> &V, const PatchHead &h, int wv, uint32_t lane) {
 #pragma unroll
     for (int j = J0; j < J1; ++j) {
-      const int k = j * kPatchWaves + wv;
+      const int k = j * G::waves + wv;
       o[j] = h.poff[k];
       w[j] = h.poff[k + 1] - o[j];
       const uint32_t *ip = V.pidx + (size_t)o[j] * 64;
@@ -706,13 +790,13 @@ struct PatchRows {
     }
   }
   // values of the codes (after the dictionary is in LDS)
-  __device__ __forceinline__ void decode(const PatchView<T> &V, const T *dict) {
+  __device__ __forceinline__ void decode(const T *dict) {
     if constexpr (MC) {
 #pragma unroll
-      for (int j = 0; j < kPatchSlots; ++j)
+      for (int j = 0; j < G::slots; ++j)
 #pragma unroll
         for (int q = 0; q < N; ++q)
-          if (q < w[j]) v[j][q] = value(V, 0, 0, id[j][q], dict);
+          if (q < w[j]) v[j][q] = value(id[j][q], dict);
     }
   }
 
@@ -727,8 +811,8 @@ struct PatchRows {
       // unpacked here, not kept unpacked across the passes (32 more registers)
       uint32_t c = id[j][q];
       asm volatile("" : "+v"(c));
-      i0[q] = (int)(c & kCellMask);
-      i1[q] = (int)(c >> 16 & kCellMask);
+      i0[q] = (int)(c & ((1u << G::bits) - 1));
+      i1[q] = (int)(c >> 16 & ((1u << G::bits) - 1));
       x0[q] = xs[i0[q]];
       x1[q] = xs[i1[q]];
     }
@@ -758,13 +842,28 @@ struct PatchRows {
       case 1: add_w<1, UP, NR>(a0, a1, j, xs, above); break;
       case 2: add_w<2, UP, NR>(a0, a1, j, xs, above); break;
       case 3: add_w<3, UP, NR>(a0, a1, j, xs, above); break;
+      case 4:
+        if constexpr (N >= 4) add_w<4, UP, NR>(a0, a1, j, xs, above);
+        break;
       default:
-        if constexpr (N > 3) add_w<N, UP, NR>(a0, a1, j, xs, above);
+        if constexpr (N >= 5) add_w<5, UP, NR>(a0, a1, j, xs, above);
         break;
     }
-    for (int q = N; q < w[j]; ++q) {
-      const uint32_t c = at32(V.pidx + (size_t)(o[j] + q) * 64, lane);
-      pair_add<UP, NR, T>(a0, a1, c, value(V, o[j] + q, lane, c, dict), xs, above);
+    for (int q = N; q < w[j]; q += 4) {  // the rest of long rows, four pairs at a time
+      uint32_t c[4];
+      PPair<T> m[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (q + t < w[j]) {
+          c[t] = at32(V.pidx + (size_t)(o[j] + q + t) * 64, lane);
+          if constexpr (!MC) m[t] = at32(reinterpret_cast<const PPair<T> *>(V.pval) + (size_t)(o[j] + q + t) * 64, lane);
+        }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (q + t < w[j]) {
+          if constexpr (MC) m[t] = value(c[t], dict);
+          pair_add<G::bits, UP, NR, T>(a0, a1, c[t], m[t], xs, above);
+        }
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) a0.v[r] += a1.v[r];
@@ -778,11 +877,12 @@ __device__ __forceinline__ bool patch_owns(int g) { return g >= 0 && !(g & kPatc
 // coarse slices of a wave loaded before the sweeps (coded transfers)
 template <class T>
 constexpr int kPatchCoarse = sizeof(T) == 8 ? 1 : 2;
+static constexpr int kCoarsePairs = 4;  // entry pairs of each
 
 // Forward sweeps from zero on b (BT: its type; FP64 on the original grid in both precisions), x on the
 // own rows, and either the restricted residual bc on the coarse rows owned (fused) or the residual r.
-template <int NR, class T, class BT, bool MC, bool TC>
-__global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC) ? 2 : 4) void k_patch_down(
+template <class G, int NR, class T, class BT, bool MC, bool TC>
+__global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC)) ? 4 : 2) void k_patch_down(
     PatchView<T> V, int cells, int rows, int C, int nu, int fused, const BT *__restrict__ b, const T *__restrict__ dg,
     T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
@@ -792,29 +892,31 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   const uint32_t lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int patch = xcd_block();
-  int g[kPatchSlots];
+  int g[G::slots];
 #pragma unroll
-  for (int j = 0; j < kPatchSlots; ++j)
-    g[j] = at32(V.gidx + (size_t)(patch * kPatchSlices + j * kPatchWaves + wv) * 64, lane);
+  for (int j = 0; j < G::slots; ++j)
+    g[j] = at32(V.gidx + (size_t)(patch * G::slices + j * G::waves + wv) * 64, lane);
   const PatchHead &h = V.head[patch];
   const int ns = h.ns, nco = fused ? h.nco : 0;
   const int stop = done ? *done : 0;  // the solve has ended: nothing is written
-  int turn[kPatchSlots];  // colour of each slice, in scalar registers: the passes read no memory but LDS
+  int turn[G::slots];  // colour of each slice, in scalar registers: the passes read no memory but LDS
 #pragma unroll
-  for (int j = 0; j < kPatchSlots; ++j) turn[j] = h.sc[j] >> 4 * wv & 15;
+  for (int j = 0; j < G::slots; ++j) turn[j] = (int)(h.sc[j] >> 4 * wv & 15);
   if (MC && threadIdx.x < kPatchCodes) dict[threadIdx.x] = V.pval[threadIdx.x];
-  PatchRows<T, MC, TC ? 3 : kPatchPairs> A;
+  // (the rows of the 2-D auxiliary levels hold at most 6 entries: three pairs fit two FP64 blocks per CU)
+  constexpr int pairs = G::waves > 8 ? G::template pairs<T> : TC ? 3 : G::template pairs<T>;
+  PatchRows<G, T, MC, pairs> A;
   // the last slot's 64-bit values wait until b and the diagonal are out of their registers
-  constexpr int early = sizeof(T) == 8 ? kPatchSlots - 1 : kPatchSlots;
+  constexpr int early = sizeof(T) == 8 || G::waves > 8 ? G::slots - 1 : G::slots;
   A.template load<0, early>(V, h, wv, lane);
   X *bs = xs + cells;
   T *ds = reinterpret_cast<T *>(bs + rows);
-  T iv[kPatchSlots];
+  T iv[G::slots];
   {
-    X bv[kPatchSlots];
-    T dv[kPatchSlots];
+    X bv[G::slots];
+    T dv[G::slots];
 #pragma unroll
-    for (int j = 0; j < kPatchSlots; ++j) {
+    for (int j = 0; j < G::slots; ++j) {
       const int i = patch_row(g[j]);
       const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b), i);
 #pragma unroll
@@ -824,8 +926,8 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
     if (stop) return;
     // colour 0 of the first sweep; every other cell starts from zero
 #pragma unroll
-    for (int j = 0; j < kPatchSlots; ++j) {
-      const int k = j * kPatchWaves + wv;
+    for (int j = 0; j < G::slots; ++j) {
+      const int k = j * G::waves + wv;
       if (k >= ns) continue;
       iv[j] = T(1) / dv[j];
       bs[k * 64 + lane] = bv[j];
@@ -835,7 +937,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
       for (int q = 0; q < NR; ++q) o.v[q] = turn[j] == 0 ? bv[j].v[q] * iv[j] : T(0);
       xs[k * 64 + lane] = o;
     }
-    for (int k = ns + wv; k < h.ncs; k += kPatchWaves) {
+    for (int k = ns + wv; k < h.ncs; k += G::waves) {
       X o;
 #pragma unroll
       for (int q = 0; q < NR; ++q) o.v[q] = T(0);
@@ -844,32 +946,32 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   }
   // coarse rows of the restriction: their loads are in flight during the sweeps
   int crow[kPatchCoarse<T>], co[kPatchCoarse<T>], cw[kPatchCoarse<T>];
-  uint32_t cid[kPatchCoarse<T>][kPatchPairs];
+  uint32_t cid[kPatchCoarse<T>][kCoarsePairs];
   if (TC) {
 #pragma unroll
     for (int j = 0; j < kPatchCoarse<T>; ++j) {
-      const int k = j * kPatchWaves + wv;
+      const int k = j * G::waves + wv;
       co[j] = cw[j] = 0;
       crow[j] = -1;
-      static_assert(kPatchCoarse<T> * kPatchWaves <= kPatchHeadCoarse, "offsets in the head");
       if (k < nco) {
-        co[j] = h.roff[k];
-        cw[j] = h.roff[k + 1] - co[j];
+        const bool in_head = k < kPatchHeadCoarse;
+        co[j] = in_head ? h.roff[k] : V.roff[h.coarse0 + k];
+        cw[j] = (in_head ? h.roff[k + 1] : V.roff[h.coarse0 + k + 1]) - co[j];
         crow[j] = at32(V.rrow + (size_t)(h.coarse0 + k) * 64, lane);
       }
 #pragma unroll
-      for (int q = 0; q < kPatchPairs; ++q)
+      for (int q = 0; q < kCoarsePairs; ++q)
         if (q < cw[j]) cid[j][q] = at32(V.ridx + (size_t)(co[j] + q) * 64, lane);
     }
   }
-  A.template load<early, kPatchSlots>(V, h, wv, lane);
+  A.template load<early, G::slots>(V, h, wv, lane);
   __syncthreads();
-  A.decode(V, dict);
+  A.decode(dict);
   for (int s = 0; s < nu; ++s)
     for (int c = s == 0 ? 1 : 0; c < C; ++c) {
 #pragma unroll
-      for (int j = 0; j < kPatchSlots; ++j) {
-        const int k = j * kPatchWaves + wv;
+      for (int j = 0; j < G::slots; ++j) {
+        const int k = j * G::waves + wv;
         if (turn[j] == c) {
           X a = A.template dot<false, NR>(V, j, xs, dict, lane);
 #pragma unroll
@@ -881,8 +983,8 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
     }
   // x out; residual in b's place (zero on the last colour: its pass came last)
 #pragma unroll
-  for (int j = 0; j < kPatchSlots; ++j) {
-    const int k = j * kPatchWaves + wv;
+  for (int j = 0; j < G::slots; ++j) {
+    const int k = j * G::waves + wv;
     if (k >= ns) continue;
     const X xi = xs[k * 64 + lane];
     if (patch_owns(g[j])) put32(reinterpret_cast<X *>(x), g[j], xi);
@@ -907,8 +1009,8 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   if (!fused) return;
   __syncthreads();
   auto add = [&](X &a0, X &a1, uint32_t id) {
-    const PPair<T> v{patch_weight<T>(id >> kPatchCellBits & 15u), patch_weight<T>(id >> (16 + kPatchCellBits))};
-    pair_add<false, NR, T>(a0, a1, id, v, bs, 0);
+    const PPair<T> v{patch_weight<T>(id >> G::bits & (65535u >> G::bits)), patch_weight<T>(id >> (16 + G::bits))};
+    pair_add<G::bits, false, NR, T>(a0, a1, id, v, bs, 0);
   };
   auto put = [&](int row, X a0, const X &a1) {
     if (row < 0) return;
@@ -919,19 +1021,19 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   int k = wv;
   if (TC) {
 #pragma unroll
-    for (int j = 0; j < kPatchCoarse<T>; ++j, k += kPatchWaves)
+    for (int j = 0; j < kPatchCoarse<T>; ++j, k += G::waves)
       if (k < nco) {
         X a0, a1;
 #pragma unroll
         for (int q = 0; q < NR; ++q) a0.v[q] = a1.v[q] = T(0);
 #pragma unroll
-        for (int q = 0; q < kPatchPairs; ++q)
+        for (int q = 0; q < kCoarsePairs; ++q)
           if (q < cw[j]) add(a0, a1, cid[j][q]);
-        for (int q = kPatchPairs; q < cw[j]; ++q) add(a0, a1, at32(V.ridx + (size_t)(co[j] + q) * 64, lane));
+        for (int q = kCoarsePairs; q < cw[j]; ++q) add(a0, a1, at32(V.ridx + (size_t)(co[j] + q) * 64, lane));
         put(crow[j], a0, a1);
       }
   }
-  for (; k < nco; k += kPatchWaves) {
+  for (; k < nco; k += G::waves) {
     const int row = at32(V.rrow + (size_t)(h.coarse0 + k) * 64, lane);
     const int o = V.roff[h.coarse0 + k], w = V.roff[h.coarse0 + k + 1] - o;
     X a0, a1;
@@ -953,7 +1055,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
           if constexpr (TC)
             add(a0, a1, ids[t]);
           else
-            pair_add<false, NR, T>(a0, a1, ids[t], vs[t], bs, 0);
+            pair_add<G::bits, false, NR, T>(a0, a1, ids[t], vs[t], bs, 0);
         }
     }
     put(row, a0, a1);
@@ -962,8 +1064,8 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
 
 // Backward sweeps on b from x + P e, result in xo on the own rows (other patches still read x); with
 // `part` also each patch's share of b.xo.
-template <int NR, class T, class BT, bool MC, bool TC, bool DOT = false>
-__global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC) ? 2 : 4) void k_patch_up(
+template <class G, int NR, class T, class BT, bool MC, bool TC, bool DOT = false>
+__global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC)) ? 4 : 2) void k_patch_up(
     PatchView<T> V, int cells, int C, int nu, const BT *__restrict__ b, const T *__restrict__ id,
     const T *__restrict__ x, const T *__restrict__ e, T *__restrict__ xo, double *__restrict__ part, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
@@ -973,23 +1075,25 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   const uint32_t lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int patch = xcd_block();
-  int g[kPatchSlots];
+  int g[G::slots];
 #pragma unroll
-  for (int j = 0; j < kPatchSlots; ++j)
-    g[j] = at32(V.gidx + (size_t)(patch * kPatchSlices + j * kPatchWaves + wv) * 64, lane);
+  for (int j = 0; j < G::slots; ++j)
+    g[j] = at32(V.gidx + (size_t)(patch * G::slices + j * G::waves + wv) * 64, lane);
   const PatchHead &h = V.head[patch];
   const int ns = h.ns, nst = h.nst;
   const int stop = done ? *done : 0;
-  int turn[kPatchSlots];
+  int turn[G::slots];
 #pragma unroll
-  for (int j = 0; j < kPatchSlots; ++j) turn[j] = h.sc[j] >> 4 * wv & 15;
+  for (int j = 0; j < G::slots; ++j) turn[j] = (int)(h.sc[j] >> 4 * wv & 15);
   if (MC && threadIdx.x < kPatchCodes) dict[threadIdx.x] = V.pval[threadIdx.x];
   X *bs = xs + cells;
-  T iv[kPatchSlots];
-  PatchRows<T, MC, TC ? 3 : kPatchPairs> A;
+  T iv[G::slots];
+  // (the rows of the 2-D auxiliary levels hold at most 6 entries: three pairs fit two FP64 blocks per CU)
+  constexpr int pairs = G::waves > 8 ? G::template pairs<T> : TC ? 3 : G::template pairs<T>;
+  PatchRows<G, T, MC, pairs> A;
   // with 64-bit values the second half of the matrix rows is loaded after the prolongation: both at
   // once do not fit in the registers of two blocks per CU
-  constexpr int early = sizeof(T) == 8 && TC ? kPatchSlots / 2 : kPatchSlots;
+  constexpr int early = G::waves > 8 || (sizeof(T) == 8 && TC) ? G::slots / 2 : G::slots;
   auto column = [](int c) { return TC ? c & 0xfffffff : c; };
   // Start rows, UB slices of a wave at a time: all their loads, then all gathers, then the sums. Coded
   // rows hold at most two entries; others go PW entries at a time.
@@ -1000,7 +1104,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
     X a[UB], ev[UB][PW];
 #pragma unroll
     for (int i = 0; i < UB; ++i) {
-      const int k = k0 + i * kPatchWaves;
+      const int k = k0 + i * G::waves;
       ug[i] = -1;
       o[i] = w[i] = 0;
       if (k < nst) {
@@ -1019,7 +1123,7 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
     between();
 #pragma unroll
     for (int i = 0; i < UB; ++i) {
-      if (k0 + i * kPatchWaves < nst) a[i] = at32(reinterpret_cast<const X *>(x), ug[i] < 0 ? 0 : ug[i]);
+      if (k0 + i * G::waves < nst) a[i] = at32(reinterpret_cast<const X *>(x), ug[i] < 0 ? 0 : ug[i]);
 #pragma unroll
       for (int q = 0; q < PW; ++q)
         if (q < w[i]) ev[i][q] = at32(reinterpret_cast<const X *>(e), column(uc[i][q]));
@@ -1058,10 +1162,10 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
     }
   };
   // right-hand side and diagonal of the rows: their gathers fly with the first start rows'
-  X bv[kPatchSlots];
+  X bv[G::slots];
   start(wv, [&] {
 #pragma unroll
-    for (int j = 0; j < kPatchSlots; ++j) {
+    for (int j = 0; j < G::slots; ++j) {
       const int i = patch_row(g[j]);
       const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b), i);
 #pragma unroll
@@ -1072,17 +1176,17 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   });
   if (stop) return;
 #pragma unroll
-  for (int j = 0; j < kPatchSlots; ++j)
-    if (j * kPatchWaves + wv < ns) bs[(j * kPatchWaves + wv) * 64 + lane] = bv[j];
-  for (int k = wv + UB * kPatchWaves; k < nst; k += UB * kPatchWaves) start(k, [] {});
-  A.template load<early, kPatchSlots>(V, h, wv, lane);
+  for (int j = 0; j < G::slots; ++j)
+    if (j * G::waves + wv < ns) bs[(j * G::waves + wv) * 64 + lane] = bv[j];
+  for (int k = wv + UB * G::waves; k < nst; k += UB * G::waves) start(k, [] {});
+  A.template load<early, G::slots>(V, h, wv, lane);
   __syncthreads();
-  A.decode(V, dict);
+  A.decode(dict);
   for (int s = 0; s < nu; ++s)
     for (int c = C - 1; c >= 0; --c) {
 #pragma unroll
-      for (int j = 0; j < kPatchSlots; ++j) {
-        const int k = j * kPatchWaves + wv;
+      for (int j = 0; j < G::slots; ++j) {
+        const int k = j * G::waves + wv;
         if (turn[j] == c) {
           X y = A.template dot<false, NR>(V, j, xs, dict, lane);
 #pragma unroll
@@ -1098,15 +1202,15 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
   if constexpr (DOT) {
     double v = 0;
 #pragma unroll
-    for (int j = 0; j < kPatchSlots; ++j)
-      if (patch_owns(g[j])) v += at32(b, g[j]) * (double)xs[(j * kPatchWaves + wv) * 64 + lane].v[0];
-    __shared__ double sm[kPatchWaves];
+    for (int j = 0; j < G::slots; ++j)
+      if (patch_owns(g[j])) v += at32(b, g[j]) * (double)xs[(j * G::waves + wv) * 64 + lane].v[0];
+    __shared__ double sm[G::waves];
     v = group_sum<64>(v);
     if (lane == 0) sm[wv] = v;
     __syncthreads();
     if (threadIdx.x == 0) {
       v = 0;
-      for (int i = 0; i < kPatchWaves; ++i) v += sm[i];
+      for (int i = 0; i < G::waves; ++i) v += sm[i];
       part[patch] = v;
     }
   }
@@ -1115,31 +1219,40 @@ __global__ __launch_bounds__(kPatchThreads, NR * sizeof(T) > 8 || (sizeof(T) == 
 // launch of a patch kernel, one block per patch; LDS: x on the cells, b (then the residual) and the
 // diagonal on the rows, `vec` and `scalar` bytes each
 template <class K, class... A>
-static void launch_patch(K kernel, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
+static void launch_patch(K kernel, int threads, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1, A... args) {
   const size_t lds = (size_t)D.cells * vec + (size_t)D.lrows * (vec + scalar);
   if (lds > 64 * 1024)
     HIPCHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)lds));
   if (e0) {
-    hipExtLaunchKernelGGL(kernel, dim3(D.np), dim3(kPatchThreads), lds, s, e0, e1, 0, args...);
+    hipExtLaunchKernelGGL(kernel, dim3(D.np), dim3(threads), lds, s, e0, e1, 0, args...);
     HIPCHECK(hipGetLastError());
   } else {
-    hipLaunchKernelGGL(kernel, dim3(D.np), dim3(kPatchThreads), lds, s, args...);
+    hipLaunchKernelGGL(kernel, dim3(D.np), dim3(threads), lds, s, args...);
   }
 }
 
-// calls f(matrix coded, transfers coded) with the level's variant as compile-time constants
-template <class F>
+// calls f(geometry, matrix coded, transfers coded) with the level's variant as compile-time values; BIG:
+// the larger geometry is possible (its matrices are not coded)
+template <bool BIG, class F>
 static void with_codes(const DPatch &D, F &&f) {
+  if constexpr (BIG)
+    if (D.big) {
+      if (D.tcode)
+        f(PatchBig(), std::false_type(), std::true_type());
+      else
+        f(PatchBig(), std::false_type(), std::false_type());
+      return;
+    }
   if (D.mcode && D.tcode)
-    f(std::true_type(), std::true_type());
+    f(PatchSmall(), std::true_type(), std::true_type());
   else if (D.tcode)
-    f(std::false_type(), std::true_type());
+    f(PatchSmall(), std::false_type(), std::true_type());
   else if (D.mcode)
-    f(std::true_type(), std::false_type());
+    f(PatchSmall(), std::true_type(), std::false_type());
   else
-    f(std::false_type(), std::false_type());
+    f(PatchSmall(), std::false_type(), std::false_type());
 }
 
 }  // namespace asmg
