@@ -599,7 +599,7 @@ int asmg_export(asmg_handle H, const char *name_c, int level, void *buf, int64_t
       }
       return put(v, buf, count);
     }
-    if (name == "coarse_inv") return put(h.coarse_inv, buf, count);
+    if (name == "coarse_inv") return put(H->dev ? device_coarse_inverse(H->dev) : h.coarse_inv, buf, count);
     if (name == "solve_stats") {
       if (!H->dev) return set_err(ASMG_EINVAL, "host-only handle");
       std::vector<int64_t> v = {device_last_iterations(H->dev), device_restarts(H->dev)};

@@ -26,6 +26,7 @@
 #include "batch.hpp"
 #include "common.hpp"
 #include "host_parallel.hpp"
+#include "inverse.hpp"
 #include "patch.hpp"
 #include "trace.hpp"
 
@@ -1621,13 +1622,14 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
       dv->bt_moff = bupload(dv, moff);
       dv->inv64 = balloc<double>(dv, len);
       dv->inv32 = balloc<float>(dv, len);
-      int at = 0;
+      std::vector<InvInput> in;
       for (int k = 0; k <= K; ++k)
         for (int m : bottom_m[k]) {
-          const std::vector<double> &v = H[m]->coarse_inv;
-          if (!v.empty()) HIPCHECK(hipMemcpy(dv->inv64 + moff[at], v.data(), v.size() * 8, hipMemcpyHostToDevice));
-          ++at;
+          in.emplace_back();
+          in.back().A = &H[m]->Al.at(H[m]->lc);
+          coarse_components(*H[m], in.back().comp, in.back().gamma);
         }
+      device_inverses(in, moff, dv->inv64);
       patch_round(len, dv->inv64, dv->inv32);
       std::vector<double *> g64, y64;
       std::vector<float *> g32, y32;

@@ -39,6 +39,7 @@
 #include "common.hpp"
 #include "device.hpp"
 #include "host_parallel.hpp"
+#include "inverse.hpp"
 #include "patch.hpp"
 #include "trace.hpp"
 
@@ -1750,21 +1751,45 @@ static void build_refresh(Device *dv, Hierarchy &h, const HCsr &H, const std::ve
   dv->rf_nslots = (int)slot_map.size();
 }
 
-static void upload_coarse(Device *dv, Hierarchy &h, bool first_time) {
+// the bottom inverse, built on the device; a new coefficient replaces the old inverse only once the new
+// one stands
+static void build_coarse_inverse(Device *dv, Hierarchy &h, bool first_time) {
   const int64_t n = h.nc;
-  std::vector<float> f(h.coarse_inv.begin(), h.coarse_inv.end());
   if (first_time) {
     dv->nc = (int)n;
-    dv->cinv64 = dupload(dv, h.coarse_inv);
-    dv->cinv32 = dupload(dv, f);
+    dv->cinv64 = dalloc<double>(dv, n * n);
+    dv->cinv32 = dalloc<float>(dv, n * n);
     dv->cb64 = dalloc<double>(dv, n);
     dv->cx64 = dalloc<double>(dv, n);
     dv->cb32 = dalloc<float>(dv, n);
     dv->cx32 = dalloc<float>(dv, n);
-  } else if (n > 0) {
-    HIPCHECK(hipMemcpy(dv->cinv64, h.coarse_inv.data(), n * n * 8, hipMemcpyHostToDevice));
-    HIPCHECK(hipMemcpy(dv->cinv32, f.data(), n * n * 4, hipMemcpyHostToDevice));
   }
+  if (n == 0) return;
+  std::vector<InvInput> in(1);
+  in[0].A = &h.Al.at(h.lc);
+  coarse_components(h, in[0].comp, in[0].gamma);
+  struct Temp {
+    void *p = nullptr;
+    ~Temp() {
+      if (p) (void)hipFree(p);
+    }
+  } temp;
+  double *M = dv->cinv64;
+  if (!first_time) {
+    HIPCHECK(hipMalloc(&temp.p, (size_t)(n * n) * 8));
+    M = (double *)temp.p;
+  }
+  device_inverses(in, {0}, M);
+  if (M != dv->cinv64) HIPCHECK(hipMemcpy(dv->cinv64, M, (size_t)(n * n) * 8, hipMemcpyDeviceToDevice));
+  patch_round(n * n, dv->cinv64, dv->cinv32);
+  HIPCHECK(hipDeviceSynchronize());
+}
+
+std::vector<double> device_coarse_inverse(Device *dv) {
+  std::vector<double> v((size_t)dv->nc * dv->nc);
+  HIPCHECK(hipSetDevice(dv->ordinal));
+  if (!v.empty()) HIPCHECK(hipMemcpy(v.data(), dv->cinv64, v.size() * 8, hipMemcpyDeviceToHost));
+  return v;
 }
 
 Device *device_create(Hierarchy &h, int ordinal) {
@@ -1919,7 +1944,8 @@ Device *device_create(Hierarchy &h, int ordinal) {
       jobs[i].all = PatchHost();
     }
     lap("upload");
-    upload_coarse(dv, h, true);
+    build_coarse_inverse(dv, h, true);
+    lap("bottom inverse");
     dv->nested = h.opt.nested;
     if (dv->nested > 0) {
       for (int l = dv->J; l > dv->lc; --l) {
@@ -2008,6 +2034,7 @@ void device_update_values(Device *dv, Hierarchy &h) {
     if (it != h.nb.end()) stage_nb(it->second, L, st[t].H, nst[t]);
   });
   rebuild_patches(dv, h, mats, jobs);
+  build_coarse_inverse(dv, h, false);
   for (int i = 0; i <= naux; ++i) {
     DPatch &D = (i == 0 ? dv->fine : dv->aux[h.J + 1 - i]).pt;
     if (!D.np) continue;
@@ -2032,7 +2059,6 @@ void device_update_values(Device *dv, Hierarchy &h) {
     commit_level(dv, dv->aux[l], st[h.J - l + 1], false, false);
     commit_nb(dv, dv->aux[l].nb, nst[h.J - l + 1], false);
   }
-  upload_coarse(dv, h, false);
   HIPCHECK(hipMemcpy(dv->kappa, h.kappa.data(), h.kappa.size() * 8, hipMemcpyHostToDevice));
   HIPCHECK(hipDeviceSynchronize());
 }

@@ -16,6 +16,8 @@ Device *device_create(Hierarchy &h, int ordinal);
 // Re-upload matrix values after a coefficient update (patterns unchanged).
 void device_update_values(Device *dv, Hierarchy &h);
 void device_destroy(Device *dv);
+// the bottom inverse (nc * nc, row-major)
+std::vector<double> device_coarse_inverse(Device *dv);
 void device_set_precision(Device *dv, int precision);
 
 int device_solve(Device *dv, const double *d_f, double tol, double *d_u, int *iters, double *true_rel, void *stream);

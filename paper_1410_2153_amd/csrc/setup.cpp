@@ -1465,6 +1465,8 @@ void build_coarse(Hierarchy &h) {
   const Csr &A = h.Al.at(h.lc);
   const int64_t n = A.nrows;
   h.nc = n;
+  h.coarse_inv.clear();
+  if (h.opt.device >= 0) return;  // inverted on the device, with its layout
   h.coarse_inv.assign(n * n, 0.0);
   if (n == 0) return;
   for (int64_t i = 0; i < n; ++i)
@@ -1472,6 +1474,42 @@ void build_coarse(Hierarchy &h) {
   // Cholesky factor and explicit inverse; a singular component (a pure Neumann problem: rows
   // summing to zero) is regularised by its rank-one term first
   spd_inverse(h.coarse_inv, n, h.threads, true);
+}
+
+// the same regularisation for the inverse on the device: connected components of A_lc, and for each one
+// whose rows sum to zero gamma = mean diagonal / size (0 for the others)
+void coarse_components(const Hierarchy &h, std::vector<int> &comp, std::vector<double> &gamma) {
+  const Csr &A = h.Al.at(h.lc);
+  const int64_t n = A.nrows;
+  comp.assign(n, -1);
+  gamma.clear();
+  std::vector<int64_t> stack;
+  for (int64_t s = 0; s < n; ++s) {
+    if (comp[s] >= 0) continue;
+    const int id = (int)gamma.size();
+    double scale = 0.0, rmax = 0.0, dsum = 0.0, size = 0.0;
+    comp[s] = id;
+    stack.assign(1, s);
+    while (!stack.empty()) {
+      const int64_t i = stack.back();
+      stack.pop_back();
+      double rs = 0.0;
+      for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p) {
+        const int64_t j = A.ci[p];
+        rs += A.v[p];
+        if (j == i) {
+          scale = std::max(scale, std::fabs(A.v[p]));
+          dsum += A.v[p];
+        } else if (comp[j] < 0 && A.v[p] != 0.0) {
+          comp[j] = id;
+          stack.push_back(j);
+        }
+      }
+      rmax = std::max(rmax, std::fabs(rs));
+      size += 1.0;
+    }
+    gamma.push_back(rmax <= 1e-10 * scale ? dsum / size / size : 0.0);
+  }
 }
 
 // ---------------------------------------------------------------------------

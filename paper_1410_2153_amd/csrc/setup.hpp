@@ -115,7 +115,8 @@ struct Hierarchy {
   std::unordered_map<int, std::vector<uint8_t>> local_set;   // N~_l, lc+1..J (1 = smoothed locally)
   int64_t nc = 0;
   std::vector<double> coarse_inv;     // nc * nc, row-major, explicit inverse of A_lc (regularised
-                                      // on components with zero row sums: pure Neumann problems)
+                                      // on components with zero row sums: pure Neumann problems);
+                                      // host-only handles (the others hold it on the device)
   std::unordered_map<int, NearBnd> nb;  // near-boundary correction, lc+1..J (option nb_layers)
 
   int64_t n() const { return (int64_t)dofs.size(); }
@@ -144,6 +145,7 @@ std::vector<uint8_t> domain_keeps(const Hierarchy &h, const LevelMesh &lm);
 void domain_mixed(const Hierarchy &h, const LevelMesh &lm, std::vector<uint8_t> &kept,
                   std::vector<uint8_t> &touch);
 void build_coarse(Hierarchy &h);
+void coarse_components(const Hierarchy &h, std::vector<int> &comp, std::vector<double> &gamma);
 // near-boundary correction (nearbnd.cpp): J_{l,j} of a level, and every level's set and solver
 std::vector<int64_t> near_boundary_set(Hierarchy &h, int level, int layers);
 void build_near_boundary(Hierarchy &h);
