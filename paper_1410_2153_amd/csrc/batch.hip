@@ -1842,9 +1842,11 @@ static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &
   patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes<false>(D, [&](auto geom, auto mc, auto tc) {
       using G = decltype(geom);
-      launch_patch(k_patch_down<G, NR, T, BT, decltype(mc)::value, decltype(tc)::value>, G::threads, D, NR * sizeof(T), sizeof(T), s,
-                   e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, 1, b, BV<T>::dg(L), BV<T>::x(L), (T *)nullptr,
-                   BV<T>::b(Lc), (const int *)nullptr);
+      constexpr bool MC = decltype(mc)::value, TC = decltype(tc)::value;
+      constexpr int RS = patch_split<T, TC>(NR), N1 = NR / RS;
+      launch_patch(k_patch_down<G, N1, T, BT, MC, TC, RS>, G::threads, D.np * RS, D, N1 * sizeof(T),
+                   patch_diag<T, TC>(N1) ? sizeof(T) : 0, s, e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, 1, b,
+                   BV<T>::dg(L), BV<T>::x(L), (T *)nullptr, BV<T>::b(Lc), (const int *)nullptr);
     });
   });
   if (!Lc.pt.np && Lc.nsmooth > 0)
@@ -1862,7 +1864,9 @@ static void patch_up(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &Lc
   patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes<false>(D, [&](auto geom, auto mc, auto tc) {
       using G = decltype(geom);
-      launch_patch(k_patch_up<G, NR, T, BT, decltype(mc)::value, decltype(tc)::value>, G::threads, D, NR * sizeof(T), 0, s, e0, e1,
+      constexpr bool MC = decltype(mc)::value, TC = decltype(tc)::value;
+      constexpr int RS = patch_split<T, TC>(NR), N1 = NR / RS;
+      launch_patch(k_patch_up<G, N1, T, BT, MC, TC, false, RS>, G::threads, D.np * RS, D, N1 * sizeof(T), 0, s, e0, e1,
                    D.view<T>(), D.cells, L.C, nu, b, BV<T>::id(L), (const T *)BV<T>::x(L),
                    (const T *)b_result<T>(Lc), BV<T>::r(L), (double *)nullptr, (const int *)nullptr);
     });

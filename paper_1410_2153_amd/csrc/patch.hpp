@@ -879,10 +879,32 @@ template <class T>
 constexpr int kPatchCoarse = sizeof(T) == 8 ? 1 : 2;
 static constexpr int kCoarsePairs = 4;  // entry pairs of each
 
+// Waves per SIMD that the registers are held to: four (two blocks of PatchSmall per CU, one of PatchBig),
+// or two where 64-bit values leave no room for that: on the original grid (rows of four pairs, gathers of
+// Pi) and with four values a row. Six for one FP32 value (three blocks) spill: 9.0 ms a solve at 1M rows
+// against 8.7.
+template <class G, class T, bool TC>
+constexpr int patch_waves(int NR) {
+  return G::waves > 8 || sizeof(T) == 4 || (TC && NR <= 2) ? 4 : 2;
+}
+
+// whether `down` keeps the diagonal in LDS between the sweeps and the residual (else it is read again):
+// two FP64 values a row leave no room for it beside a second block
+template <class T, bool TC>
+constexpr bool patch_diag(int NR) { return !(sizeof(T) == 8 && NR == 2 && TC); }
+
+// RS: the vectors hold RS * NR values a row, and block p RS + k serves values k NR .. of patch p. Four
+// FP64 values at once leave one block per CU (LDS, registers) and the memory idle while it computes; two
+// halves run side by side and share the patch's matrix rows in L2 (40 meshes, 2860 patches: `down` 193 ->
+// 187 us, `up` 185 -> 171). The original grid's kernels are bound by their gathers, each half of which
+// fetches the same lines: one block there (`up` 362 us in two halves, 234 in one).
+template <class T, bool TC>
+constexpr int patch_split(int NR) { return NR * sizeof(T) > 16 && TC ? 2 : 1; }
+
 // Forward sweeps from zero on b (BT: its type; FP64 on the original grid in both precisions), x on the
 // own rows, and either the restricted residual bc on the coarse rows owned (fused) or the residual r.
-template <class G, int NR, class T, class BT, bool MC, bool TC>
-__global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC)) ? 4 : 2) void k_patch_down(
+template <class G, int NR, class T, class BT, bool MC, bool TC, int RS = 1>
+__global__ __launch_bounds__(G::threads, (patch_waves<G, T, TC>(NR))) void k_patch_down(
     PatchView<T> V, int cells, int rows, int C, int nu, int fused, const BT *__restrict__ b, const T *__restrict__ dg,
     T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
@@ -891,7 +913,8 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
   X *xs = reinterpret_cast<X *>(patch_lds);
   const uint32_t lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int patch = xcd_block();
+  const int block = xcd_block(), patch = block / RS;
+  const uint32_t sub = block % RS;
   int g[G::slots];
 #pragma unroll
   for (int j = 0; j < G::slots; ++j)
@@ -918,7 +941,7 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
 #pragma unroll
     for (int j = 0; j < G::slots; ++j) {
       const int i = patch_row(g[j]);
-      const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b), i);
+      const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b) + sub, i * RS);
 #pragma unroll
       for (int q = 0; q < NR; ++q) bv[j].v[q] = (T)t.v[q];
       dv[j] = at32(dg, i);
@@ -931,7 +954,7 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
       if (k >= ns) continue;
       iv[j] = T(1) / dv[j];
       bs[k * 64 + lane] = bv[j];
-      ds[k * 64 + lane] = dv[j];
+      if constexpr (patch_diag<T, TC>(NR)) ds[k * 64 + lane] = dv[j];
       X o;
 #pragma unroll
       for (int q = 0; q < NR; ++q) o.v[q] = turn[j] == 0 ? bv[j].v[q] * iv[j] : T(0);
@@ -981,13 +1004,17 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
       }
       __syncthreads();
     }
+  T dv[G::slots];
+  if constexpr (!patch_diag<T, TC>(NR))
+#pragma unroll
+    for (int j = 0; j < G::slots; ++j) dv[j] = at32(dg, patch_row(g[j]));
   // x out; residual in b's place (zero on the last colour: its pass came last)
 #pragma unroll
   for (int j = 0; j < G::slots; ++j) {
     const int k = j * G::waves + wv;
     if (k >= ns) continue;
     const X xi = xs[k * 64 + lane];
-    if (patch_owns(g[j])) put32(reinterpret_cast<X *>(x), g[j], xi);
+    if (patch_owns(g[j])) put32(reinterpret_cast<X *>(x) + sub, g[j] * RS, xi);
     X rv;
     if (turn[j] == C - 1) {
 #pragma unroll
@@ -999,12 +1026,16 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
     } else {
       rv = A.template dot<false, NR>(V, j, xs, dict, lane);
       const X bi = bs[k * 64 + lane];
-      const T d = ds[k * 64 + lane];
+      T d;
+      if constexpr (patch_diag<T, TC>(NR))
+        d = ds[k * 64 + lane];
+      else
+        d = dv[j];
 #pragma unroll
       for (int q = 0; q < NR; ++q) rv.v[q] = bi.v[q] - d * xi.v[q] - rv.v[q];
     }
     bs[k * 64 + lane] = rv;
-    if (!fused && patch_owns(g[j])) put32(reinterpret_cast<X *>(r), g[j], rv);
+    if (!fused && patch_owns(g[j])) put32(reinterpret_cast<X *>(r) + sub, g[j] * RS, rv);
   }
   if (!fused) return;
   __syncthreads();
@@ -1016,7 +1047,7 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
     if (row < 0) return;
 #pragma unroll
     for (int q = 0; q < NR; ++q) a0.v[q] += a1.v[q];
-    put32(reinterpret_cast<X *>(bc), row, a0);
+    put32(reinterpret_cast<X *>(bc) + sub, row * RS, a0);
   };
   int k = wv;
   if (TC) {
@@ -1064,8 +1095,8 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
 
 // Backward sweeps on b from x + P e, result in xo on the own rows (other patches still read x); with
 // `part` also each patch's share of b.xo.
-template <class G, int NR, class T, class BT, bool MC, bool TC, bool DOT = false>
-__global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 || (sizeof(T) == 8 && !TC)) ? 4 : 2) void k_patch_up(
+template <class G, int NR, class T, class BT, bool MC, bool TC, bool DOT = false, int RS = 1>
+__global__ __launch_bounds__(G::threads, (patch_waves<G, T, TC>(NR))) void k_patch_up(
     PatchView<T> V, int cells, int C, int nu, const BT *__restrict__ b, const T *__restrict__ id,
     const T *__restrict__ x, const T *__restrict__ e, T *__restrict__ xo, double *__restrict__ part, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
@@ -1074,7 +1105,8 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
   X *xs = reinterpret_cast<X *>(patch_lds);
   const uint32_t lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int patch = xcd_block();
+  const int block = xcd_block(), patch = block / RS;
+  const uint32_t sub = block % RS;
   int g[G::slots];
 #pragma unroll
   for (int j = 0; j < G::slots; ++j)
@@ -1123,10 +1155,10 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
     between();
 #pragma unroll
     for (int i = 0; i < UB; ++i) {
-      if (k0 + i * G::waves < nst) a[i] = at32(reinterpret_cast<const X *>(x), ug[i] < 0 ? 0 : ug[i]);
+      if (k0 + i * G::waves < nst) a[i] = at32(reinterpret_cast<const X *>(x) + sub, ug[i] < 0 ? 0 : ug[i] * RS);
 #pragma unroll
       for (int q = 0; q < PW; ++q)
-        if (q < w[i]) ev[i][q] = at32(reinterpret_cast<const X *>(e), column(uc[i][q]));
+        if (q < w[i]) ev[i][q] = at32(reinterpret_cast<const X *>(e) + sub, column(uc[i][q]) * RS);
     }
 #pragma unroll
     for (int i = 0; i < UB; ++i) {
@@ -1149,7 +1181,7 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
           }
 #pragma unroll
         for (int q = 0; q < PW; ++q)
-          if (t + q < w[i]) ex[q] = at32(reinterpret_cast<const X *>(e), column(c[q]));
+          if (t + q < w[i]) ex[q] = at32(reinterpret_cast<const X *>(e) + sub, column(c[q]) * RS);
 #pragma unroll
         for (int q = 0; q < PW; ++q)
           if (t + q < w[i]) {
@@ -1167,7 +1199,7 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
 #pragma unroll
     for (int j = 0; j < G::slots; ++j) {
       const int i = patch_row(g[j]);
-      const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b), i);
+      const PVec<NR, BT> t = at32(reinterpret_cast<const PVec<NR, BT> *>(b) + sub, i * RS);
 #pragma unroll
       for (int q = 0; q < NR; ++q) bv[j].v[q] = (T)t.v[q];
       iv[j] = at32(id, i);
@@ -1193,7 +1225,7 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
           for (int q = 0; q < NR; ++q) y.v[q] = (bs[k * 64 + lane].v[q] - y.v[q]) * iv[j];
           xs[k * 64 + lane] = y;
           // the last sweep's value is final
-          if (s == nu - 1 && patch_owns(g[j])) put32(reinterpret_cast<X *>(xo), g[j], y);
+          if (s == nu - 1 && patch_owns(g[j])) put32(reinterpret_cast<X *>(xo) + sub, g[j] * RS, y);
         }
       }
       __syncthreads();
@@ -1216,20 +1248,20 @@ __global__ __launch_bounds__(G::threads, G::waves > 8 || !(NR * sizeof(T) > 8 ||
   }
 }
 
-// launch of a patch kernel, one block per patch; LDS: x on the cells, b (then the residual) and the
+// launch of a patch kernel; LDS: x on the cells, b (then the residual) and the
 // diagonal on the rows, `vec` and `scalar` bytes each
 template <class K, class... A>
-static void launch_patch(K kernel, int threads, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
+static void launch_patch(K kernel, int threads, int grid, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1, A... args) {
   const size_t lds = (size_t)D.cells * vec + (size_t)D.lrows * (vec + scalar);
   if (lds > 64 * 1024)
     HIPCHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)lds));
   if (e0) {
-    hipExtLaunchKernelGGL(kernel, dim3(D.np), dim3(threads), lds, s, e0, e1, 0, args...);
+    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, s, e0, e1, 0, args...);
     HIPCHECK(hipGetLastError());
   } else {
-    hipLaunchKernelGGL(kernel, dim3(D.np), dim3(threads), lds, s, args...);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, s, args...);
   }
 }
 

@@ -79,3 +79,29 @@ def test_coefficient_update_changes_the_coding(first):
         u, it, _ = S.solve_device(f, 1e-8)
         v, jt, _ = R.solve_device(f, 1e-8)
         assert it == jt and torch.equal(u, v)
+
+
+# two and four right-hand sides (four FP64 values go as two blocks of two) on the same sizes in one batch; the
+# bars of the batched parity tests: iterates within 1e-10 of the oracle's after the same number of steps
+@pytest.mark.parametrize("nr", [2, 4])
+@pytest.mark.parametrize("sigma", [0.0, 0.5])
+def test_batched_right_hand_sides(nr, sigma):
+    rng = np.random.default_rng(6)
+    meshes, H, F = [], [], []
+    for name in ("square9", "square33", "wheel", "square95"):
+        X, T, fixed = _mesh(name)
+        kappa = np.exp(sigma * rng.standard_normal(len(T)))
+        meshes.append((X, T, kappa, fixed))
+        H.append(Hierarchy(X, T, kappa, dirichlet=fixed, colouring="smallest_last"))
+        F.append(rng.standard_normal((nr, H[-1].n)))
+    B = A.BatchSolver(meshes)
+    U, its, _ = B.solve(torch.from_numpy(np.concatenate([f.ravel() for f in F])).cuda(), nr, 1e-8)
+    U, off = U.cpu().numpy(), B.offsets(nr)
+    for m, h in enumerate(H):
+        u = U[off[m]:off[m + 1]].reshape(nr, h.n)
+        for r in range(nr):
+            v, it, info = h.solve(F[m][r], 1e-8, record=True)
+            near = any(abs(x - 1e-8) < 1e-3 * 1e-8 for x in info["history"][-2:])
+            assert its[m, r] == it or near
+            if its[m, r] == it:
+                assert np.linalg.norm(u[r] - v) <= 1e-10 * np.linalg.norm(v)
