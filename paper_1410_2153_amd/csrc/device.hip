@@ -1874,6 +1874,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
     // right-hand side).
     std::vector<PatchJob<HCsr>> jobs(naux + 1);
     jobs[0].code_matrix = false;  // its values may be refreshed on the device
+    jobs[0].src.want_cells = true;
     host_parallel(h.threads, naux + 1, [&](int i) {
       DLevel &L = level_of(i);
       if (L.local || (i > 0 && h.nb.count(h.J + 1 - i))) return;
@@ -1999,7 +2000,7 @@ static void rebuild_patches(Device *dv, Hierarchy &h, const std::vector<const HC
   host_parallel(h.threads, naux + 1, [&](int i) {
     const int l = h.J + 1 - i;
     DLevel &L = i == 0 ? dv->fine : dv->aux[l];
-    if (L.cuts.empty() || !mats[i]) return;
+    if (L.cuts.empty()) return;
     const std::vector<int> *cmap = l - 1 > h.lc ? &dv->aux[l - 1].iperm : nullptr;
     Pm[i] = permute(i == 0 ? h.Pi : h.P.at(l), L.perm, cmap, false, nullptr);
     std::vector<int> order = L.iperm;
@@ -2892,13 +2893,9 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
     std::vector<int> slots;
     build_sell(dv, F, H, false, &slots);
     build_refresh(dv, h, H, slots);
-    if (F.pt.np) {
-      std::vector<PatchJob<HCsr>> jobs(1 + h.J - h.lc);
-      std::vector<const HCsr *> mats(jobs.size(), nullptr);
-      mats[0] = &H;
-      jobs[0].src.want_map = true;
-      rebuild_patches(dv, h, mats, jobs);
-      dv->rf_patch_map = dupload(dv, jobs[0].all.pmap);
+    if (F.pt.npair > 0) {
+      dv->rf_patch_map = dalloc<int>(dv, 2 * F.pt.npair);
+      patch_map(F.pt, F.A.rp, F.A.ci, dv->rf_patch_map, s);
     }
     dv->rf_ready = true;
   }

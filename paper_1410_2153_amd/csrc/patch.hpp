@@ -65,6 +65,7 @@ struct alignas(64) PatchHead {
   int ns, ncs;          // matrix slices, cell slices (the first ns are the matrix slices)
   int start0, nst;      // first slice of start rows, slices
   int coarse0, nco;     // first slice of coarse rows, slices
+  int cell0;            // first slice of the cells that are no rows (on request)
   uint64_t sc[PatchBig::slots];         // colour of slice (waves j + i) in bits 4 i of sc[j], 15 = none
   int poff[kPatchBig.slices + 1];       // first pair row of each matrix slice
   int uoff[kPatchBig.cell_slices + 1];  // first prolongation row of each slice of start rows
@@ -77,7 +78,7 @@ struct PatchHost {
   std::vector<int> gidx;            // level row per matrix lane, -1 = none; as many slices a patch as fit
   std::vector<uint32_t> pidx;       // two cells per pair
   std::vector<double> pval;         // two values
-  std::vector<int> pmap;            // matrix entry of each value, -1 = padding (on request)
+  std::vector<int> cgidx;           // level row of each cell that is no row, -1 = none (on request)
   std::vector<int> ugidx, ucell;    // start rows: level row (-1 = none), cell
   std::vector<int> ucol;            // and prolongation row
   std::vector<double> uval;
@@ -87,11 +88,12 @@ struct PatchHost {
   int64_t rows = 0, own = 0;
 
   void append(const PatchHost &b) {
-    const int c0 = (int)(ugidx.size() / 64), r0 = (int)roff.size() - 1;
+    const int c0 = (int)(ugidx.size() / 64), r0 = (int)roff.size() - 1, l0 = (int)(cgidx.size() / 64);
     const int p0 = (int)(pidx.size() / 64), u0 = (int)(ucol.size() / 64), q0 = roff.back();
     for (PatchHead h : b.head) {
       h.start0 += c0;
       h.coarse0 += r0;
+      h.cell0 += l0;
       for (int &o : h.poff) o += p0;
       for (int &o : h.uoff) o += u0;
       for (int &o : h.roff) o += q0;
@@ -104,7 +106,7 @@ struct PatchHost {
     cat(gidx, b.gidx);
     cat(pidx, b.pidx);
     cat(pval, b.pval);
-    cat(pmap, b.pmap);
+    cat(cgidx, b.cgidx);
     cat(ugidx, b.ugidx);
     cat(ucell, b.ucell);
     cat(ucol, b.ucol);
@@ -130,7 +132,7 @@ struct PatchSource {
   const M *P = nullptr;       // prolongation: rows of this level, columns of the coarser one
   int ncoarse = 0;            // rows of the coarser level
   const M *R = nullptr;       // restriction: all rows of the coarser level; null = write the residual
-  bool want_map = false;
+  bool want_cells = false;    // list the cells that are no rows (patch_map reads them)
   PatchShape shape = kPatchSmall;
   // filled by prepare()
   std::vector<int> pos;           // position of each row in the order
@@ -317,6 +319,8 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   while (list.size() % 64) list.push_back(-1);
   for (size_t i = 0; i < list.size(); ++i)
     if (list[i] >= 0) W.cell[list[i]] = (int)i;
+  h.cell0 = (int)(out.cgidx.size() / 64);
+  if (S.want_cells) out.cgidx.insert(out.cgidx.end(), list.begin() + 64 * ns, list.end());
   // own rows: marked by position
   std::vector<uint8_t> own(list.size(), 0);
   for (int i = a; i < b; ++i) own[W.cell[S.order[i]]] = 1;
@@ -333,7 +337,6 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
     h.poff[k] = (int)(base / 64);
     out.pidx.resize(base + (size_t)w * 64, 0);
     out.pval.resize(2 * (base + (size_t)w * 64), 0.0);
-    if (S.want_map) out.pmap.resize(2 * (base + (size_t)w * 64), -1);
     for (int l = 0; l < 64; ++l) {
       const int r = list[64 * k + l];
       if (r < 0) continue;
@@ -345,7 +348,6 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
         const size_t e = base + (size_t)(q >> 1) * 64 + l;
         out.pidx[e] |= (uint32_t)c << (q & 1 ? 16 : 0);
         out.pval[2 * e + (q & 1)] = A.v[p];
-        if (S.want_map) out.pmap[2 * e + (q & 1)] = p;
         ++q;
       }
       for (; q < 2 * w; ++q)  // padding: the row's first neighbour with value 0
@@ -633,7 +635,7 @@ struct DPatch {
   bool mcode = false, tcode = false;  // matrix entries, transfer entries coded
   int cells = 0, lrows = 0;  // LDS cells and matrix lanes of the largest patch
   PatchHead *head = nullptr;
-  int *gidx = nullptr, *ugidx = nullptr, *ucell = nullptr, *ucol = nullptr, *roff = nullptr, *rrow = nullptr;
+  int *gidx = nullptr, *cgidx = nullptr, *ugidx = nullptr, *ucell = nullptr, *ucol = nullptr, *roff = nullptr, *rrow = nullptr;
   uint32_t *pidx = nullptr, *ridx = nullptr;
   double *pval64 = nullptr, *uval64 = nullptr, *rval64 = nullptr;
   float *pval32 = nullptr, *uval32 = nullptr, *rval32 = nullptr;
@@ -689,6 +691,7 @@ static void patch_commit(const PatchHost &H, const PatchCodes &K, DPatch &D, boo
   patch_commit_matrix(H, K, D, up, room32);
   D.head = up(H.head);
   D.gidx = up(H.gidx);
+  if (!H.cgidx.empty()) D.cgidx = up(H.cgidx);
   D.ugidx = up(H.ugidx);
   D.ucell = up(H.ucell);
   D.ucol = up(H.ucol);
@@ -1266,6 +1269,54 @@ __global__ __launch_bounds__(G::threads, (patch_waves<G, T, TC>(NR))) void k_pat
       part[patch] = v;
     }
   }
+}
+
+// map[slot] = entry of the level's matrix (CSR rp, ci, columns ascending) that each stored value of a patch
+// came from, -1 = padding (a repeat of the row's first cell). One block per patch: the rows of its cells go
+// to LDS, every pair looks its two columns up. Run once, at the first change of the coefficient on the
+// device; the host's patches built again for it took 65 of that call's 200 ms at 250k rows.
+static __global__ __launch_bounds__(512) void k_patch_map(const PatchHead *head, const int *__restrict__ gidx,
+                                                          const int *__restrict__ cgidx, const uint32_t *__restrict__ pidx,
+                                                          int slices, int bits, const int *__restrict__ rp,
+                                                          const int *__restrict__ ci, int *__restrict__ map) {
+  extern __shared__ int row_of[];
+  const PatchHead &h = head[blockIdx.x];
+  const int *g = gidx + (size_t)blockIdx.x * slices * 64, *cg = cgidx + (size_t)h.cell0 * 64;
+  for (int i = threadIdx.x; i < 64 * h.ncs; i += 512) {
+    const int r = i < 64 * h.ns ? g[i] : cg[i - 64 * h.ns];
+    row_of[i] = r < 0 ? -1 : patch_row(r);
+  }
+  __syncthreads();
+  const uint32_t mask = (1u << bits) - 1;
+  for (int i = threadIdx.x; i < 64 * h.ns; i += 512) {
+    const int row = row_of[i], k = i >> 6;
+    const int a = row < 0 ? 0 : rp[row], b = row < 0 ? 0 : rp[row + 1];
+    auto entry = [&](int cell) {
+      const int c = row_of[cell];
+      int lo = a, hi = b;
+      while (lo < hi) {
+        const int m = (lo + hi) >> 1;
+        if (ci[m] < c)
+          lo = m + 1;
+        else
+          hi = m;
+      }
+      return lo < b && ci[lo] == c ? lo : -1;
+    };
+    for (int o = h.poff[k], q = o; q < h.poff[k + 1]; ++q) {
+      const size_t at = (size_t)q * 64 + (i & 63);
+      const int c0 = (int)(pidx[at] & mask), c1 = (int)(pidx[at] >> 16 & mask);
+      const int first = (int)(pidx[(size_t)o * 64 + (i & 63)] & mask);
+      map[2 * at] = q > o && c0 == first ? -1 : entry(c0);
+      map[2 * at + 1] = c1 == first ? -1 : entry(c1);
+    }
+  }
+}
+
+static void patch_map(const DPatch &D, const int *rp, const int *ci, int *map, hipStream_t s) {
+  const PatchShape sh = D.big ? kPatchBig : kPatchSmall;
+  hipLaunchKernelGGL(k_patch_map, dim3(D.np), dim3(512), (size_t)D.cells * sizeof(int), s, D.head, D.gidx, D.cgidx,
+                     D.pidx, sh.slices, sh.bits, rp, ci, map);
 }
 
 // launch of a patch kernel; LDS: x on the cells, b (then the residual) and the

@@ -89,10 +89,10 @@ def test_batched_right_hand_sides(nr, sigma):
     rng = np.random.default_rng(6)
     meshes, H, F = [], [], []
     for name in ("square9", "square33", "wheel", "square95"):
-        X, T, fixed = _mesh(name)
+        X, T, _ = _mesh(name)
         kappa = np.exp(sigma * rng.standard_normal(len(T)))
-        meshes.append((X, T, kappa, fixed))
-        H.append(Hierarchy(X, T, kappa, dirichlet=fixed, colouring="smallest_last"))
+        meshes.append((X, T, kappa))
+        H.append(Hierarchy(X, T, kappa, colouring="smallest_last"))
         F.append(rng.standard_normal((nr, H[-1].n)))
     B = A.BatchSolver(meshes)
     U, its, _ = B.solve(torch.from_numpy(np.concatenate([f.ravel() for f in F])).cuda(), nr, 1e-8)
@@ -105,3 +105,21 @@ def test_batched_right_hand_sides(nr, sigma):
             assert its[m, r] == it or near
             if its[m, r] == it:
                 assert np.linalg.norm(u[r] - v) <= 1e-10 * np.linalg.norm(v)
+
+
+# the map from matrix entries to the patches' values, on the sizes above: the original grid's sweeps follow a
+# coefficient set on the device, the auxiliary hierarchy keeps the first one
+@pytest.mark.parametrize("name", ["square9", "square33", "square40", "square95", "wheel"])
+def test_device_coefficient(name):
+    X, T, fixed = _mesh(name)
+    rng = np.random.default_rng(8)
+    kappa = np.exp(0.5 * rng.standard_normal(len(T)))
+    S = A.Solver(X, T, np.ones(len(T)), fixed)
+    H = Hierarchy(X, T, np.ones(len(T)), dirichlet=fixed, colouring="smallest_last")
+    H.A = Hierarchy(X, T, kappa, dirichlet=fixed, colouring="smallest_last").A
+    r = rng.standard_normal(H.n)
+    z = H.preconditioner(nu_aux=2, nu_fine=1)(r)
+    S.set_coefficient_device(torch.from_numpy(kappa).cuda())
+    rd = torch.from_numpy(r).cuda()
+    assert _rel_inf(S.apply_preconditioner(rd).cpu().numpy(), z) <= 1e-12
+    assert _rel_inf(S.apply_preconditioner(rd, precision=A.PREC_MIXED).cpu().numpy(), z) <= 1e-5
