@@ -227,7 +227,7 @@ def cube3d(steps: int, colouring: int = 2, kernel_timing: bool = True, autotune:
             res[key] = {"ms": ms_k, "model_bytes": by_k, "GBs": by_k / ms_k / 1e6}
         ms_gs, by_gs = S.time_kernel(4, reps=10, precision=A.PREC_FP64)
         rec = counter_record("cube2M")
-        res["roofline"] = {"bound": "hbm", "kernel": "asmg::k_sell<0, double, VAR> (Gauss-Seidel colour pass, sliced ELL; VAR = the variant tuned per launch site; traffic from a run with the default, VAR 0)",
+        res["roofline"] = {"bound": "hbm", "kernel": "asmg::k_sell<0, double, VAR> on the levels smoothed by colour passes (sliced ELL; VAR = the variant tuned per launch site), asmg::k_patch_down / k_patch_up on the others (a level's sweeps, residual and transfer over overlapped patches); traffic of the colour pass with the default, VAR 0",
                            "achieved": by_gs / ms_gs / 1e6, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": by_gs / ms_gs / 1e6 / HBM_PEAK_GBS, "traffic": rec.get("traffic_bytes_per_launch"),
                            "bytes_per_launch": by_gs, "ms_per_launch": ms_gs}
@@ -424,7 +424,7 @@ def graded(args):
         ms_b64, by_b64 = S64.time_kernel(2, reps=20, precision=A.PREC_FP64)
         ms_b32, by_b32 = S64.time_kernel(2, reps=20, precision=A.PREC_MIXED)
     crec = counter_record("graded1M")
-    roof = {"bound": "hbm", "kernel": "asmg::k_sell<0, double, VAR> (Gauss-Seidel colour pass, sliced ELL; VAR = the variant tuned per launch site; traffic from a run with the default, VAR 0)",
+    roof = {"bound": "hbm", "kernel": "asmg::k_patch_down, asmg::k_patch_up <PatchGeom, 1, double, ...> (a level's sweeps, residual and restriction, or prolongation and sweeps, over overlapped patches; mean over every such launch in B_co; traffic of k_patch_down on the auxiliary levels)",
             "achieved": by_gs / ms_gs / 1e6, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": by_gs / ms_gs / 1e6 / HBM_PEAK_GBS, "traffic": crec.get("traffic_bytes_per_launch"),
             "bytes_per_launch": by_gs, "ms_per_launch": ms_gs}
@@ -599,10 +599,10 @@ def main():
                    "max_true_rel_residual_fp64": b["fp64"]["max_true_rel_residual"], "setup_s": b["setup_s"]},
         "mixed": b["mixed"],
         "vcycle": vc,
-        "roofline": {"bound": "hbm", "kernel": "asmg::kb_sell<MODE, 4, double, VAR> (batched Gauss-Seidel colour "
-                                               "pass, sliced ELL, 4 interleaved right-hand sides; MODE 3 in sweeps "
-                                               "from zero, 0 otherwise; VAR = the variant tuned per launch site; "
-                                               "traffic from a run with the default, VAR 0)",
+        "roofline": {"bound": "hbm", "kernel": "asmg::k_patch_down, asmg::k_patch_up <PatchGeom, NR, double, ...> (every "
+                                               "mesh's sweeps, residual and restriction, or prolongation and sweeps, on "
+                                               "one level over overlapped patches; 4 interleaved right-hand sides; mean "
+                                               "over every such launch in B_co; traffic of the auxiliary levels')",
                      "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
                      "traffic": crec.get("traffic_bytes_per_launch"), "bytes_per_launch": gs["bytes_per_launch"],
                      "ms_per_launch": gs["ms_per_launch"]},

@@ -40,7 +40,9 @@ import os
 import re
 import sys
 
-KERNEL = "asmg::k_sell<0, double, 0>"
+# sweeps from zero, residual and restriction of an auxiliary level over overlapped patches (matrix values
+# stored, transfers coded)
+KERNEL = "asmg::k_patch_down<asmg::PatchGeom<8, 4, 4, 4, 12>, 1, double, double, false, true, 1>"
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = 64 * 2 ** 20 * 8
 
@@ -49,18 +51,20 @@ def _srcs(*names):
     return [os.path.join(ROOT, "paper_1410_2153_amd", "csrc", f) for f in names]
 
 
-KERNEL_SRCS = _srcs("device.hip", "common.hpp")
+KERNEL_SRCS = _srcs("device.hip", "common.hpp", "patch.hpp")
 
 # workload -> dominant kernel, the sources that define it, the bench selection of the counter runs
 WORKLOADS = {
-    "graded1M": dict(kernel="asmg::k_sell<0, double, 0>", sources=("device.hip", "common.hpp"),
+    "graded1M": dict(kernel=KERNEL, sources=("device.hip", "common.hpp", "patch.hpp"),
                      bench="--only graded --no-extra", engine="single",
                      desc="graded 2-D Delaunay mesh, 1002722 vertices, FP64 and mixed solves"),
     "cube2M": dict(kernel="asmg::k_sell<0, double, 0>", sources=("device.hip", "common.hpp"),
                    bench="--only cube3d", engine="single",
                    desc="Kuhn cube 128^3 x 6 tetrahedra, 2048383 unknowns, FP64 and mixed solves"),
-    "batched256x4": dict(kernel=("asmg::kb_sell<0, 4, double, 0>", "asmg::kb_sell<3, 4, double, 0>"),
-                         sources=("batch.hip", "common.hpp"),
+    "batched256x4": dict(kernel=("asmg::k_patch_down<asmg::PatchGeom<8, 4, 4, 4, 12>, 2, double, double, true, true, 2>",
+                                 "asmg::k_patch_up<asmg::PatchGeom<8, 4, 4, 4, 12>, 2, double, double, true, true, "
+                                 "false, 2>"),
+                         sources=("batch.hip", "common.hpp", "patch.hpp"),
                          bench="--only batched", engine="batch",
                          desc="256 jittered squares (sides 32..512) x 4 right-hand sides, FP64 and mixed solves"),
 }
@@ -108,18 +112,18 @@ def _targs(name):
 
 def _bco_kernel(name, prec, engine="single"):
     """True for the kernels of one B_co application in precision prec ("double" or "float"):
-    colour passes, residuals, transfers, bottom GEMVs and a first pass run on its own."""
+    patch launches, colour passes, residuals, transfers, bottom GEMVs and a first pass run on its own."""
     if not name.startswith("asmg::"):
         return False
-    base, targs = _targs(name[len("asmg::"):])
+    base, targs = _targs(name[len("asmg::"):])  # (the patch kernels' first argument counts as five)
     if engine == "batch":
         if base == "kb_first_cvt":
             return prec == "float"
-        pos = {"kb_sell": 2, "kb_sell_spmv": 3, "kb_gemv": 1, "kb_first": 1}
+        pos = {"k_patch_down": 6, "k_patch_up": 6, "kb_sell": 2, "kb_sell_spmv": 3, "kb_gemv": 1, "kb_first": 1}
     else:
         if base == "k_gs_first_cvt":
             return prec == "float"
-        pos = {"k_sell": 1, "k_sell_spmv": 2, "k_gemv": 0, "k_gs_first": 0}
+        pos = {"k_patch_down": 6, "k_patch_up": 6, "k_sell": 1, "k_sell_spmv": 2, "k_gemv": 0, "k_gs_first": 0}
     return base in pos and len(targs) > pos[base] and targs[pos[base]] == prec
 
 

@@ -7,17 +7,18 @@
 // P_l^T, stored explicitly in the internal numbering) are sliced ELL with 64-row
 // slices, one row per wave lane; the diagonal is held apart (diag and 1/diag);
 // values in FP64 and FP32 copies. The bottom level keeps the unknown order and
-// holds the explicit inverse of its matrix (from the Cholesky factor built on the
-// host), applied as a wave-per-row GEMV.
+// holds the explicit inverse of its matrix (inverse.hpp), applied as a block-per-row GEMV.
 //
+// Most levels run their sweeps, residual and transfers in two launches over overlapped
+// patches (patch.hpp); the slice kernels below serve the others, one launch per colour.
 // A slice kernel is latency-bound on short colour passes, so its row product
 // issues all loads of a row before the first gather (three dependent round trips
 // per slice), and its blocks are remapped so that each XCD (own L2) takes a
 // contiguous run of slices. The first colour pass of a sweep from zero runs inside
 // the kernel that writes the level's right-hand side.
 //
-// PCG: reductions write one partial per block and a one-block finalize kernel sums
-// them in a fixed order (reproducible, no atomics); the CG kernels read a device
+// PCG: reductions write one partial per block and every block of the next kernel sums
+// them in the same fixed order (reproducible, no atomics); the CG kernels read a device
 // `done` flag and return when it is set, so the host may enqueue (replay a graph of)
 // several iterations ahead and the iteration count stays exact.
 #include <hip/hip_runtime.h>
@@ -350,9 +351,9 @@ __global__ __launch_bounds__(BS) void k_scatter_cvt(int n, const int *__restrict
 }
 
 // Reductions: a producer kernel runs a bounded grid-stride grid (at most RED_BLOCKS blocks, or
-// the handle's smaller cap) and writes one partial per block; a one-block finalize kernel
-// reduces the partials in a fixed order and updates the PCG scalars. No atomics, reproducible
-// results.
+// the handle's smaller cap) and writes one partial per block; each block of the kernel that needs
+// the sum (or, outside the iteration, a one-block finalize kernel) adds the partials up in a fixed
+// order. No atomics, reproducible results.
 static constexpr int RED_BLOCKS = 1024;
 
 // f gathered into internal order (perm; null: in place), r = f, u = 0, p = 0; partials of ||f||^2
