@@ -1846,7 +1846,7 @@ static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &
       constexpr int RS = patch_split<T, TC>(NR), N1 = NR / RS;
       launch_patch(k_patch_down<G, N1, T, BT, MC, TC, RS>, G::threads, D.np * RS, D, N1 * sizeof(T),
                    patch_diag<T, TC>(N1) ? sizeof(T) : 0, s, e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, 1, b,
-                   BV<T>::dg(L), BV<T>::x(L), (T *)nullptr, BV<T>::b(Lc), (const int *)nullptr);
+                   BV<T>::dg(L), (const T *)BV<T>::id(L), BV<T>::x(L), (T *)nullptr, BV<T>::b(Lc), (const int *)nullptr);
     });
   });
   if (!Lc.pt.np && Lc.nsmooth > 0)

@@ -904,12 +904,15 @@ constexpr bool patch_diag(int NR) { return !(sizeof(T) == 8 && NR == 2 && TC); }
 template <class T, bool TC>
 constexpr int patch_split(int NR) { return NR * sizeof(T) > 16 && TC ? 2 : 1; }
 
+// The FP64 reciprocal of the diagonal is computed (id holds the same bits); in FP32 id is 1/a_ii rounded
+// once, the value that `up` multiplies with, where the reciprocal of the rounded diagonal can differ in the
+// last bit.
 // Forward sweeps from zero on b (BT: its type; FP64 on the original grid in both precisions), x on the
 // own rows, and either the restricted residual bc on the coarse rows owned (fused) or the residual r.
 template <class G, int NR, class T, class BT, bool MC, bool TC, int RS = 1>
 __global__ __launch_bounds__(G::threads, (patch_waves<G, T, TC>(NR))) void k_patch_down(
     PatchView<T> V, int cells, int rows, int C, int nu, int fused, const BT *__restrict__ b, const T *__restrict__ dg,
-    T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc, const int *__restrict__ done) {
+    const T *__restrict__ id, T *__restrict__ x, T *__restrict__ r, T *__restrict__ bc, const int *__restrict__ done) {
   extern __shared__ __align__(32) unsigned char patch_lds[];
   __shared__ T dict[kPatchCodes];
   using X = PVec<NR, T>;
@@ -948,6 +951,7 @@ __global__ __launch_bounds__(G::threads, (patch_waves<G, T, TC>(NR))) void k_pat
 #pragma unroll
       for (int q = 0; q < NR; ++q) bv[j].v[q] = (T)t.v[q];
       dv[j] = at32(dg, i);
+      if constexpr (sizeof(T) == 4) iv[j] = at32(id, i);
     }
     if (stop) return;
     // colour 0 of the first sweep; every other cell starts from zero
@@ -955,7 +959,7 @@ __global__ __launch_bounds__(G::threads, (patch_waves<G, T, TC>(NR))) void k_pat
     for (int j = 0; j < G::slots; ++j) {
       const int k = j * G::waves + wv;
       if (k >= ns) continue;
-      iv[j] = T(1) / dv[j];
+      if constexpr (sizeof(T) == 8) iv[j] = T(1) / dv[j];
       bs[k * 64 + lane] = bv[j];
       if constexpr (patch_diag<T, TC>(NR)) ds[k * 64 + lane] = dv[j];
       X o;
