@@ -17,7 +17,10 @@
 // (one per lane), dealt to the waves in turn, and cell 64 k + lane of the LDS image is its row. Cells
 // that are read but never computed follow the last slice. The cells whose value counts before the first
 // backward pass form slices of their own (start rows), by the length of their prolongation row. Matrix entries come in pairs: two values and
-// two 16-bit cell numbers, 64 lanes side by side. Matrices with few distinct values (the level matrices
+// two 16-bit cell numbers, 64 lanes side by side; shorter rows of a slice are filled up with products 0 * the
+// row's own first neighbour. A row without any neighbour has no such cell, and another row's may hold anything (a
+// cell that `up` does not write, a non-finite value of another mesh of a batch): those rows form slices of their
+// own, of width 0, and so do prolongation and restriction rows without entries. Matrices with few distinct values (the level matrices
 // of a constant coefficient) keep a 4-bit code above each 12-bit cell number instead of the value, and
 // so do prolongations, whose entries are 1 and 1/2 (above the column number).
 #pragma once
@@ -134,6 +137,7 @@ struct PatchSource {
   const M *R = nullptr;       // restriction: all rows of the coarser level; null = write the residual
   bool want_cells = false;    // list the cells that are no rows (patch_map reads them)
   PatchShape shape = kPatchSmall;
+  bool alone(int r) const { return A->rp[r] == A->rp[r + 1]; }  // no neighbours
   // filled by prepare()
   std::vector<int> pos;           // position of each row in the order
   std::vector<int> cpos0, clist;  // coarse rows by the position of the row that decides their owner
@@ -256,16 +260,16 @@ template <class M>
 static int patch_rows(const PatchSource<M> &S, int a, int b, PatchMarks &W, std::vector<int> &need,
                       std::vector<int> &uni) {
   if (!patch_closure(S, a, b, W, need, uni)) return 0;
-  std::vector<int> count(S.C + 1, 0);
+  std::vector<int> count(2 * S.C, 0);
   int rows = 0;
   for (int r : uni) {
-    const bool row = W.row[r] == W.epoch;
-    count[row ? S.col[r] : S.C]++;
-    rows += row;
+    if (W.row[r] != W.epoch) continue;
+    count[2 * S.col[r] + S.alone(r)]++;
+    ++rows;
   }
   int ns = 0;
-  for (int c = 0; c < S.C; ++c) ns += (count[c] + 63) / 64;
-  return ns > S.shape.slices || ns + (count[S.C] + 63) / 64 > S.shape.cell_slices ? 0 : rows;
+  for (int k : count) ns += (k + 63) / 64;
+  return ns > S.shape.slices || ns + ((int)uni.size() - rows + 63) / 64 > S.shape.cell_slices ? 0 : rows;
 }
 
 // Patch of the rows order[a..b): appended to out; false (nothing appended) where it does not fit.
@@ -276,17 +280,23 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   std::vector<int> &need = W.list[0], &uni = W.list[1];
   if (!patch_closure(S, a, b, W, need, uni)) return false;
   const int E = W.epoch;
-  std::vector<std::vector<int>> by(C);
+  std::vector<std::vector<int>> by(2 * C);  // rows of each colour with neighbours, and without
   std::vector<int> cells;
   for (int i : uni)
     if (W.row[i] == E)
-      by[S.col[i]].push_back(i);
+      by[2 * S.col[i] + S.alone(i)].push_back(i);
     else
       cells.push_back(i);
   int ns = 0;
   for (auto &v : by) ns += ((int)v.size() + 63) / 64;
   const int ncs = ns + ((int)cells.size() + 63) / 64;
   if (ns > S.shape.slices || ncs > S.shape.cell_slices) return false;
+  // start rows: the cells that some backward pass reads as they were
+  auto plen = [&](int r) { return S.P->rp[r + 1] - S.P->rp[r]; };
+  std::vector<std::pair<int, int>> start[2];  // with prolongation entries, without
+  for (int r : need)
+    if (W.need[r] == E && S.col[r] != C - 1) start[plen(r) == 0].push_back({plen(r), r});
+  if ((start[0].size() + 63) / 64 + (start[1].size() + 63) / 64 > (size_t)kPatchBig.cell_slices) return false;
   // spatial order inside a colour: internal numbers ascend with the spatial order there
   PatchHead h{};
   h.start0 = (int)(out.ugidx.size() / 64);
@@ -301,11 +311,11 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   std::vector<int> list;  // row per cell, -1 = empty lane
   std::vector<std::pair<int, int>> key;
   for (uint64_t &x : h.sc) x = ~0ull;
-  for (int c = 0; c < C; ++c) {
-    const int k0 = (int)list.size() / 64;
-    std::sort(by[c].begin(), by[c].end());
+  for (int i = 0; i < 2 * C; ++i) {
+    const int c = i / 2, k0 = (int)list.size() / 64;
+    std::sort(by[i].begin(), by[i].end());
     key.clear();
-    for (int r : by[c]) key.push_back({(kept(r) + 1) / 2, r});
+    for (int r : by[i]) key.push_back({(kept(r) + 1) / 2, r});
     std::stable_sort(key.begin(), key.end(), [](auto &x, auto &y) { return x.first > y.first; });
     for (auto &kr : key) list.push_back(kr.second);
     while (list.size() % 64) list.push_back(-1);
@@ -355,35 +365,28 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
     }
   }
   for (int k = ns; k <= kPatchBig.slices; ++k) h.poff[k] = (int)(out.pidx.size() / 64);
-  // start rows: the cells that some backward pass reads as they were
-  auto plen = [&](int r) { return S.P->rp[r + 1] - S.P->rp[r]; };
-  key.clear();
-  for (int r : need)
-    if (W.need[r] == E && S.col[r] != C - 1) key.push_back({plen(r), r});
-  // in spatial order (the gathers of a slice then share lines), by length inside windows
-  std::sort(key.begin(), key.end(), [&](auto &x, auto &y) { return S.pos[x.second] < S.pos[y.second]; });
-  for (size_t k = 0; k < key.size(); k += 256)
-    std::stable_sort(key.begin() + k, key.begin() + std::min(k + 256, key.size()),
-                     [](auto &x, auto &y) { return x.first > y.first; });
-  for (size_t k = 0; k < key.size(); k += 64) {
-    const int w = key[k].first;
-    const size_t base = out.ucol.size();
-    h.uoff[h.nst++] = (int)(base / 64);
-    out.ucol.resize(base + (size_t)w * 64, 0);
-    out.uval.resize(base + (size_t)w * 64, 0.0);
-    for (size_t l = 0; l < 64; ++l) {
-      const int r = k + l < key.size() ? key[k + l].second : -1;
-      out.ugidx.push_back(r);
-      out.ucell.push_back(r < 0 ? 0 : W.cell[r]);
-      if (r < 0) continue;
-      const int m = plen(r);
-      for (int q = 0; q < w; ++q) {
-        const size_t e = base + (size_t)q * 64 + l;
-        if (q < m) {
-          out.ucol[e] = S.P->ci[S.P->rp[r] + q];
-          out.uval[e] = S.P->v[S.P->rp[r] + q];
-        } else if (m > 0) {
-          out.ucol[e] = S.P->ci[S.P->rp[r]];
+  for (auto &st : start) {
+    // in spatial order (the gathers of a slice then share lines), by length inside windows
+    std::sort(st.begin(), st.end(), [&](auto &x, auto &y) { return S.pos[x.second] < S.pos[y.second]; });
+    for (size_t k = 0; k < st.size(); k += 256)
+      std::stable_sort(st.begin() + k, st.begin() + std::min(k + 256, st.size()),
+                       [](auto &x, auto &y) { return x.first > y.first; });
+    for (size_t k = 0; k < st.size(); k += 64) {
+      const int w = st[k].first;
+      const size_t base = out.ucol.size();
+      h.uoff[h.nst++] = (int)(base / 64);
+      out.ucol.resize(base + (size_t)w * 64, 0);
+      out.uval.resize(base + (size_t)w * 64, 0.0);
+      for (size_t l = 0; l < 64; ++l) {
+        const int r = k + l < st.size() ? st[k + l].second : -1;
+        out.ugidx.push_back(r);
+        out.ucell.push_back(r < 0 ? 0 : W.cell[r]);
+        if (r < 0) continue;
+        const int m = plen(r);
+        for (int q = 0; q < w; ++q) {
+          const size_t e = base + (size_t)q * 64 + l;
+          out.ucol[e] = S.P->ci[S.P->rp[r] + (q < m ? q : 0)];
+          if (q < m) out.uval[e] = S.P->v[S.P->rp[r] + q];
         }
       }
     }
@@ -391,40 +394,45 @@ static bool patch_one(const PatchSource<M> &S, int a, int b, PatchMarks &W, Patc
   for (int k = h.nst; k <= kPatchBig.cell_slices; ++k) h.uoff[k] = (int)(out.ucol.size() / 64);
   // coarse rows
   if (S.R) {
-    key.clear();
     auto len = [&](int k) {
       int w = 0;
       for (int p = S.R->rp[k]; p < S.R->rp[k + 1]; ++p) w += S.col[S.R->ci[p]] != C - 1;
       return w;
     };
-    for (int q = S.cpos0[a]; q < S.cpos0[b]; ++q) key.push_back({(len(S.clist[q]) + 1) / 2, S.clist[q]});
-    std::stable_sort(key.begin(), key.end(), [](auto &x, auto &y) { return x.first > y.first; });
-    for (size_t k = 0; k < key.size(); k += 64) {
-      const int w = key[k].first;
-      const size_t base = (size_t)out.roff.back() * 64;
-      out.ridx.resize(base + (size_t)w * 64, 0);
-      out.rval.resize(2 * (base + (size_t)w * 64), 0.0);
-      for (size_t l = 0; l < 64; ++l) {
-        if (k + l >= key.size()) {
-          out.rrow.push_back(-1);
-          continue;
+    std::vector<std::pair<int, int>> coarse[2];  // with entries, without
+    for (int q = S.cpos0[a]; q < S.cpos0[b]; ++q) {
+      const int m = len(S.clist[q]);
+      coarse[m == 0].push_back({(m + 1) / 2, S.clist[q]});
+    }
+    for (auto &rows : coarse) {
+      std::stable_sort(rows.begin(), rows.end(), [](auto &x, auto &y) { return x.first > y.first; });
+      for (size_t k = 0; k < rows.size(); k += 64) {
+        const int w = rows[k].first;
+        const size_t base = (size_t)out.roff.back() * 64;
+        out.ridx.resize(base + (size_t)w * 64, 0);
+        out.rval.resize(2 * (base + (size_t)w * 64), 0.0);
+        for (size_t l = 0; l < 64; ++l) {
+          if (k + l >= rows.size()) {
+            out.rrow.push_back(-1);
+            continue;
+          }
+          const int row = rows[k + l].second;
+          out.rrow.push_back(row);
+          int q = 0, first = 0;
+          for (int p = S.R->rp[row]; p < S.R->rp[row + 1]; ++p) {
+            if (S.col[S.R->ci[p]] == C - 1) continue;
+            const int c = W.cell[S.R->ci[p]];
+            if (q == 0) first = c;
+            const size_t e = base + (size_t)(q >> 1) * 64 + l;
+            out.ridx[e] |= (uint32_t)c << (q & 1 ? 16 : 0);
+            out.rval[2 * e + (q & 1)] = S.R->v[p];
+            ++q;
+          }
+          for (; q < 2 * w; ++q) out.ridx[base + (size_t)(q >> 1) * 64 + l] |= (uint32_t)first << (q & 1 ? 16 : 0);
         }
-        const int row = key[k + l].second;
-        out.rrow.push_back(row);
-        int q = 0, first = 0;
-        for (int p = S.R->rp[row]; p < S.R->rp[row + 1]; ++p) {
-          if (S.col[S.R->ci[p]] == C - 1) continue;
-          const int c = W.cell[S.R->ci[p]];
-          if (q == 0) first = c;
-          const size_t e = base + (size_t)(q >> 1) * 64 + l;
-          out.ridx[e] |= (uint32_t)c << (q & 1 ? 16 : 0);
-          out.rval[2 * e + (q & 1)] = S.R->v[p];
-          ++q;
-        }
-        for (; q < 2 * w; ++q) out.ridx[base + (size_t)(q >> 1) * 64 + l] |= (uint32_t)first << (q & 1 ? 16 : 0);
+        out.roff.push_back(out.roff.back() + w);
+        ++h.nco;
       }
-      out.roff.push_back(out.roff.back() + w);
-      ++h.nco;
     }
   }
   for (int k = 0; k <= kPatchHeadCoarse; ++k) h.roff[k] = out.roff[h.coarse0 + std::min(k, h.nco)];
