@@ -862,8 +862,8 @@ static T *balloc(BatchDevice *dv, int64_t n) {
   return (T *)p;
 }
 
-template <class T>
-static T *bupload(BatchDevice *dv, const std::vector<T> &v) {
+template <class T, class Al>
+static T *bupload(BatchDevice *dv, const std::vector<T, Al> &v) {
   T *p = balloc<T>(dv, (int64_t)v.size());
   if (!v.empty()) HIPCHECK(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
   return p;
@@ -1242,19 +1242,21 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
     int K = 0;
     dv->n_m.resize(nm);
     dv->dof_off.assign(nm + 1, 0);
-    for (int m = 0; m < nm; ++m) {
+    host_parallel(0, nm, [&](int m) {
       Hierarchy &h = *H[m];
       const std::vector<int> mrank = morton_rank(h);
       colour_perm(h.colour_fine, fine[m].perm, fine[m].iperm, fine[m].coff, &mrank);
       fine[m].morton.resize(mrank.size());
       for (size_t i = 0; i < mrank.size(); ++i) fine[m].morton[mrank[i]] = fine[m].iperm[i];
       const int D = h.J - h.lc;
-      K = std::max(K, D);
       lev[m].resize(D);
       for (int k = 0; k < D; ++k)
         colour_perm(h.colour_aux.at(h.J - k), lev[m][k].perm, lev[m][k].iperm, lev[m][k].coff);
-      dv->n_m[m] = h.n();
-      dv->dof_off[m + 1] = dv->dof_off[m] + h.n();
+    });
+    for (int m = 0; m < nm; ++m) {
+      K = std::max(K, H[m]->J - H[m]->lc);
+      dv->n_m[m] = H[m]->n();
+      dv->dof_off[m + 1] = dv->dof_off[m] + H[m]->n();
     }
     if (dv->dof_off[nm] * 4 > INT32_MAX) throw AsmgError{ASMG_EINVAL, "batch too large"};
     // ---- row layout of every merged level (sequential, cheap): the fine level is mesh-major;
@@ -1330,6 +1332,11 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
     BLevel &L0 = dv->aux[0];
     int Cf = 0;  // colours of the original grids (most over the meshes)
     host_parallel(0, 2, [&](int t) {
+      HMat &M = t == 0 ? fine_img.A : Pi;
+      size_t nnz = 0;
+      for (int m = 0; m < nm; ++m) nnz += t == 0 ? H[m]->A.ci.size() : H[m]->Pi.ci.size();
+      M.ci.reserve(nnz);
+      M.v.reserve(nnz);
       if (t == 0) {
         LevelImage &X = fine_img;
         for (int m = 0; m < nm; ++m) {

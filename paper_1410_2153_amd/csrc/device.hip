@@ -1093,8 +1093,8 @@ static T *dalloc(Device *dv, int64_t n) {
   return (T *)p;
 }
 
-template <class T>
-static T *dupload(Device *dv, const std::vector<T> &v) {
+template <class T, class Al>
+static T *dupload(Device *dv, const std::vector<T, Al> &v) {
   T *p = dalloc<T>(dv, (int64_t)v.size());
   if (!v.empty()) HIPCHECK(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
   return p;
@@ -1115,6 +1115,8 @@ static HCsr permute(const Csr &A, const std::vector<int> &rperm, const std::vect
   B.nrows = (int)rperm.size();
   B.ncols = (int)A.ncols;
   B.rp.assign(B.nrows + 1, 0);
+  B.ci.reserve(A.ci.size());
+  B.v.reserve(A.v.size());
   if (diag) diag->assign(B.nrows, 0.0);
   std::vector<std::pair<int, double>> row;
   for (int i = 0; i < B.nrows; ++i) {
@@ -1593,8 +1595,8 @@ static void stage_nb(const NearBnd &nb, const DLevel &L, const HCsr &H, NbStage 
 
 static std::vector<float> to32(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
 
-template <class T>
-static void dcopy(T *d, const std::vector<T> &v) {
+template <class T, class Al>
+static void dcopy(T *d, const std::vector<T, Al> &v) {
   if (!v.empty()) HIPCHECK(hipMemcpy(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
 }
 
@@ -2055,10 +2057,13 @@ void device_update_values(Device *dv, Hierarchy &h) {
           [&](int64_t n) { return dalloc<float>(dv, n); });
       continue;
     }
-    const std::vector<double> &v = D.mcode ? jobs[i].codes.dict : jobs[i].all.pval;
-    if (D.mcode) dcopy(D.pidx, jobs[i].all.pidx);
-    dcopy(D.pval64, v);
-    patch_round((int64_t)v.size(), D.pval64, D.pval32);
+    if (D.mcode) {
+      dcopy(D.pidx, jobs[i].all.pidx);
+      dcopy(D.pval64, jobs[i].codes.dict);
+    } else {
+      dcopy(D.pval64, jobs[i].all.pval);
+    }
+    patch_round(D.mcode ? kPatchCodes : (int64_t)jobs[i].all.pval.size(), D.pval64, D.pval32);
   }
   commit_level(dv, dv->fine, st[0], false, true);
   for (int l = h.J; l > h.lc; --l) {

@@ -29,6 +29,8 @@
 #include <atomic>
 #include <cmath>
 #include <cstdint>
+#include <memory>
+#include <mutex>
 #include <vector>
 
 #include "common.hpp"
@@ -75,51 +77,118 @@ struct alignas(64) PatchHead {
   int roff[kPatchHeadCoarse + 1];       // first pair row of the first coarse slices
 };
 
-// host image of a level's patches
+// a vector whose plain resize leaves the new elements unwritten: parallel tasks copy into them, and the first
+// touch of the pages is theirs
+template <class T>
+struct RawAlloc : std::allocator<T> {
+  template <class U>
+  struct rebind {
+    using other = RawAlloc<U>;
+  };
+  template <class U>
+  void construct(U *p) {
+    ::new ((void *)p) U;
+  }
+  template <class U, class... A>
+  void construct(U *p, A &&...a) {
+    ::new ((void *)p) U(std::forward<A>(a)...);
+  }
+};
+template <class T>
+using RawVector = std::vector<T, RawAlloc<T>>;
+
+// host image of a level's patches, or of a run of them
 struct PatchHost {
   std::vector<PatchHead> head;
-  std::vector<int> gidx;            // level row per matrix lane, -1 = none; as many slices a patch as fit
-  std::vector<uint32_t> pidx;       // two cells per pair
-  std::vector<double> pval;         // two values
-  std::vector<int> cgidx;           // level row of each cell that is no row, -1 = none (on request)
-  std::vector<int> ugidx, ucell;    // start rows: level row (-1 = none), cell
-  std::vector<int> ucol;            // and prolongation row
-  std::vector<double> uval;
-  std::vector<int> roff{0}, rrow;   // coarse rows owned, and their restriction over cells
-  std::vector<uint32_t> ridx;
-  std::vector<double> rval;
+  RawVector<int> gidx;              // level row per matrix lane, -1 = none; as many slices a patch as fit
+  RawVector<uint32_t> pidx;         // two cells per pair
+  RawVector<double> pval;           // two values
+  RawVector<int> cgidx;             // level row of each cell that is no row, -1 = none (on request)
+  RawVector<int> ugidx, ucell;      // start rows: level row (-1 = none), cell
+  RawVector<int> ucol;              // and prolongation row
+  RawVector<double> uval;
+  RawVector<int> roff, rrow;        // coarse rows owned, and their restriction over cells
+  RawVector<uint32_t> ridx;
+  RawVector<double> rval;
   int64_t rows = 0, own = 0;
+  PatchHost() { roff.push_back(0); }
 
-  void append(const PatchHost &b) {
-    const int c0 = (int)(ugidx.size() / 64), r0 = (int)roff.size() - 1, l0 = (int)(cgidx.size() / 64);
-    const int p0 = (int)(pidx.size() / 64), u0 = (int)(ucol.size() / 64), q0 = roff.back();
-    for (PatchHead h : b.head) {
+  // appends b in two steps: room for its elements, then (any thread) the elements. The values of coded entries
+  // are left out.
+  struct Place {
+    size_t head, gidx, pidx, cgidx, start, ucol, coarse, ridx;
+  };
+  void reserve(const std::vector<PatchHost> &parts, bool pvals, bool tvals) {
+    Place n{};
+    for (const PatchHost &b : parts) {
+      n.head += b.head.size();
+      n.gidx += b.gidx.size();
+      n.pidx += b.pidx.size();
+      n.cgidx += b.cgidx.size();
+      n.start += b.ugidx.size();
+      n.ucol += b.ucol.size();
+      n.coarse += b.rrow.size();
+      n.ridx += b.ridx.size();
+    }
+    head.reserve(n.head);
+    gidx.reserve(n.gidx);
+    pidx.reserve(n.pidx);
+    if (pvals) pval.reserve(2 * n.pidx);
+    cgidx.reserve(n.cgidx);
+    ugidx.reserve(n.start);
+    ucell.reserve(n.start);
+    ucol.reserve(n.ucol);
+    if (tvals) uval.reserve(n.ucol);
+    rrow.reserve(n.coarse);
+    roff.reserve(n.coarse / 64 + 1);
+    ridx.reserve(n.ridx);
+    if (tvals) rval.reserve(2 * n.ridx);
+  }
+  Place room(const PatchHost &b, bool pvals, bool tvals) {
+    const Place at{head.size(), gidx.size(), pidx.size(), cgidx.size(), ugidx.size(), ucol.size(), rrow.size(), ridx.size()};
+    head.resize(at.head + b.head.size());
+    gidx.resize(at.gidx + b.gidx.size());
+    pidx.resize(at.pidx + b.pidx.size());
+    if (pvals) pval.resize(2 * pidx.size());
+    cgidx.resize(at.cgidx + b.cgidx.size());
+    ugidx.resize(at.start + b.ugidx.size());
+    ucell.resize(at.start + b.ucell.size());
+    ucol.resize(at.ucol + b.ucol.size());
+    if (tvals) uval.resize(ucol.size());
+    rrow.resize(at.coarse + b.rrow.size());
+    roff.resize(rrow.size() / 64 + 1);
+    ridx.resize(at.ridx + b.ridx.size());
+    if (tvals) rval.resize(2 * ridx.size());
+    rows += b.rows;
+    own += b.own;
+    return at;
+  }
+  void put(const PatchHost &b, const Place &at, bool pvals, bool tvals) {
+    const int c0 = (int)(at.start / 64), r0 = (int)(at.coarse / 64), l0 = (int)(at.cgidx / 64);
+    const int p0 = (int)(at.pidx / 64), u0 = (int)(at.ucol / 64), q0 = (int)(at.ridx / 64);
+    for (size_t i = 0; i < b.head.size(); ++i) {
+      PatchHead h = b.head[i];
       h.start0 += c0;
       h.coarse0 += r0;
       h.cell0 += l0;
       for (int &o : h.poff) o += p0;
       for (int &o : h.uoff) o += u0;
       for (int &o : h.roff) o += q0;
-      head.push_back(h);
+      head[at.head + i] = h;
     }
-    auto cat = [](auto &x, const auto &y) { x.insert(x.end(), y.begin(), y.end()); };
-    auto shift = [](std::vector<int> &x, const std::vector<int> &y, int d) {
-      for (size_t i = 1; i < y.size(); ++i) x.push_back(y[i] + d);
-    };
-    cat(gidx, b.gidx);
-    cat(pidx, b.pidx);
-    cat(pval, b.pval);
-    cat(cgidx, b.cgidx);
-    cat(ugidx, b.ugidx);
-    cat(ucell, b.ucell);
-    cat(ucol, b.ucol);
-    cat(uval, b.uval);
-    shift(roff, b.roff, q0);
-    cat(rrow, b.rrow);
-    cat(ridx, b.ridx);
-    cat(rval, b.rval);
-    rows += b.rows;
-    own += b.own;
+    auto copy = [](const auto &x, auto &y, size_t o) { std::copy(x.begin(), x.end(), y.begin() + o); };
+    copy(b.gidx, gidx, at.gidx);
+    copy(b.pidx, pidx, at.pidx);
+    if (pvals) copy(b.pval, pval, 2 * at.pidx);
+    copy(b.cgidx, cgidx, at.cgidx);
+    copy(b.ugidx, ugidx, at.start);
+    copy(b.ucell, ucell, at.start);
+    copy(b.ucol, ucol, at.ucol);
+    if (tvals) copy(b.uval, uval, at.ucol);
+    for (size_t i = 1; i < b.roff.size(); ++i) roff[at.coarse / 64 + i] = b.roff[i] + q0;
+    copy(b.rrow, rrow, at.coarse);
+    copy(b.ridx, ridx, at.ridx);
+    if (tvals) copy(b.rval, rval, 2 * at.ridx);
   }
 };
 
@@ -169,7 +238,7 @@ struct PatchSource {
   }
 };
 
-// per-thread marks over a level's rows
+// marks over a level's rows
 struct PatchMarks {
   std::vector<int> need, uni, cell, row;
   std::vector<int> list[2];
@@ -185,7 +254,24 @@ struct PatchMarks {
   }
 };
 
-// Rows and cells of the patch of order[a..b): `uni` all of them (W.row marks the computed ones), `need` the
+// the marks of the threads that build a set of levels
+struct PatchPool {
+  std::mutex mu;
+  std::vector<std::unique_ptr<PatchMarks>> idle;
+  std::unique_ptr<PatchMarks> take() {
+    std::lock_guard<std::mutex> g(mu);
+    if (idle.empty()) return std::make_unique<PatchMarks>();
+    std::unique_ptr<PatchMarks> w = std::move(idle.back());
+    idle.pop_back();
+    return w;
+  }
+  void give(std::unique_ptr<PatchMarks> w) {
+    std::lock_guard<std::mutex> g(mu);
+    idle.push_back(std::move(w));
+  }
+};
+
+// Rows and cells of the patch of order[a..b): `uni` all of them (`row` marks the computed ones), `need` the
 // cells whose value before the first backward pass counts; false where they cannot fit.
 template <class M>
 static bool patch_closure(const PatchSource<M> &S, int a, int b, PatchMarks &W, std::vector<int> &need,
@@ -528,16 +614,16 @@ static std::vector<int> patch_plan(PatchSource<M> &S, bool big) {
   return cut;
 }
 
-// the distinct values of v in ascending order, at most `most` of them (else empty)
-static inline std::vector<double> patch_codes(const std::vector<double> &v, size_t most) {
-  std::vector<double> d;
+// the distinct values of v in ascending order, added to d; false: more than kPatchCodes
+template <class V>
+static bool patch_codes(const V &v, std::vector<double> &d) {
   for (double x : v) {
     auto it = std::lower_bound(d.begin(), d.end(), x);
     if (it != d.end() && *it == x) continue;
-    if (d.size() == most || !(x == x)) return {};
+    if (d.size() == kPatchCodes || !(x == x)) return false;
     d.insert(it, x);
   }
-  return d;
+  return true;
 }
 
 // Codes of a level: of its matrix entries (code, the index of the value in `dict`) and of its transfers
@@ -545,37 +631,59 @@ static inline std::vector<double> patch_codes(const std::vector<double> &v, size
 struct PatchCodes {
   bool matrix = false, transfer = false;
   std::vector<double> dict;
+  int used = 0;  // values in dict
 };
 
-static inline PatchCodes patch_code(PatchHost &H, bool matrix, int bits) {
+// what a run's values allow
+struct PatchValues {
+  std::vector<double> distinct;
+  bool few = false, simple = false;
+  void read(const PatchHost &H, bool matrix) {
+    auto weights = [](const auto &v) {
+      for (double x : v)
+        if (x != 1.0 && x != 0.5 && x != 0.0) return false;
+      return true;
+    };
+    few = matrix && patch_codes(H.pval, distinct);
+    int most = 0;
+    for (int c : H.ucol) most = std::max(most, c);
+    simple = most < 1 << 28 && weights(H.uval) && weights(H.rval);
+  }
+};
+
+static inline PatchCodes patch_code(const std::vector<PatchValues> &V) {
   PatchCodes K;
   K.dict.assign(kPatchCodes, 0.0);
-  auto halves = [bits](std::vector<uint32_t> &idx, const std::vector<double> &v, auto &&code) {
+  std::vector<double> d;
+  K.matrix = K.transfer = !V.empty();
+  for (const PatchValues &v : V) {
+    K.matrix = K.matrix && v.few && patch_codes(v.distinct, d);
+    K.transfer = K.transfer && v.simple;
+  }
+  K.matrix = K.matrix && !d.empty();
+  if (K.matrix) {
+    std::copy(d.begin(), d.end(), K.dict.begin());
+    K.used = (int)d.size();
+  }
+  return K;
+}
+
+// the codes of a run's entries, into their cell and column numbers
+static inline void patch_encode(PatchHost &H, const PatchCodes &K, int bits) {
+  auto halves = [bits](auto &idx, const auto &v, auto &&code) {
     for (size_t e = 0; e < idx.size(); ++e)
       idx[e] |= (uint32_t)code(v[2 * e]) << bits | (uint32_t)code(v[2 * e + 1]) << (16 + bits);
   };
-  if (matrix) {
-    const std::vector<double> d = patch_codes(H.pval, kPatchCodes);
-    if (!d.empty()) {
-      K.matrix = true;
-      std::copy(d.begin(), d.end(), K.dict.begin());
-      halves(H.pidx, H.pval, [&](double x) { return std::lower_bound(d.begin(), d.end(), x) - d.begin(); });
-    }
+  if (K.matrix) {
+    const auto end = K.dict.begin() + K.used;
+    halves(H.pidx, H.pval, [&](double x) { return std::lower_bound(K.dict.begin(), end, x) - K.dict.begin(); });
   }
-  auto simple = [](const std::vector<double> &v) {
-    for (double x : v)
-      if (x != 1.0 && x != 0.5 && x != 0.0) return false;
-    return true;
-  };
-  auto code = [](double x) { return x == 1.0 ? 0 : x == 0.5 ? 1 : 2; };
-  int most = 0;
-  for (int c : H.ucol) most = std::max(most, c);
-  if (simple(H.uval) && simple(H.rval) && most < 1 << 28) {
-    K.transfer = true;
-    for (size_t e = 0; e < H.ucol.size(); ++e) H.ucol[e] = (int)((uint32_t)H.ucol[e] | (uint32_t)code(H.uval[e]) << 28);
+  if (K.transfer) {
+    auto code = [](double x) { return x == 1.0 ? 0 : x == 0.5 ? 1 : 2; };
+    for (size_t e = 0; e < H.ucol.size(); ++e)
+      H.ucol[e] = (int)((uint32_t)H.ucol[e] | (uint32_t)code(H.uval[e]) << 28);
     halves(H.ridx, H.rval, code);
   }
-  return K;
 }
 
 // A level's patches under construction; one task builds a run of kPatchRun patches.
@@ -586,6 +694,8 @@ struct PatchJob {
   PatchSource<M> src;
   std::vector<int> cuts;  // patch boundaries in the spatial order; empty: none
   std::vector<PatchHost> parts;
+  std::vector<PatchValues> values;
+  std::vector<PatchHost::Place> place;
   PatchHost all;
   PatchCodes codes;
   bool code_matrix = true;
@@ -599,26 +709,36 @@ static void patch_build(int threads, std::vector<PatchJob<M>> &jobs) {
   std::vector<std::pair<int, int>> runs;
   for (size_t j = 0; j < jobs.size(); ++j) {
     jobs[j].parts.resize(jobs[j].runs());
+    jobs[j].values.resize(jobs[j].runs());
     for (int t = 0; t < jobs[j].runs(); ++t) runs.push_back({(int)j, t});
   }
+  PatchPool pool;
   host_parallel(threads, (int)runs.size(), [&](int i) {
-    static thread_local PatchMarks W;
     PatchJob<M> &J = jobs[runs[i].first];
     const int t = runs[i].second, np = (int)J.cuts.size() - 1;
+    std::unique_ptr<PatchMarks> W = pool.take();
     for (int p = t * kPatchRun; p < std::min(np, (t + 1) * kPatchRun) && J.fits; ++p)
-      if (!patch_range(J.src, J.cuts[p], J.cuts[p + 1], W, J.parts[t])) J.fits = false;
+      if (!patch_range(J.src, J.cuts[p], J.cuts[p + 1], *W, J.parts[t])) J.fits = false;
+    pool.give(std::move(W));
+    J.values[t].read(J.parts[t], J.code_matrix && J.src.shape.bits == kPatchSmall.bits);
   });
-  host_parallel(threads, (int)jobs.size(), [&](int j) {
-    PatchJob<M> &J = jobs[j];
+  for (PatchJob<M> &J : jobs) {
     if (!J.fits) {
       J.cuts.clear();
       J.parts.clear();
+      J.values.clear();
     }
-    for (PatchHost &p : J.parts) {
-      J.all.append(p);
-      p = PatchHost();
-    }
-    J.codes = patch_code(J.all, J.code_matrix && J.src.shape.bits == kPatchSmall.bits, J.src.shape.bits);
+    J.codes = patch_code(J.values);
+    J.all.reserve(J.parts, !J.codes.matrix, !J.codes.transfer);
+    for (const PatchHost &p : J.parts) J.place.push_back(J.all.room(p, !J.codes.matrix, !J.codes.transfer));
+  }
+  host_parallel(threads, (int)runs.size(), [&](int i) {
+    PatchJob<M> &J = jobs[runs[i].first];
+    if (J.parts.empty()) return;
+    PatchHost &p = J.parts[runs[i].second];
+    patch_encode(p, J.codes, J.src.shape.bits);
+    J.all.put(p, J.place[runs[i].second], !J.codes.matrix, !J.codes.transfer);
+    p = PatchHost();
   });
 }
 
@@ -680,10 +800,10 @@ static void patch_commit_matrix(const PatchHost &H, const PatchCodes &K, DPatch 
   D.mcode = K.matrix;
   D.pidx = up(H.pidx);
   D.npair = (int64_t)H.pidx.size();
-  const std::vector<double> &v = K.matrix ? K.dict : H.pval;
-  D.pval64 = up(v);
-  D.pval32 = room32((int64_t)v.size());
-  patch_round((int64_t)v.size(), D.pval64, D.pval32);
+  const int64_t n = K.matrix ? kPatchCodes : (int64_t)H.pval.size();
+  D.pval64 = K.matrix ? up(K.dict) : up(H.pval);
+  D.pval32 = room32(n);
+  patch_round(n, D.pval64, D.pval32);
 }
 
 // uploads a level's patches; up(vector) -> device copy, room32(n) -> n floats
