@@ -1445,18 +1445,20 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         S.order = smooth_order(i - 1);
         S.col = colour[i - 1];
       }
+      L.pt.use[1] = patch_fp32(dv->d);
+      if (dv->precision == ASMG_PREC_MIXED && !L.pt.use[1]) return;
       S.prepare();
       jobs[i].cuts = patch_plan(S, false);
     });
     jobs[0].code_matrix = false;  // values of the mesh's own geometry
     patch_build(0, jobs);
-    auto patched = [&](int i) { return !jobs[i].cuts.empty(); };
-    // ---- sliced ELL images: the product of the original grids, and what has no patches. Tasks: 0-2 the
+    auto passes = [&](int i) { return jobs[i].cuts.empty() || !patch_fp32(dv->d); };
+    // ---- sliced ELL images: the product of the original grids, and what some cycle does by passes. Tasks: 0-2 the
     // original grids' smoothing, product and residual images, 3-4 Pi and Pi^T, 5..K+4 the auxiliary
     // levels, K+5 the bottom inverses, then the prolongations
     host_parallel(0, 2 * K + 6, [&](int t) {
       if (t == 0) {
-        if (patched(0)) return;
+        if (!passes(0)) return;
         LevelImage &X = fine_img;
         // Gauss-Seidel passes: group c = colour c of every mesh
         Groups groups(Cf);
@@ -1476,7 +1478,7 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         for (int m = 0; m < nm; ++m) mg[m].push_back({r0[m], r1[m]});
         bsell_host(X.A, mg, true, X.cg, &mo);
       } else if (t == 2) {
-        if (patched(0)) return;
+        if (!passes(0)) return;
         // residual after a single forward sweep from zero: r = U x with U the later colours' entries
         // of each row (columns above the row: each mesh numbers its rows colour by colour), negated;
         // the rows that have such entries, in Morton order. The other rows' r stays zero.
@@ -1504,12 +1506,12 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         X.up.nrows = (int)uo.size();  // byte model: rows written, distinct x entries gathered
         X.up.ncols = ucols;
       } else if (t == 3) {
-        if (patched(0)) return;
+        if (!passes(0)) return;
         const std::vector<int> oPi = keep_rows(mo, last);
         bsell_host(Pi, {{{0, (int)oPi.size()}}}, false, pi_img, &oPi);
         transfer_stats(Pi, oPi, pi_img);
       } else if (t == 4) {
-        if (patched(0)) return;
+        if (!passes(0)) return;
         const HMat R = drop_cols(PiT, zero);
         const std::vector<int> oPiT = natural_rows(L0, 0);
         bsell_host(R, {{{0, R.nrows}}}, false, pit_img, &oPiT);
@@ -1518,7 +1520,7 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         const int k = t - 5;
         BLevel &L = dv->aux[k];
         LevelImage &X = aux_img[k];
-        if (k < K && !patched(k + 1)) {
+        if (k < K && passes(k + 1)) {
           Groups groups(L.C);
           for (int c = 0; c < L.C; ++c)
             for (size_t i = 0; i < smooth_m[k].size(); ++i) {
@@ -1530,7 +1532,7 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
         }
       } else {
         const int k = t - (K + 6);
-        if (patched(k + 1)) return;
+        if (!passes(k + 1)) return;
         BLevel &L = dv->aux[k], &Lc = dv->aux[k + 1];
         const HMat &P = Pm[k];
         std::vector<uint8_t> last(P.nrows, 0), zero(P.nrows, 0);
@@ -1643,8 +1645,8 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
       for (BLevel &L : dv->aux) {
         g64.push_back(L.b64);
         g32.push_back(L.b32);
-        y64.push_back(L.pt.np ? L.r64 : L.x64);
-        y32.push_back(L.pt.np ? L.r32 : L.x32);
+        y64.push_back(L.pt.on<double>() ? L.r64 : L.x64);
+        y32.push_back(L.pt.on<float>() ? L.r32 : L.x32);
       }
       dv->bt_g64 = bupload(dv, g64);
       dv->bt_g32 = bupload(dv, g32);
@@ -1821,7 +1823,7 @@ static void slice_launch(BatchDevice *dv, int nslices, hipStream_t s, F &&launch
 
 // V-cycle result of a level: patches write it beside x, which their neighbours still read, in r
 template <class T>
-static T *b_result(BLevel &L) { return L.pt.np ? BV<T>::r(L) : BV<T>::x(L); }
+static T *b_result(BLevel &L) { return L.pt.on<T>() ? BV<T>::r(L) : BV<T>::x(L); }
 
 // One patch launch; it stands for `passes` launch sites of the pass-by-pass path, whose entries in the
 // table of launch shapes it leaves at the default.
@@ -1856,7 +1858,7 @@ static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &
                    BV<T>::dg(L), (const T *)BV<T>::id(L), BV<T>::x(L), (T *)nullptr, BV<T>::b(Lc), (const int *)nullptr);
     });
   });
-  if (!Lc.pt.np && Lc.nsmooth > 0)
+  if (!Lc.pt.on<T>() && Lc.nsmooth > 0)
     hipLaunchKernelGGL((kb_first<NR, T>), dim3(nblk(Lc.nsmooth)), dim3(BS), 0, s, Lc.nsmooth,
                        (const T *)BV<T>::b(Lc), bid0<T>(Lc), BV<T>::x(Lc));
 }
@@ -2015,7 +2017,7 @@ static void b_vcycle(BatchDevice *dv, int k, hipStream_t s) {
     return;
   }
   BLevel &Lc = dv->aux[k + 1];
-  if (L.pt.np) {
+  if (L.pt.on<T>()) {
     patch_down<NR, T>(dv, L, dv->nu_aux, b, Lc, s);
     b_vcycle<NR, T>(dv, k + 1, s);
     patch_up<NR, T>(dv, L, dv->nu_aux, b, Lc, s);
@@ -2037,7 +2039,7 @@ static void b_apply(BatchDevice *dv, const double *r, bool first_done, hipStream
   dv->site = 0;
   dv->shape_pi = sizeof(T) == 4 ? 1 : 0;
   dv->shape_nr = NR;
-  if (F.pt.np) {
+  if (F.pt.on<T>()) {
     patch_down<NR, T>(dv, F, dv->nu_fine, r, dv->aux[0], s);
     b_vcycle<NR, T>(dv, 0, s);
     patch_up<NR, T>(dv, F, dv->nu_fine, r, dv->aux[0], s);
@@ -2086,7 +2088,7 @@ static void b_iteration(BatchDevice *dv, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(dv->ew_blocks), dim3(BS), 0, s, dv->ew_m, dv->ew_r0, dv->ew_r1, dv->u, dv->r, dv->p,
                        dv->q, dv->ctl, dv->partials, bid0<T>(F), BV<T>::b(F), BV<T>::x(F));
   };
-  if (F.pt.np)
+  if (F.pt.on<T>())
     axpy(kb_cg_axpy<NR, T, false>);
   else
     axpy(kb_cg_axpy<NR, T, true>);

@@ -1881,20 +1881,20 @@ Device *device_create(Hierarchy &h, int ordinal) {
     host_parallel(h.threads, naux + 1, [&](int i) {
       DLevel &L = level_of(i);
       if (L.local || (i > 0 && h.nb.count(h.J + 1 - i))) return;
-      // 3-D handles with an FP32 cycle keep the passes: a patch adds up a row in another order, and CG on some
-      // cubes takes a change in the last bits of an FP32 cycle to 1e-9 of the solution (30^3 unknowns, 15 steps:
-      // 1e-14 on most, 3e-12 to 4e-9 on one, by either path, from scaling f alone), so the same sums stay
-      if (h.d == 3 && dv->precision == ASMG_PREC_MIXED) return;
+      if (dv->precision == ASMG_PREC_MIXED && !patch_fp32(h.d)) return;
       const bool fused = i == naux || !level_of(i + 1).local;
       patch_source(jobs[i], L, stage_of(i).H, Pm[i], fused ? &PTm[i] : nullptr, i == 0 ? forder : L.iperm,
                    i == 0 ? dv->nu_fine : dv->nu_aux);
       jobs[i].cuts = patch_plan(jobs[i].src, i > 0);
     });
     patch_build(h.threads, jobs);
-    for (int i = 0; i <= naux; ++i) level_of(i).cuts = jobs[i].cuts;
-    // sliced ELL images: the original grid's (PCG products), those of the levels without patches and
-    // their transfers, and all of them for the nested iteration
-    auto patched = [&](int i) { return !jobs[i].cuts.empty(); };
+    for (int i = 0; i <= naux; ++i) {
+      level_of(i).cuts = jobs[i].cuts;
+      level_of(i).pt.use[1] = patch_fp32(h.d);
+    }
+    // sliced ELL images: the original grid's (PCG products), those of the levels that some cycle smooths by
+    // passes and their transfers, and all of them for the nested iteration
+    auto passes = [&](int i) { return jobs[i].cuts.empty() || !level_of(i).pt.use[0] || !level_of(i).pt.use[1]; };
     host_parallel(h.threads, 3 * (naux + 1), [&](int t) {
       const int i = t / 3;
       DLevel &L = level_of(i);
@@ -1902,7 +1902,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
       const std::vector<int> &order = i == 0 ? forder : L.iperm;
       const std::vector<int> *corder = coarse_map(i);
       if (t % 3 == 0) {
-        if (i == 0 || !patched(i) || h.opt.nested > 0) stage_sell(L, true, stage_of(i));
+        if (i == 0 || passes(i) || h.opt.nested > 0) stage_sell(L, true, stage_of(i));
         if (i > 0) {
           auto it = h.nb.find(h.J + 1 - i);
           if (it != h.nb.end()) stage_nb(it->second, L, stage_of(i).H, nb_st[i - 1]);
@@ -1910,14 +1910,14 @@ Device *device_create(Hierarchy &h, int ordinal) {
       } else if (t % 3 == 1) {
         TransferStage &X = i == 0 ? pi_st : p_st[i - 1];
         stage_shape(Pm[i], X);
-        if (!patched(i) || h.opt.nested > 0) {
+        if (passes(i) || h.opt.nested > 0) {
           stage_transfer(Pm[i], &order, X);
-          if (!patched(i) && ll.second > ll.first) stage_prolong_v(Pm[i], order, ll.first, ll.second, X);
+          if (passes(i) && ll.second > ll.first) stage_prolong_v(Pm[i], order, ll.first, ll.second, X);
         }
       } else {
         TransferStage &X = i == 0 ? pit_st : pt_st[i - 1];
         stage_shape(PTm[i], X);
-        const bool own = !patched(i) || !jobs[i].src.R;  // restricted by its own launch
+        const bool own = passes(i) || !jobs[i].src.R;  // restricted by its own launch
         if (own || h.opt.nested > 0) {
           stage_transfer(PTm[i], corder, X);
           if (own && ll.second > ll.first) stage_restrict_v(PTm[i], corder, ll.first, ll.second, X);
@@ -2364,7 +2364,7 @@ template <class T>
 static T *lvl_b(Device *dv, int l) { return l == dv->lc ? cvec_b<T>(dv) : LV<T>::b(dv->aux[l]); }
 // (patches write their result beside x, which their neighbours still read: in r)
 template <class T>
-static T *result(DLevel &L) { return L.pt.np ? LV<T>::r(L) : LV<T>::x(L); }
+static T *result(DLevel &L) { return L.pt.on<T>() ? LV<T>::r(L) : LV<T>::x(L); }
 template <class T>
 static T *lvl_x(Device *dv, int l) { return l == dv->lc ? cvec_x<T>(dv) : result<T>(dv->aux[l]); }
 
@@ -2516,7 +2516,7 @@ template <class T>
 static void after_down(Device *dv, DLevel &F, const DCsr &PT, int l, hipStream_t s) {
   if (!F.pt.fused) {
     restrict_to<T>(dv, PT, (const T *)LV<T>::r(F), l, s);
-  } else if (l != dv->lc && !dv->aux[l].pt.np) {
+  } else if (l != dv->lc && !dv->aux[l].pt.on<T>()) {
     DLevel &L = dv->aux[l];
     hipLaunchKernelGGL((k_gs_first<T>), dim3(nblk(L.n)), dim3(BS), 0, s, L.n, L.first_rows, (const T *)LV<T>::b(L),
                        LV<T>::id(L), LV<T>::x(L));
@@ -2540,7 +2540,7 @@ static void vcycle(Device *dv, int l, hipStream_t s) {
   DLevel &L = dv->aux[l];
   T *x = LV<T>::x(L);
   T *b = LV<T>::b(L);
-  if (L.pt.np) {
+  if (L.pt.on<T>()) {
     patch_down<T>(dv, L, dv->nu_aux, (const T *)b, lvl_b<T>(dv, l - 1), s);
     after_down<T>(dv, L, L.PT, l - 1, s);
     vcycle<T>(dv, l - 1, s);
@@ -2568,7 +2568,7 @@ static void apply_Bco(Device *dv, const double *r, bool first_done, hipStream_t 
   dv->shape_pi = sizeof(T) == 4 ? 1 : 0;
   T *x = LV<T>::x(F);
   const T *b;
-  if (F.pt.np) {
+  if (F.pt.on<T>()) {
     patch_down<T>(dv, F, dv->nu_fine, r, lvl_b<T>(dv, dv->J), s);
     after_down<T>(dv, F, dv->PiT, dv->J, s);
     vcycle<T>(dv, dv->J, s);
@@ -2638,7 +2638,7 @@ static void nested_start(Device *dv, hipStream_t s) {
     spmv<T, 0>(dv, L.P, NV<T>::e(dv, l - 1), e, s);
     for (int k = 0; k < dv->nested; ++k) {
       residual<T>(dv, L, g, e, LV<T>::b(L), s, true);
-      if (!L.pt.np)
+      if (!L.pt.on<T>())
         hipLaunchKernelGGL((k_gs_first<T>), dim3(nblk(L.n)), dim3(BS), 0, s, L.n, L.first_rows,
                            (const T *)LV<T>::b(L), LV<T>::id(L), LV<T>::x(L));
       vcycle<T>(dv, l, s);
@@ -2671,7 +2671,7 @@ static void nested_start(Device *dv, hipStream_t s) {
 // first colour pass of B_co on r). r.z comes from the last patch launch where its partials fit.
 template <class T>
 static void pcg_tail(Device *dv, hipStream_t s, bool first_done) {
-  const int n = dv->fine.n, np = dv->fine.pt.np;
+  const int n = dv->fine.n, np = dv->fine.pt.on<T>() ? dv->fine.pt.np : 0;
   double *rz = dv->partials + 2 * RED_BLOCKS;
   const bool fused = np > 0 && np <= RED_BLOCKS;
   dv->stop = &dv->ctl->a.done;
@@ -2740,7 +2740,7 @@ static void pcg_iteration(Device *dv, hipStream_t s) {
   const int npq = g;
   double *rr = dv->partials + RED_BLOCKS;
   g = red_grid(dv, n, 1);
-  if (F.pt.np)
+  if (F.pt.on<T>())
     hipLaunchKernelGGL((k_cg_axpy<T, false>), dim3(g), dim3(BS), 0, s, n, dv->u, dv->r, dv->p, dv->q, dv->ctl, pq, npq,
                        rr, 0, (const T *)nullptr, (T *)nullptr, (T *)nullptr);
   else
@@ -2813,8 +2813,8 @@ static int pcg(Device *dv, const double *d_f, double tol, double *d_u, int *iter
   // convergence return at once; one less where B_co has launches that do not), then after every
   // iteration; with no history, every `check_every` (default 4) iterations. The true residual in FP64 and
   // u in the caller's order follow each run, so that the look at the flag is the solve's only wait.
-  bool all = F.pt.np > 0;
-  for (int l = dv->lc + 1; l <= dv->J; ++l) all = all && dv->aux[l].pt.np > 0;
+  bool all = F.pt.on<T>();
+  for (int l = dv->lc + 1; l <= dv->J; ++l) all = all && dv->aux[l].pt.on<T>();
   int run = dv->last_iters[pi] - (all ? 0 : 1);
   const int K = dv->check_every > 0 ? dv->check_every : (dv->last_iters[pi] > 0 ? 1 : 4);
   int restarts = 0;

@@ -742,6 +742,12 @@ static void patch_build(int threads, std::vector<PatchJob<M>> &jobs) {
   });
 }
 
+// Whether the FP32 cycle may run patches. In 3-D it keeps the passes: a patch adds up a row in another order, and CG
+// on some cubes takes a change in the last bits of an FP32 cycle to 1e-9 of the solution (30^3 unknowns, 15 steps:
+// 1e-14 on most, 3e-12 to 4e-9 on one, by either path, from scaling f alone), so the same sums stay. The precision
+// is chosen call by call, so 3-D handles hold both; one created for the FP32 cycle builds no patches.
+static inline bool patch_fp32(int dim) { return dim == 2; }
+
 // device arrays of a level's patches, values in precision T
 template <class T>
 struct PatchView {
@@ -761,6 +767,9 @@ struct DPatch {
   bool big = false;    // PatchBig
   bool fused = false;  // `down` restricts (else it writes the residual)
   bool mcode = false, tcode = false;  // matrix entries, transfer entries coded
+  bool use[2] = {true, true};         // whether the FP64 and the FP32 cycle run them (else the level's passes)
+  template <class T>
+  bool on() const { return np > 0 && use[sizeof(T) == 4]; }
   int cells = 0, lrows = 0;  // LDS cells and matrix lanes of the largest patch
   PatchHead *head = nullptr;
   int *gidx = nullptr, *cgidx = nullptr, *ugidx = nullptr, *ucell = nullptr, *ucol = nullptr, *roff = nullptr, *rrow = nullptr;
