@@ -1885,13 +1885,18 @@ Device *device_create(Hierarchy &h, int ordinal) {
       const bool fused = i == naux || !level_of(i + 1).local;
       patch_source(jobs[i], L, stage_of(i).H, Pm[i], fused ? &PTm[i] : nullptr, i == 0 ? forder : L.iperm,
                    i == 0 ? dv->nu_fine : dv->nu_aux);
-      jobs[i].cuts = patch_plan(jobs[i].src, i > 0);
+      PatchSource<HCsr> &S = jobs[i].src;
+      S.lone = i == 0 && h.d == 2 && i < naux && (!fused || h.nb.count(h.J));
+      jobs[i].cuts = patch_plan(S, i > 0);
+      bool *use = L.pt.use;
+      use[0] = S.use[0];
+      use[1] = S.use[1] && patch_fp32(h.d);
+      // a handle created for the FP32 cycle that runs patches holds no passes beside them
+      if (dv->precision == ASMG_PREC_MIXED) use[0] = use[1];
+      if (!use[0] && !use[1]) jobs[i].cuts.clear();
     });
     patch_build(h.threads, jobs);
-    for (int i = 0; i <= naux; ++i) {
-      level_of(i).cuts = jobs[i].cuts;
-      level_of(i).pt.use[1] = patch_fp32(h.d);
-    }
+    for (int i = 0; i <= naux; ++i) level_of(i).cuts = jobs[i].cuts;
     // sliced ELL images: the original grid's (PCG products), those of the levels that some cycle smooths by
     // passes and their transfers, and all of them for the nested iteration
     auto passes = [&](int i) { return jobs[i].cuts.empty() || !level_of(i).pt.use[0] || !level_of(i).pt.use[1]; };

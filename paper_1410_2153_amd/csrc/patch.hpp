@@ -205,7 +205,9 @@ struct PatchSource {
   int ncoarse = 0;            // rows of the coarser level
   const M *R = nullptr;       // restriction: all rows of the coarser level; null = write the residual
   bool want_cells = false;    // list the cells that are no rows (patch_map reads them)
+  bool lone = false;          // original grid of a 2-D single-mesh handle above a level that runs passes
   PatchShape shape = kPatchSmall;
+  bool use[2] = {true, true}; // whether the patches are faster in an FP64, an FP32 cycle (patch_plan)
   bool alone(int r) const { return A->rp[r] == A->rp[r + 1]; }  // no neighbours
   // filled by prepare()
   std::vector<int> pos;           // position of each row in the order
@@ -543,30 +545,48 @@ static bool patch_range(const PatchSource<M> &S, int a, int b, PatchMarks &W, Pa
 static constexpr int kPatchOwnMin = 256;
 static constexpr int kPatchOwnMax = 1536;
 
-// Estimated us of a level's two patch launches, from measured ones: 5 us each, and beyond that 4 us for
-// every 512 patches of PatchSmall (two per CU at a time), for every 256 of PatchBig 14 and 1.2 for each
-// pass, or its rows (own and halo) at 4 TB/s and some 70 bytes; and the prolongation's gathers, 1.6 us for
+// Estimated us of a level's two patch launches in an FP64 (p = 0) or FP32 cycle, from measured ones: 5 us each, and
+// beyond that 4 us for every 512 patches of PatchSmall (two per CU at a time), for every 256 of PatchBig 14 and 1.2
+// for each pass, or its rows (own and halo) at 4 TB/s and some 70 bytes; and the prolongation's gathers, 1.6 us for
 // each entry of a row beyond two (the original grid: 2-D 6 entries, up 15 us; 3-D 12, 29 us).
-static inline double patch_cost(bool big, int np, double rows, int passes, double pw) {
-  const double one = big ? (14 + 1.2 * passes) * ((np + 255) / 256) : 4.0 * ((np + 511) / 512);
-  return 2 * (5 + std::max(one, 1.75e-5 * rows)) + 1.6 * std::max(0.0, pw - 2);
+// Where the levels below run passes (local smoothing, near-boundary correction), their launch shapes are tuned and
+// the original grid's passes cost a first solve nothing more, so the line is drawn more exactly there: an FP64
+// block has a CU to itself, and beyond 256 patches the second round of blocks costs more than the passes save; FP32
+// rows take 22 ps, and beyond 512 patches the next level's own first pass and restriction weigh as well. Measured, us
+// an iteration that the patches gain with local smoothing: FP64 102k rows +15, 249k +9 (256 patches), 489k -34
+// (398), 998k -41 (813); FP32 +18, +11, +9, -14; with the near-boundary correction: FP64 55k +15, 218k +16, 869k -55;
+// FP32 +16, +26, -39. (Where every level has patches a first FP64 solve of 998k rows takes 19 ms with passes on the
+// original grid, 8 without, and a later one 6.0 against 6.4.)
+template <class M>
+static double patch_cost(const PatchSource<M> &S, bool big, int np, double rows, double pw, int p) {
+  const double gathers = 1.6 * std::max(0.0, pw - 2);
+  if (S.lone && p == 0 && np > 256) return 40.0 * ((np + 255) / 256);
+  if (S.lone && p == 1)
+    return 2 * (5 + std::max(4.0 * ((np + 511) / 512), 2.2e-5 * rows)) + gathers + (np > 512 ? 25 : 0);
+  const double one = big ? (14 + 1.2 * S.nu * S.C) * ((np + 255) / 256) : 4.0 * ((np + 511) / 512);
+  return 2 * (5 + std::max(one, 1.75e-5 * rows)) + gathers;
 }
 
 // and of its passes one by one: one per colour, sweep and direction, the residual and the transfers, 3 us
 // each and 18 more per million rows of their colour (measured in a graph: 2.9 us at 2000 rows, 4.75 at
-// 125,000, 12.5 at 540,000).
-static inline double pass_cost(int n, int C, int nu) { return (2 * nu * C + 3) * (3.0 + 1.8e-5 * n / C); }
+// 125,000, 12.5 at 540,000; on the 2-D original grid 32 in FP64, 21 in FP32). Where the patches write the
+// residual, the restriction is a launch of its own on both sides.
+template <class M>
+static double pass_cost(const PatchSource<M> &S, int p) {
+  const double slope = !S.lone ? 1.8e-5 : p == 0 ? 3.2e-5 : 2.1e-5;
+  return (2 * S.nu * S.C + (S.lone && !S.R ? 2 : 3)) * (3.0 + slope * S.n / S.C);
+}
 
-// Plan of one level's patches: the chunk boundaries in the spatial order, and the shape in S; empty = the
-// passes are faster. `big`: the larger shape may be used.
+// Plan of one level's patches: the chunk boundaries in the spatial order, and in S the shape and the precisions
+// that gain; empty = the passes are faster in both. `big`: the larger shape may be used.
 template <class M>
 static std::vector<int> patch_plan(PatchSource<M> &S, bool big) {
   std::vector<int> cut;
   if (S.n < 1 || S.C < 1 || S.C > kPatchColours || S.n >= 1 << 27) return cut;
   if (S.ncoarse >= 1 << 27) return cut;
   PatchMarks W;
-  const double pw = (double)S.P->ci.size() / S.n, passes = pass_cost(S.n, S.C, S.nu);
-  double best = passes;
+  const double pw = (double)S.P->ci.size() / S.n, passes[2] = {pass_cost(S, 0), pass_cost(S, 1)};
+  double best = 0;  // us gained
   int best_np = 0;
   PatchShape shape = kPatchSmall;
   // computed rows per own row of `np` patches, from up to 5 of them; 0 where one does not fit
@@ -601,11 +621,13 @@ static std::vector<int> patch_plan(PatchSource<M> &S, bool big) {
       ratio = r;
     }
     // the larger shape has to be clearly better: its patches take longer to lay out
-    const double cost = patch_cost(k == 1, np, ratio * S.n, S.nu * S.C, pw) * (k ? 1.25 : 1.0);
-    if (cost < best) {
-      best = cost;
+    double gain[2];
+    for (int p = 0; p < 2; ++p) gain[p] = passes[p] - patch_cost(S, k == 1, np, ratio * S.n, pw, p) * (k ? 1.25 : 1.0);
+    if (std::max(gain[0], gain[1]) > best) {
+      best = std::max(gain[0], gain[1]);
       best_np = np;
       shape = S.shape;
+      for (int p = 0; p < 2; ++p) S.use[p] = gain[p] > 0;
     }
     if (ratio <= 2) break;
   }
