@@ -1055,6 +1055,8 @@ struct Device {
   hipStream_t stream = nullptr;
   hipEvent_t ev_in = nullptr;
   hipGraphExec_t graph[4] = {nullptr, nullptr, nullptr, nullptr};  // one iteration, then kGraphRun
+  size_t graph_nodes[2] = {0, 0};    // of one iteration
+  double graph_saved[2] = {0, 0};    // us that replays of kGraphRun would have saved so far
   // launch shapes of the V-cycle slice kernels per precision and launch site (the k-th slice
   // launch of one B_co application), chosen by the autotuner at the first solve
   std::vector<Shape> shape[2];  // (threads per block, xcd order, kernel variant)
@@ -2761,20 +2763,25 @@ static void pcg_iteration(Device *dv, hipStream_t s) {
 
 // graph of k PCG iterations
 template <class T>
-static hipGraphExec_t iteration_graph(Device *dv, int k, hipStream_t s) {
+static hipGraphExec_t iteration_graph(Device *dv, int k, hipStream_t s, size_t *nodes = nullptr) {
   hipGraph_t g;
   hipGraphExec_t e;
   HIPCHECK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   for (int i = 0; i < k; ++i) pcg_iteration<T>(dv, s);
   HIPCHECK(hipStreamEndCapture(s, &g));
+  if (nodes) HIPCHECK(hipGraphGetNodes(g, nullptr, nodes));
   HIPCHECK(hipGraphInstantiate(&e, g, nullptr, nullptr, 0));
   HIPCHECK(hipGraphDestroy(g));
   return e;
 }
 
-// A graph launch costs about 10 us beside its kernels (1.75 us each where they do nothing): handles that
-// solve again replay kGraphRun iterations at once.
+// A graph launch costs about 10 us beside its kernels (1.75 us each where they do nothing), so handles that solve
+// again replay kGraphRun iterations at once. Capturing and instantiating that graph takes some 6 us for each node
+// of one iteration (7 nodes, a 32 x 32 square: 70 us; 72, a cube of 31^3 cells: 500; 167, near-boundary correction:
+// 860): it is built once the launches that it would have saved add up to that, in the second solve of short
+// iterations, after some more of long ones.
 static constexpr int kGraphRun = 4;
+static constexpr double kGraphLaunchUs = 10.0, kGraphNodeUs = 6.0;
 
 template <class T>
 static void launch_iterations(Device *dv, int k, hipStream_t s) {
@@ -2783,13 +2790,15 @@ static void launch_iterations(Device *dv, int k, hipStream_t s) {
     for (int i = 0; i < k; ++i) pcg_iteration<T>(dv, s);
     return;
   }
+  hipGraphExec_t &run = dv->graph[2 + pi];
+  double &saved = dv->graph_saved[pi];
   if (k >= kGraphRun && dv->last_iters[pi] > 0) {
-    hipGraphExec_t &run = dv->graph[2 + pi];
-    if (!run) run = iteration_graph<T>(dv, kGraphRun, s);
-    for (; k >= kGraphRun; k -= kGraphRun) HIPCHECK(hipGraphLaunch(run, s));
+    if (!run && dv->graph[pi] && saved >= kGraphNodeUs * dv->graph_nodes[pi]) run = iteration_graph<T>(dv, kGraphRun, s);
+    for (; run && k >= kGraphRun; k -= kGraphRun) HIPCHECK(hipGraphLaunch(run, s));
   }
-  if (k > 0 && !dv->graph[pi]) dv->graph[pi] = iteration_graph<T>(dv, 1, s);
+  if (k > 0 && !dv->graph[pi]) dv->graph[pi] = iteration_graph<T>(dv, 1, s, &dv->graph_nodes[pi]);
   for (int i = 0; i < k; ++i) HIPCHECK(hipGraphLaunch(dv->graph[pi], s));
+  if (!run) saved += k * kGraphLaunchUs * (kGraphRun - 1) / kGraphRun;
 }
 
 // x -= mean(x) over the fine unknowns (pure Neumann problems: the constants span the kernel of A)
