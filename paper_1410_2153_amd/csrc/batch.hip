@@ -1602,7 +1602,8 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
     for (int i = 0; i <= K; ++i) {
       patch_commit(
           jobs[i].all, jobs[i].codes, (i == 0 ? dv->fine : dv->aux[i - 1]).pt, true,
-          [&](const auto &v) { return bupload(dv, v); }, [&](int64_t n) { return balloc<float>(dv, n); });
+          [&](const auto &v) { return bupload(dv, v); }, [&](int64_t n) { return balloc<double>(dv, n); },
+          [&](int64_t n) { return balloc<float>(dv, n); });
       jobs[i].all = PatchHost();
     }
     // ---- bottom solves of all levels

@@ -1960,7 +1960,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
       level_of(i).pt.big = jobs[i].src.shape.waves == kPatchBig.waves;
       patch_commit(
           jobs[i].all, jobs[i].codes, level_of(i).pt, jobs[i].src.R != nullptr, [&](const auto &v) { return dupload(dv, v); },
-          [&](int64_t n) { return dalloc<float>(dv, n); });
+          [&](int64_t n) { return dalloc<double>(dv, n); }, [&](int64_t n) { return dalloc<float>(dv, n); });
       jobs[i].all = PatchHost();
     }
     lap("upload");
@@ -2064,18 +2064,12 @@ void device_update_values(Device *dv, Hierarchy &h) {
         if (g) HIPCHECK(hipGraphExecDestroy(g));
         g = nullptr;
       }
-      patch_commit_matrix(
-          jobs[i].all, jobs[i].codes, D, [&](const auto &v) { return dupload(dv, v); },
-          [&](int64_t n) { return dalloc<float>(dv, n); });
-      continue;
+      D.mcode = jobs[i].codes.matrix;
+      patch_values(
+          D, [&](int64_t n) { return dalloc<double>(dv, n); }, [&](int64_t n) { return dalloc<float>(dv, n); });
     }
-    if (D.mcode) {
-      dcopy(D.pidx, jobs[i].all.pidx);
-      dcopy(D.pval64, jobs[i].codes.dict);
-    } else {
-      dcopy(D.pval64, jobs[i].all.pval);
-    }
-    patch_round(D.mcode ? kPatchCodes : (int64_t)jobs[i].all.pval.size(), D.pval64, D.pval32);
+    dcopy(D.pidx, jobs[i].all.pidx);
+    patch_put_values(jobs[i].all, jobs[i].codes, D);
   }
   commit_level(dv, dv->fine, st[0], false, true);
   for (int l = h.J; l > h.lc; --l) {
@@ -2956,7 +2950,7 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
                      F.A.v64, F.sell.sv64, F.sell.sv32);
   if (F.pt.npair > 0)
     hipLaunchKernelGGL(k_refresh_sell, dim3(nblk(2 * F.pt.npair)), dim3(BS), 0, s, (int)(2 * F.pt.npair),
-                       dv->rf_patch_map, F.A.v64, F.pt.pval64, F.pt.pval32);
+                       dv->rf_patch_map, F.A.v64, F.pt.plain64, F.pt.plain32);
   HIPCHECK(hipGetLastError());
   HIPCHECK(hipStreamSynchronize(s));
   return ASMG_OK;

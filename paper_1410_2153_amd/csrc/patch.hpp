@@ -796,18 +796,19 @@ struct DPatch {
   PatchHead *head = nullptr;
   int *gidx = nullptr, *cgidx = nullptr, *ugidx = nullptr, *ucell = nullptr, *ucol = nullptr, *roff = nullptr, *rrow = nullptr;
   uint32_t *pidx = nullptr, *ridx = nullptr;
-  double *pval64 = nullptr, *uval64 = nullptr, *rval64 = nullptr;
-  float *pval32 = nullptr, *uval32 = nullptr, *rval32 = nullptr;
+  // the dictionary or the plain values, as mcode says; a level that has been both holds both
+  double *dict64 = nullptr, *plain64 = nullptr, *uval64 = nullptr, *rval64 = nullptr;
+  float *dict32 = nullptr, *plain32 = nullptr, *uval32 = nullptr, *rval32 = nullptr;
   int64_t npair = 0, nu = 0, nr = 0, rows = 0, nstart = 0, ncoarse = 0;  // stored pairs, entries, rows
   template <class T>
   PatchView<T> view() const {
     PatchView<T> v{head, gidx, pidx, nullptr, ugidx, ucell, ucol, nullptr, roff, rrow, ridx, nullptr};
     if constexpr (sizeof(T) == 8) {
-      v.pval = pval64;
+      v.pval = mcode ? dict64 : plain64;
       v.uval = uval64;
       v.rval = rval64;
     } else {
-      v.pval = pval32;
+      v.pval = mcode ? dict32 : plain32;
       v.uval = uval32;
       v.rval = rval32;
     }
@@ -825,21 +826,29 @@ static inline void patch_round(int64_t n, const double *a, float *b) {
   if (n > 0) hipLaunchKernelGGL(k_patch_round, dim3(nblk(n)), dim3(BS), 0, nullptr, n, a, b);
 }
 
-// matrix entries of a level: coded (dictionary) or plain values, in both precisions
-template <class Up, class Room>
-static void patch_commit_matrix(const PatchHost &H, const PatchCodes &K, DPatch &D, Up &&up, Room &&room32) {
-  D.mcode = K.matrix;
-  D.pidx = up(H.pidx);
-  D.npair = (int64_t)H.pidx.size();
-  const int64_t n = K.matrix ? kPatchCodes : (int64_t)H.pval.size();
-  D.pval64 = K.matrix ? up(K.dict) : up(H.pval);
-  D.pval32 = room32(n);
-  patch_round(n, D.pval64, D.pval32);
+// room for a level's matrix values as mcode says
+template <class Room64, class Room32>
+static void patch_values(DPatch &D, Room64 &&room64, Room32 &&room32) {
+  double *&v64 = D.mcode ? D.dict64 : D.plain64;
+  float *&v32 = D.mcode ? D.dict32 : D.plain32;
+  const int64_t n = D.mcode ? kPatchCodes : 2 * D.npair;
+  if (!v64) v64 = room64(n);
+  if (!v32) v32 = room32(n);
 }
 
-// uploads a level's patches; up(vector) -> device copy, room32(n) -> n floats
-template <class Up, class Room>
-static void patch_commit(const PatchHost &H, const PatchCodes &K, DPatch &D, bool fused, Up &&up, Room &&room32) {
+// matrix values of a level, coded or plain, in both precisions; the room is there
+static inline void patch_put_values(const PatchHost &H, const PatchCodes &K, DPatch &D) {
+  double *v64 = D.mcode ? D.dict64 : D.plain64;
+  const int64_t n = D.mcode ? kPatchCodes : 2 * D.npair;
+  if (n == 0) return;
+  HIPCHECK(hipMemcpy(v64, D.mcode ? K.dict.data() : H.pval.data(), (size_t)n * 8, hipMemcpyHostToDevice));
+  patch_round(n, v64, D.mcode ? D.dict32 : D.plain32);
+}
+
+// uploads a level's patches; up(vector) -> device copy, room64(n), room32(n) -> n values
+template <class Up, class Room64, class Room32>
+static void patch_commit(const PatchHost &H, const PatchCodes &K, DPatch &D, bool fused, Up &&up, Room64 &&room64,
+                         Room32 &&room32) {
   D.np = (int)H.head.size();
   D.fused = fused;
   if (!D.np) return;
@@ -847,7 +856,11 @@ static void patch_commit(const PatchHost &H, const PatchCodes &K, DPatch &D, boo
     D.cells = std::max(D.cells, 64 * h.ncs);
     D.lrows = std::max(D.lrows, 64 * h.ns);
   }
-  patch_commit_matrix(H, K, D, up, room32);
+  D.mcode = K.matrix;
+  D.pidx = up(H.pidx);
+  D.npair = (int64_t)H.pidx.size();
+  patch_values(D, room64, room32);
+  patch_put_values(H, K, D);
   D.head = up(H.head);
   D.gidx = up(H.gidx);
   if (!H.cgidx.empty()) D.cgidx = up(H.cgidx);
