@@ -1010,7 +1010,6 @@ struct DLevel {
   DCsr P, PT;                 // from the next coarser level (aux levels only)
   DNb nb;                     // near-boundary correction (n = 0: none)
   DPatch pt;                  // overlapped patches (np = 0: colour passes one by one)
-  std::vector<int> cuts;      // patch boundaries in the level's spatial order
 };
 
 struct Device {
@@ -1041,8 +1040,7 @@ struct Device {
   int restarts = 0;            // restarts from the true residual in the last solve
   int solve_iters = 0;         // PCG iterations of the last solve
   // operator refresh from a device coefficient (original grid)
-  int *rf_off_ptr = nullptr, *rf_off_el = nullptr, *rf_dg_ptr = nullptr, *rf_dg_el = nullptr, *rf_sell_map = nullptr,
-      *rf_patch_map = nullptr;
+  int *rf_off_ptr = nullptr, *rf_off_el = nullptr, *rf_dg_ptr = nullptr, *rf_dg_el = nullptr, *rf_sell_map = nullptr;
   double *rf_off_w = nullptr, *rf_dg_w = nullptr;
   int rf_nslots = 0;
   bool rf_ready = false;      // the refresh maps are built at the first device coefficient refresh
@@ -1884,7 +1882,6 @@ Device *device_create(Hierarchy &h, int ordinal) {
     // right-hand side).
     std::vector<PatchJob<HCsr>> jobs(naux + 1);
     jobs[0].code_matrix = false;  // its values may be refreshed on the device
-    jobs[0].src.want_cells = true;
     host_parallel(h.threads, naux + 1, [&](int i) {
       DLevel &L = level_of(i);
       if (L.local || (i > 0 && h.nb.count(h.J + 1 - i))) return;
@@ -1893,6 +1890,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
       patch_source(jobs[i], L, stage_of(i).H, Pm[i], fused ? &PTm[i] : nullptr, i == 0 ? forder : L.iperm,
                    i == 0 ? dv->nu_fine : dv->nu_aux);
       PatchSource<HCsr> &S = jobs[i].src;
+      S.want_cells = true;
       S.lone = i == 0 && h.d == 2 && i < naux && (!fused || h.nb.count(h.J));
       jobs[i].cuts = patch_plan(S, i > 0);
       bool *use = L.pt.use;
@@ -1903,7 +1901,6 @@ Device *device_create(Hierarchy &h, int ordinal) {
       if (!use[0] && !use[1]) jobs[i].cuts.clear();
     });
     patch_build(h.threads, jobs);
-    for (int i = 0; i <= naux; ++i) level_of(i).cuts = jobs[i].cuts;
     // sliced ELL images: the original grid's (PCG products), those of the levels that some cycle smooths by
     // passes and their transfers, and all of them for the nested iteration
     auto passes = [&](int i) { return jobs[i].cuts.empty() || !level_of(i).pt.use[0] || !level_of(i).pt.use[1]; };
@@ -2012,71 +2009,89 @@ Device *device_create(Hierarchy &h, int ordinal) {
   return dv;
 }
 
-// the patches of every patched level again (same cuts): new values on the same patterns
-static void rebuild_patches(Device *dv, Hierarchy &h, const std::vector<const HCsr *> &mats, std::vector<PatchJob<HCsr>> &jobs) {
-  const int naux = h.J - h.lc;
-  std::vector<HCsr> Pm(naux + 1), PTm(naux + 1);
-  host_parallel(h.threads, naux + 1, [&](int i) {
-    const int l = h.J + 1 - i;
-    DLevel &L = i == 0 ? dv->fine : dv->aux[l];
-    if (L.cuts.empty()) return;
-    const std::vector<int> *cmap = l - 1 > h.lc ? &dv->aux[l - 1].iperm : nullptr;
-    Pm[i] = permute(i == 0 ? h.Pi : h.P.at(l), L.perm, cmap, false, nullptr);
-    std::vector<int> order = L.iperm;
-    if (i == 0) {
-      const std::vector<int> rank = morton_rank(h);
-      for (size_t k = 0; k < rank.size(); ++k) order[rank[k]] = L.iperm[k];
-    }
-    if (L.pt.fused) PTm[i] = transpose(Pm[i]);
-    patch_source(jobs[i], L, *mats[i], Pm[i], L.pt.fused ? &PTm[i] : nullptr, order, i == 0 ? dv->nu_fine : dv->nu_aux);
-    jobs[i].cuts = L.cuts;
-    jobs[i].src.shape = L.pt.big ? kPatchBig : kPatchSmall;
-    jobs[i].code_matrix = i > 0;
-  });
-  patch_build(h.threads, jobs);
-}
-
 void device_update_values(Device *dv, Hierarchy &h) {
   HIPCHECK(hipSetDevice(dv->ordinal));
   const int naux = h.J - h.lc;
+  auto level_of = [&](int i) -> DLevel & { return i == 0 ? dv->fine : dv->aux[h.J + 1 - i]; };
   std::vector<LevelStage> st(1 + naux);
   std::vector<NbStage> nst(1 + naux);
-  std::vector<PatchJob<HCsr>> jobs(1 + naux);
-  std::vector<const HCsr *> mats(1 + naux);
+  std::vector<std::vector<double>> dict(1 + naux);  // of the coded levels
   host_parallel(h.threads, 1 + naux, [&](int t) {
     const int l = h.J + 1 - t;
-    DLevel &L = t == 0 ? dv->fine : dv->aux[l];
+    DLevel &L = level_of(t);
     stage_matrix(L, t == 0 ? h.A : h.Al.at(l), st[t]);
     if (L.sell.sv64) stage_sell(L, false, st[t]);
-    mats[t] = &st[t].H;
     if (t == 0) return;
+    if (L.pt.np && !L.pt.big) dict[t] = patch_dict(st[t].H.v);
     auto it = h.nb.find(l);
     if (it != h.nb.end()) stage_nb(it->second, L, st[t].H, nst[t]);
   });
-  rebuild_patches(dv, h, mats, jobs);
-  build_coarse_inverse(dv, h, false);
-  for (int i = 0; i <= naux; ++i) {
-    DPatch &D = (i == 0 ? dv->fine : dv->aux[h.J + 1 - i]).pt;
-    if (!D.np) continue;
-    if ((int64_t)jobs[i].all.pidx.size() != D.npair) throw AsmgError{ASMG_EINVAL, "matrix pattern changed"};
-    if (jobs[i].codes.matrix != D.mcode) {  // another kernel variant from here on
-      for (hipGraphExec_t &g : dv->graph) {
-        if (g) HIPCHECK(hipGraphExecDestroy(g));
-        g = nullptr;
-      }
-      D.mcode = jobs[i].codes.matrix;
-      patch_values(
-          D, [&](int64_t n) { return dalloc<double>(dv, n); }, [&](int64_t n) { return dalloc<float>(dv, n); });
+  // what may fail comes first: the pattern, room for a level's values in another form than before, the maps, the
+  // bottom inverse
+  struct Temp {
+    std::vector<void *> p;
+    void *copy(const void *v, size_t bytes) {
+      void *x = nullptr;
+      HIPCHECK(hipMalloc(&x, std::max<size_t>(bytes, 8)));
+      p.push_back(x);
+      if (bytes) HIPCHECK(hipMemcpy(x, v, bytes, hipMemcpyHostToDevice));
+      return x;
     }
-    dcopy(D.pidx, jobs[i].all.pidx);
-    patch_put_values(jobs[i].all, jobs[i].codes, D);
+    ~Temp() {
+      for (void *x : p) (void)hipFree(x);
+    }
+  } temp;
+  std::vector<const double *> vals(1 + naux, nullptr);
+  for (int i = 0; i <= naux; ++i) {
+    DPatch &D = level_of(i).pt;
+    if (!D.np) continue;
+    const HCsr &H = st[i].H;
+    if ((int64_t)H.ci.size() != level_of(i).A.nnz) throw AsmgError{ASMG_EINVAL, "matrix pattern changed"};
+    patch_values(
+        D, !dict[i].empty(), [&](int64_t n) { return dalloc<double>(dv, n); },
+        [&](int64_t n) { return dalloc<float>(dv, n); });
+    if (!D.map) {
+      int *m = dalloc<int>(dv, 2 * D.npair);
+      const int *rp = level_of(i).A.rp, *ci = level_of(i).A.ci;  // on the device on the original grid only
+      if (!rp) rp = (const int *)temp.copy(H.rp.data(), H.rp.size() * 4);
+      if (!ci) ci = (const int *)temp.copy(H.ci.data(), H.ci.size() * 4);
+      patch_map(D, rp, ci, m, nullptr);
+      D.map = m;
+    }
+    vals[i] = (const double *)temp.copy(H.v.data(), H.v.size() * 8);
   }
+  build_coarse_inverse(dv, h, false);
+  bool recoded = false;
+  for (int i = 0; i <= naux; ++i) {
+    DPatch &D = level_of(i).pt;
+    if (!D.np) continue;
+    recoded = recoded || D.mcode != !dict[i].empty();
+    D.mcode = !dict[i].empty();
+    if (D.mcode) {
+      const int used = (int)dict[i].size();
+      dict[i].resize(kPatchCodes, 0.0);
+      dcopy(D.dict64, dict[i]);
+      patch_round(kPatchCodes, D.dict64, D.dict32);
+      if (D.npair)
+        hipLaunchKernelGGL(k_patch_recode, dim3(nblk(D.npair)), dim3(BS), 0, nullptr, D.npair, kPatchSmall.bits,
+                           (const int *)D.map, vals[i], used, (const double *)D.dict64, D.pidx);
+    } else if (D.npair) {
+      hipLaunchKernelGGL(k_refresh_sell, dim3(nblk(2 * D.npair)), dim3(BS), 0, nullptr, (int)(2 * D.npair),
+                         (const int *)D.map, vals[i], D.plain64, D.plain32);
+    }
+  }
+  if (recoded)  // another kernel variant from here on
+    for (hipGraphExec_t &g : dv->graph) {
+      if (g) HIPCHECK(hipGraphExecDestroy(g));
+      g = nullptr;
+    }
   commit_level(dv, dv->fine, st[0], false, true);
   for (int l = h.J; l > h.lc; --l) {
     commit_level(dv, dv->aux[l], st[h.J - l + 1], false, false);
     commit_nb(dv, dv->aux[l].nb, nst[h.J - l + 1], false);
   }
   HIPCHECK(hipMemcpy(dv->kappa, h.kappa.data(), h.kappa.size() * 8, hipMemcpyHostToDevice));
+  HIPCHECK(hipGetLastError());
   HIPCHECK(hipDeviceSynchronize());
 }
 
@@ -2936,11 +2951,12 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
     std::vector<int> slots;
     build_sell(dv, F, H, false, &slots);
     build_refresh(dv, h, H, slots);
-    if (F.pt.npair > 0) {
-      dv->rf_patch_map = dalloc<int>(dv, 2 * F.pt.npair);
-      patch_map(F.pt, F.A.rp, F.A.ci, dv->rf_patch_map, s);
-    }
     dv->rf_ready = true;
+  }
+  if (F.pt.npair > 0 && !F.pt.map) {
+    int *m = dalloc<int>(dv, 2 * F.pt.npair);
+    patch_map(F.pt, F.A.rp, F.A.ci, m, s);
+    F.pt.map = m;
   }
   hipLaunchKernelGGL(k_refresh_off, dim3(nblk(F.A.nnz)), dim3(BS), 0, s, (int)F.A.nnz, dv->rf_off_ptr, dv->rf_off_el,
                      dv->rf_off_w, dv->kappa, F.A.v64, F.A.v32);
@@ -2950,7 +2966,7 @@ static int refresh_operator(Device *dv, Hierarchy &h, hipStream_t s) {
                      F.A.v64, F.sell.sv64, F.sell.sv32);
   if (F.pt.npair > 0)
     hipLaunchKernelGGL(k_refresh_sell, dim3(nblk(2 * F.pt.npair)), dim3(BS), 0, s, (int)(2 * F.pt.npair),
-                       dv->rf_patch_map, F.A.v64, F.pt.plain64, F.pt.plain32);
+                       F.pt.map, F.A.v64, F.pt.plain64, F.pt.plain32);
   HIPCHECK(hipGetLastError());
   HIPCHECK(hipStreamSynchronize(s));
   return ASMG_OK;

@@ -676,13 +676,12 @@ struct PatchValues {
 static inline PatchCodes patch_code(const std::vector<PatchValues> &V) {
   PatchCodes K;
   K.dict.assign(kPatchCodes, 0.0);
-  std::vector<double> d;
+  std::vector<double> d{0.0};  // the padding's, whether there is any or not: patch_recode decides by the matrix alone
   K.matrix = K.transfer = !V.empty();
   for (const PatchValues &v : V) {
     K.matrix = K.matrix && v.few && patch_codes(v.distinct, d);
     K.transfer = K.transfer && v.simple;
   }
-  K.matrix = K.matrix && !d.empty();
   if (K.matrix) {
     std::copy(d.begin(), d.end(), K.dict.begin());
     K.used = (int)d.size();
@@ -799,6 +798,7 @@ struct DPatch {
   // the dictionary or the plain values, as mcode says; a level that has been both holds both
   double *dict64 = nullptr, *plain64 = nullptr, *uval64 = nullptr, *rval64 = nullptr;
   float *dict32 = nullptr, *plain32 = nullptr, *uval32 = nullptr, *rval32 = nullptr;
+  int *map = nullptr;  // matrix entry of each stored value (patch_map), made when the values first change
   int64_t npair = 0, nu = 0, nr = 0, rows = 0, nstart = 0, ncoarse = 0;  // stored pairs, entries, rows
   template <class T>
   PatchView<T> view() const {
@@ -826,12 +826,12 @@ static inline void patch_round(int64_t n, const double *a, float *b) {
   if (n > 0) hipLaunchKernelGGL(k_patch_round, dim3(nblk(n)), dim3(BS), 0, nullptr, n, a, b);
 }
 
-// room for a level's matrix values as mcode says
+// room for a level's matrix values, coded or plain
 template <class Room64, class Room32>
-static void patch_values(DPatch &D, Room64 &&room64, Room32 &&room32) {
-  double *&v64 = D.mcode ? D.dict64 : D.plain64;
-  float *&v32 = D.mcode ? D.dict32 : D.plain32;
-  const int64_t n = D.mcode ? kPatchCodes : 2 * D.npair;
+static void patch_values(DPatch &D, bool coded, Room64 &&room64, Room32 &&room32) {
+  double *&v64 = coded ? D.dict64 : D.plain64;
+  float *&v32 = coded ? D.dict32 : D.plain32;
+  const int64_t n = coded ? kPatchCodes : 2 * D.npair;
   if (!v64) v64 = room64(n);
   if (!v32) v32 = room32(n);
 }
@@ -859,7 +859,7 @@ static void patch_commit(const PatchHost &H, const PatchCodes &K, DPatch &D, boo
   D.mcode = K.matrix;
   D.pidx = up(H.pidx);
   D.npair = (int64_t)H.pidx.size();
-  patch_values(D, room64, room32);
+  patch_values(D, D.mcode, room64, room32);
   patch_put_values(H, K, D);
   D.head = up(H.head);
   D.gidx = up(H.gidx);
@@ -1449,8 +1449,8 @@ __global__ __launch_bounds__(G::threads, (patch_waves<G, T, TC>(NR))) void k_pat
 
 // map[slot] = entry of the level's matrix (CSR rp, ci, columns ascending) that each stored value of a patch
 // came from, -1 = padding (a repeat of the row's first cell). One block per patch: the rows of its cells go
-// to LDS, every pair looks its two columns up. Run once, at the first change of the coefficient on the
-// device; the host's patches built again for it took 65 of that call's 200 ms at 250k rows.
+// to LDS, every pair looks its two columns up. Run once, at the first change of the coefficient; the host's patches
+// built again for it took 65 of that call's 200 ms at 250k rows.
 static __global__ __launch_bounds__(512) void k_patch_map(const PatchHead *head, const int *__restrict__ gidx,
                                                           const int *__restrict__ cgidx, const uint32_t *__restrict__ pidx,
                                                           int slices, int bits, const int *__restrict__ rp,
@@ -1493,6 +1493,33 @@ static void patch_map(const DPatch &D, const int *rp, const int *ci, int *map, h
   const PatchShape sh = D.big ? kPatchBig : kPatchSmall;
   hipLaunchKernelGGL(k_patch_map, dim3(D.np), dim3(512), (size_t)D.cells * sizeof(int), s, D.head, D.gidx, D.cgidx,
                      D.pidx, sh.slices, sh.bits, rp, ci, map);
+  HIPCHECK(hipGetLastError());
+}
+
+// new values of a coded matrix: the codes of its entries above their cell numbers (dict: `used` values, ascending)
+static __global__ __launch_bounds__(BS) void k_patch_recode(int64_t npair, int bits, const int *__restrict__ map,
+                                                            const double *__restrict__ v, int used,
+                                                            const double *__restrict__ dict, uint32_t *__restrict__ pidx) {
+  const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
+  if (i >= npair) return;
+  const uint32_t cells = (1u << bits) - 1;
+  uint32_t c = pidx[i] & (cells | cells << 16);
+  for (int h = 0; h < 2; ++h) {
+    const int p = map[2 * i + h];
+    const double x = p >= 0 ? v[p] : 0.0;
+    uint32_t k = 0;
+    while ((int)k < used - 1 && dict[k] < x) ++k;
+    c |= k << (16 * h + bits);
+  }
+  pidx[i] = c;
+}
+
+// dictionary of a matrix's values; empty: more than kPatchCodes, it stays plain
+template <class V>
+static std::vector<double> patch_dict(const V &v) {
+  std::vector<double> d{0.0};
+  if (!patch_codes(v, d)) d.clear();
+  return d;
 }
 
 // launch of a patch kernel; LDS: x on the cells, b (then the residual) and the
