@@ -1854,7 +1854,7 @@ static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &
       using G = decltype(geom);
       constexpr bool MC = decltype(mc)::value, TC = decltype(tc)::value;
       constexpr int RS = patch_split<T, TC>(NR), N1 = NR / RS;
-      launch_patch(k_patch_down<G, N1, T, BT, MC, TC, RS>, G::threads, D.np * RS, D, N1 * sizeof(T),
+      launch_patch<G>(k_patch_down<G, N1, T, BT, MC, TC, RS>, D.np * RS, D, N1 * sizeof(T),
                    patch_diag<T, TC>(N1) ? sizeof(T) : 0, s, e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, 1, b,
                    BV<T>::dg(L), (const T *)BV<T>::id(L), BV<T>::x(L), (T *)nullptr, BV<T>::b(Lc), (const int *)nullptr);
     });
@@ -1876,7 +1876,7 @@ static void patch_up(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &Lc
       using G = decltype(geom);
       constexpr bool MC = decltype(mc)::value, TC = decltype(tc)::value;
       constexpr int RS = patch_split<T, TC>(NR), N1 = NR / RS;
-      launch_patch(k_patch_up<G, N1, T, BT, MC, TC, false, RS>, G::threads, D.np * RS, D, N1 * sizeof(T), 0, s, e0, e1,
+      launch_patch<G>(k_patch_up<G, N1, T, BT, MC, TC, false, RS>, D.np * RS, D, N1 * sizeof(T), 0, s, e0, e1,
                    D.view<T>(), D.cells, L.C, nu, b, BV<T>::id(L), (const T *)BV<T>::x(L),
                    (const T *)b_result<T>(Lc), BV<T>::r(L), (double *)nullptr, (const int *)nullptr);
     });

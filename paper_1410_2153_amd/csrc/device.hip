@@ -2418,7 +2418,7 @@ static void patch_down(Device *dv, DLevel &L, int nu, const BT *b, T *bc, hipStr
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes<std::is_same<T, BT>::value>(D, [&](auto geom, auto mc, auto tc) {
       using G = decltype(geom);
-      launch_patch(k_patch_down<G, 1, T, BT, decltype(mc)::value, decltype(tc)::value>, G::threads, D.np, D, sizeof(T),
+      launch_patch<G>(k_patch_down<G, 1, T, BT, decltype(mc)::value, decltype(tc)::value>, D.np, D, sizeof(T),
                    sizeof(T), s, e0, e1, D.view<T>(), D.cells, D.lrows, L.C, nu, D.fused ? 1 : 0, b, LV<T>::dg(L),
                    (const T *)LV<T>::id(L), LV<T>::x(L), LV<T>::r(L), bc, dv->stop);
     });
@@ -2437,7 +2437,7 @@ static void patch_up(Device *dv, DLevel &L, int nu, const BT *b, const T *e, dou
       using G = decltype(geom);
       constexpr bool MC = decltype(mc)::value, TC = decltype(tc)::value;
       auto go = [&](auto kernel) {
-        launch_patch(kernel, G::threads, D.np, D, sizeof(T), 0, s, e0, e1, D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L),
+        launch_patch<G>(kernel, D.np, D, sizeof(T), 0, s, e0, e1, D.view<T>(), D.cells, L.C, nu, b, LV<T>::id(L),
                      (const T *)LV<T>::x(L), e, LV<T>::r(L), part, dv->stop);
       };
       if constexpr (sizeof(BT) == 8 && !MC) {

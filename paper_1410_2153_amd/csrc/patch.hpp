@@ -1523,19 +1523,22 @@ static std::vector<double> patch_dict(const V &v) {
 }
 
 // launch of a patch kernel; LDS: x on the cells, b (then the residual) and the
-// diagonal on the rows, `vec` and `scalar` bytes each
-template <class K, class... A>
-static void launch_patch(K kernel, int threads, int grid, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
+// diagonal on the rows, `vec` and `scalar` bytes each. The kernel's limit is set to what its largest patch can take,
+// the same value at every launch: handles of other sizes launch it from other threads.
+template <class G, class K, class... A>
+static void launch_patch(K kernel, int grid, const DPatch &D, size_t vec, size_t scalar, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1, A... args) {
+  constexpr PatchShape sh = G::waves == PatchBig::waves ? kPatchBig : kPatchSmall;
   const size_t lds = (size_t)D.cells * vec + (size_t)D.lrows * (vec + scalar);
-  if (lds > 64 * 1024)
+  const size_t most = 64 * ((size_t)sh.cell_slices * vec + (size_t)sh.slices * (vec + scalar));
+  if (most > 64 * 1024)
     HIPCHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)lds));
+                                 (int)most));
   if (e0) {
-    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, s, e0, e1, 0, args...);
+    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(G::threads), lds, s, e0, e1, 0, args...);
     HIPCHECK(hipGetLastError());
   } else {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, s, args...);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(G::threads), lds, s, args...);
   }
 }
 
