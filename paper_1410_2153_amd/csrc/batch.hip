@@ -1633,13 +1633,16 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
       dv->inv64 = balloc<double>(dv, len);
       dv->inv32 = balloc<float>(dv, len);
       std::vector<InvInput> in;
+      std::vector<int> mesh;
       for (int k = 0; k <= K; ++k)
         for (int m : bottom_m[k]) {
+          mesh.push_back(m);
           in.emplace_back();
           in.back().A = &H[m]->Al.at(H[m]->lc);
           coarse_components(*H[m], in.back().comp, in.back().gamma);
         }
-      device_inverses(in, moff, dv->inv64);
+      const int bad = device_inverses(in, moff, dv->inv64);
+      if (bad >= 0) throw AsmgError{ASMG_ENOTSPD, "mesh " + std::to_string(mesh[bad]) + ": " + kNotSpd};
       patch_round(len, dv->inv64, dv->inv32);
       std::vector<double *> g64, y64;
       std::vector<float *> g32, y32;

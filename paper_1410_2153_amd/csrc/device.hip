@@ -1787,7 +1787,7 @@ static void build_coarse_inverse(Device *dv, Hierarchy &h, bool first_time) {
     HIPCHECK(hipMalloc(&temp.p, (size_t)(n * n) * 8));
     M = (double *)temp.p;
   }
-  device_inverses(in, {0}, M);
+  if (device_inverses(in, {0}, M) >= 0) throw AsmgError{ASMG_ENOTSPD, kNotSpd};
   if (M != dv->cinv64) HIPCHECK(hipMemcpy(dv->cinv64, M, (size_t)(n * n) * 8, hipMemcpyDeviceToDevice));
   patch_round(n * n, dv->cinv64, dv->cinv32);
   HIPCHECK(hipDeviceSynchronize());

@@ -48,7 +48,7 @@ static __global__ __launch_bounds__(BS) void k_inv_panel(int k0, InvBatch B, con
   constexpr int per = kInvB * kInvB / BS;
   for (int s = 0; s < kb; ++s) {
     const double p = D[s][s];
-    if (!(p > 0.0) && tid == 0) *bad = 1;
+    if (!(p > 0.0) && tid == 0) bad[blockIdx.y] = 1;
     const double pi = 1.0 / p;
     double v[per];
 #pragma unroll
@@ -133,6 +133,8 @@ static __global__ __launch_bounds__(BS) void k_inv_fill(int n, const int *__rest
   for (int p = rp[i] + threadIdx.x; p < rp[i + 1]; p += BS) row[ci[p]] += v[p];
 }
 
+static constexpr const char *kNotSpd = "matrix of an exact subsystem solve is not positive definite";
+
 // One matrix to invert: A_lc with the rank-one terms of its singular components (coarse_components).
 struct InvInput {
   const Csr *A;
@@ -140,8 +142,9 @@ struct InvInput {
   std::vector<double> gamma;
 };
 
-// M + moff[i] = inverse of matrix i, FP64 on the device; throws ASMG_ENOTSPD where a pivot is not positive
-static void device_inverses(const std::vector<InvInput> &in, const std::vector<int64_t> &moff, double *M) {
+// M + moff[i] = inverse of matrix i, FP64 on the device; returns the first matrix with a pivot that is not
+// positive, -1 = none
+static int device_inverses(const std::vector<InvInput> &in, const std::vector<int64_t> &moff, double *M) {
   std::vector<int> ns;
   std::vector<int64_t> soff;
   int64_t scratch = 0;
@@ -172,10 +175,10 @@ static void device_inverses(const std::vector<InvInput> &in, const std::vector<i
     dv.insert(dv.end(), x.gamma.begin(), x.gamma.end());
     at.push_back(a);
   }
-  if (most == 0) return;
+  if (most == 0) return -1;
   const size_t m = in.size(), nsat = iv.size();
   iv.insert(iv.end(), ns.begin(), ns.end());
-  iv.push_back(0);  // the flag of a pivot that is not positive
+  iv.resize(iv.size() + m, 0);  // flags of a pivot that is not positive
   struct Bufs {
     std::vector<void *> p;
     void *get(size_t bytes) {
@@ -207,14 +210,16 @@ static void device_inverses(const std::vector<InvInput> &in, const std::vector<i
     const InvBatch B{di + nsat + i0, off + i0, off + m + i0};
     const unsigned c = (unsigned)std::min(kMost, m - i0);
     for (int k0 = 0; k0 < most; k0 += kInvB) {
-      hipLaunchKernelGGL(k_inv_panel, dim3(tiles, c), dim3(BS), 0, nullptr, k0, B, M, sc, bad);
+      hipLaunchKernelGGL(k_inv_panel, dim3(tiles, c), dim3(BS), 0, nullptr, k0, B, M, sc, bad + i0);
       hipLaunchKernelGGL(k_inv_update, dim3(tiles, tiles, c), dim3(BS), 0, nullptr, k0, B, M, sc);
     }
   }
   HIPCHECK(hipGetLastError());
-  int flag = 0;
-  HIPCHECK(hipMemcpy(&flag, bad, 4, hipMemcpyDeviceToHost));
-  if (flag) throw AsmgError{ASMG_ENOTSPD, "matrix of an exact subsystem solve is not positive definite"};
+  std::vector<int> flag(m);
+  HIPCHECK(hipMemcpy(flag.data(), bad, m * 4, hipMemcpyDeviceToHost));
+  for (size_t i = 0; i < m; ++i)
+    if (flag[i]) return (int)i;
+  return -1;
 }
 
 }  // namespace asmg
