@@ -2695,11 +2695,18 @@ static void pcg_tail(Device *dv, hipStream_t s, bool first_done) {
   const int n = dv->fine.n, np = dv->fine.pt.on<T>() ? dv->fine.pt.np : 0;
   double *rz = dv->partials + 2 * RED_BLOCKS;
   const bool fused = np > 0 && np <= RED_BLOCKS;
-  dv->stop = &dv->ctl->a.done;
-  dv->rz_part = fused ? rz : nullptr;
-  apply_Bco<T>(dv, dv->r, first_done, s);
-  dv->stop = nullptr;
-  dv->rz_part = nullptr;
+  {
+    struct Reset {  // an error inside must not leave the flag to a later application
+      Device *dv;
+      ~Reset() {
+        dv->stop = nullptr;
+        dv->rz_part = nullptr;
+      }
+    } reset{dv};
+    dv->stop = &dv->ctl->a.done;
+    dv->rz_part = fused ? rz : nullptr;
+    apply_Bco<T>(dv, dv->r, first_done, s);
+  }
   const int g = red_grid(dv, n, 1);
   if (!fused)
     hipLaunchKernelGGL((k_cg_rz<T>), dim3(g), dim3(BS), 0, s, n, dv->r, (const T *)result<T>(dv->fine), dv->ctl, rz);
