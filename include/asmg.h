@@ -305,7 +305,11 @@ int asmg_time_kernel(asmg_handle h, int which, int reps, int precision, void *st
  *                   slice per wave, 1 = grid-stride loop over the slices
  *   "tune_times"    double: the autotuner's best time in ms of every candidate shape at every
  *                   launch site, site-major (-1 = not timed; level = precision)
- * Batch handles: "batch_n", "batch_J", "batch_lc" (int64 per mesh), "batch_shapes"
+ *   "patches"       int64[6] of smoothed level `level`, or of the original grid (level = -1): overlapped
+ *                   patches (0 = colour passes only), 1 = the larger patch shape, matrix entries coded,
+ *                   transfer entries coded, 1 = run by the FP64 cycle, by the FP32 cycle (device handles)
+ * Batch handles: "batch_n", "batch_J", "batch_lc" (int64 per mesh), "batch_patches" (as "patches";
+ * level = merged level from the finest, 0.., or -1), "batch_shapes"
  * (level = n_rhs + 8 * precision): (threads per block, XCD order, kernel variant) triples chosen
  * by the launch-shape autotuner for every slice-kernel launch site of B_co, empty before the
  * first solve with that n_rhs and precision, and "batch_tune_times" (same level): the tuner's

@@ -523,12 +523,17 @@ int asmg_export(asmg_handle H, const char *name_c, int level, void *buf, int64_t
         if (!H->bdev) return set_err(ASMG_EINVAL, "host-only batch handle");
         return put(batch_tune_times(H->bdev, level % 8, level / 8), buf, count);
       }
+      if (name == "batch_patches") {  // level = merged level, -1 = the original grids
+        if (!H->bdev) return set_err(ASMG_EINVAL, "host-only batch handle");
+        return put(batch_patches(H->bdev, level), buf, count);
+      }
       if (name == "batch_n" || name == "batch_J" || name == "batch_lc") {
         std::vector<int64_t> v;
         for (auto &hp : H->batch) v.push_back(name == "batch_n" ? hp->n() : name == "batch_J" ? hp->J : hp->lc);
         return put(v, buf, count);
       }
-      return set_err(ASMG_EINVAL, "batch handle exports: batch_n, batch_J, batch_lc, batch_shapes, batch_tune_times");
+      return set_err(ASMG_EINVAL, "batch handle exports: batch_n, batch_J, batch_lc, batch_patches, batch_shapes, "
+                                  "batch_tune_times");
     }
     if (name == "info") {
       std::vector<int64_t> v(16, 0);
@@ -612,6 +617,10 @@ int asmg_export(asmg_handle H, const char *name_c, int level, void *buf, int64_t
     if (name == "tuned_shapes") {  // level = precision
       if (!H->dev) return set_err(ASMG_EINVAL, "host-only handle");
       return put(device_tuned_shapes(H->dev, level), buf, count);
+    }
+    if (name == "patches") {  // level = auxiliary level, -1 = the original grid
+      if (!H->dev) return set_err(ASMG_EINVAL, "host-only handle");
+      return put(device_patches(H->dev, level), buf, count);
     }
     if (name == "local_set") {
       auto it = h.local_set.find(level);

@@ -2435,6 +2435,12 @@ std::vector<int64_t> batch_tuned_shapes(BatchDevice *dv, int nr, int precision) 
   return out;
 }
 
+std::vector<int64_t> batch_patches(BatchDevice *dv, int level) {
+  if (level < 0) return patch_info(dv->fine.pt);
+  if (level >= (int)dv->aux.size()) throw AsmgError{ASMG_EINVAL, "no such merged level"};
+  return patch_info(dv->aux[level].pt);
+}
+
 std::vector<double> batch_tune_times(BatchDevice *dv, int nr, int precision) {
   std::vector<double> out;
   if (nr < 1 || nr > 4 || precision < 0 || precision > 1) return out;

@@ -26,6 +26,8 @@ int64_t batch_n_total(BatchDevice *dv);
 // launch shapes picked by the autotuner for (NR, precision): threads per block, XCD order and
 // kernel variant of every slice-kernel launch site, flattened triples (empty before the first solve)
 std::vector<int64_t> batch_tuned_shapes(BatchDevice *dv, int nr, int precision);
+// patches of a merged level, or (-1) the original grids, as device_patches
+std::vector<int64_t> batch_patches(BatchDevice *dv, int level);
 // the autotuner's best time (ms) of every candidate at every launch site, site-major (-1 = not timed)
 std::vector<double> batch_tune_times(BatchDevice *dv, int nr, int precision);
 

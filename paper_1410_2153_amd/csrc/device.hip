@@ -3321,6 +3321,12 @@ std::vector<int64_t> device_tuned_shapes(Device *dv, int precision) {
   return out;
 }
 
+std::vector<int64_t> device_patches(Device *dv, int level) {
+  if (level < 0) return patch_info(dv->fine.pt);
+  if (level <= dv->lc || level > dv->J) throw AsmgError{ASMG_EINVAL, "no smoothed level there"};
+  return patch_info(dv->aux[level].pt);
+}
+
 std::vector<double> device_tune_times(Device *dv, int precision) {
   std::vector<double> out;
   if (precision < 0 || precision > 1) return out;

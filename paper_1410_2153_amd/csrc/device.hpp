@@ -39,6 +39,9 @@ int device_time_kernel(Device *dv, int which, int reps, int precision, void *str
 // launch shapes picked by the autotuner for a precision: (threads per block, XCD order, kernel
 // variant) per slice-kernel launch site, flattened (empty before the first solve in that precision)
 std::vector<int64_t> device_tuned_shapes(Device *dv, int precision);
+// of an auxiliary level, or (-1) the original grid: patches (0 = none), larger shape, matrix coded, transfers coded,
+// run by the FP64 cycle, by the FP32 cycle
+std::vector<int64_t> device_patches(Device *dv, int level);
 // the autotuner's best time (ms) of every candidate shape at every launch site, site-major
 // (kNumShapes values per site; -1 where a candidate was not timed)
 std::vector<double> device_tune_times(Device *dv, int precision);

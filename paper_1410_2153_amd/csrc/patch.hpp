@@ -816,6 +816,11 @@ struct DPatch {
   }
 };
 
+// what the handles export of a level's patches
+static inline std::vector<int64_t> patch_info(const DPatch &D) {
+  return {D.np, D.big, D.mcode, D.tcode, D.on<double>(), D.on<float>()};
+}
+
 static __global__ __launch_bounds__(BS) void k_patch_round(int64_t n, const double *__restrict__ a,
                                                            float *__restrict__ b) {
   const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
