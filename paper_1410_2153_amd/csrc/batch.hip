@@ -1849,9 +1849,7 @@ static void patch_launch(BatchDevice *dv, int passes, double bytes, F &&launch) 
 template <int NR, class T, class BT>
 static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &Lc, hipStream_t s) {
   const DPatch &D = L.pt;
-  const double sz = sizeof(T), n = L.nsmooth;
-  const double by = (double)L.nnz * (sz + 2) + n * (4 + NR * sizeof(BT) + sz + NR * sz) + (double)D.nr * 2 * (sz + 2) +
-                    (double)D.ncoarse * (4 + NR * sz);
+  const double by = patch_down_bytes<NR, T, BT>(D, L.nsmooth, (double)L.nnz);
   patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes<false>(D, [&](auto geom, auto mc, auto tc) {
       using G = decltype(geom);
@@ -1871,9 +1869,7 @@ static void patch_down(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &
 template <int NR, class T, class BT>
 static void patch_up(BatchDevice *dv, BLevel &L, int nu, const BT *b, BLevel &Lc, hipStream_t s) {
   const DPatch &D = L.pt;
-  const double sz = sizeof(T), n = L.nsmooth;
-  const double by = (double)L.nnz * (sz + 2) + n * (4 + NR * sizeof(BT) + sz + 2 * NR * sz) +
-                    (double)D.nu * (sz + 4) + (double)D.ncoarse * NR * sz;
+  const double by = patch_up_bytes<NR, T, BT>(D, L.nsmooth, (double)L.nnz);
   patch_launch(dv, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes<false>(D, [&](auto geom, auto mc, auto tc) {
       using G = decltype(geom);

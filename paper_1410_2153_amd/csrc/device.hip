@@ -2411,10 +2411,7 @@ static void patch_launch(Device *dv, const DPatch &D, int passes, double bytes, 
 template <class T, class BT>
 static void patch_down(Device *dv, DLevel &L, int nu, const BT *b, T *bc, hipStream_t s) {
   const DPatch &D = L.pt;
-  const double sz = sizeof(T);
-  // entries once, cell numbers, b, the diagonals, x written; the restriction's entries and result
-  const double by = (double)L.A.nnz * (sz + 2) + (double)L.n * (4 + sizeof(BT) + 3 * sz) +
-                    (D.fused ? (double)D.nr * 2 * (sz + 2) + (double)D.ncoarse * (4 + sz) : (double)L.n * sz);
+  const double by = patch_down_bytes<1, T, BT>(D, L.n, (double)L.A.nnz);
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes<std::is_same<T, BT>::value>(D, [&](auto geom, auto mc, auto tc) {
       using G = decltype(geom);
@@ -2429,9 +2426,7 @@ static void patch_down(Device *dv, DLevel &L, int nu, const BT *b, T *bc, hipStr
 template <class T, class BT>
 static void patch_up(Device *dv, DLevel &L, int nu, const BT *b, const T *e, double *part, hipStream_t s) {
   const DPatch &D = L.pt;
-  const double sz = sizeof(T);
-  const double by = (double)L.A.nnz * (sz + 2) + (double)L.n * (4 + sizeof(BT) + 3 * sz) + (double)D.nu * (sz + 4) +
-                    (double)D.ncoarse * sz;
+  const double by = patch_up_bytes<1, T, BT>(D, L.n, (double)L.A.nnz);
   patch_launch<T>(dv, D, nu * L.C + 1, by, [&](hipEvent_t e0, hipEvent_t e1) {
     with_codes<std::is_same<T, BT>::value>(D, [&](auto geom, auto mc, auto tc) {
       using G = decltype(geom);

@@ -816,6 +816,24 @@ struct DPatch {
   }
 };
 
+// Algorithmic bytes of a level's two launches (n rows, nnz off-diagonal entries, NR values a row): every entry once,
+// as its 2-byte cell or 4-byte column and, where it is not coded, its value; the vectors and diagonals once.
+template <int NR, class T, class BT>
+static double patch_down_bytes(const DPatch &D, double n, double nnz) {
+  const double sz = sizeof(T), value = D.mcode ? 0 : sz, weight = D.tcode ? 0 : sz;
+  // b, the diagonal (and in FP32 its reciprocal), x written; the restriction's entries and result, or the residual
+  const double rows = 4 + NR * sizeof(BT) + (sizeof(T) == 4 ? 2 : 1) * sz + NR * sz;
+  return nnz * (2 + value) + n * rows +
+         (D.fused ? (double)D.nr * 2 * (2 + weight) + (double)D.ncoarse * (4 + NR * sz) : n * NR * sz);
+}
+template <int NR, class T, class BT>
+static double patch_up_bytes(const DPatch &D, double n, double nnz) {
+  const double sz = sizeof(T), value = D.mcode ? 0 : sz, weight = D.tcode ? 0 : sz;
+  // b, the reciprocal of the diagonal, x read and the result written; the prolongation's entries and input
+  return nnz * (2 + value) + n * (4 + NR * sizeof(BT) + sz + 2 * NR * sz) + (double)D.nu * (4 + weight) +
+         (double)D.ncoarse * NR * sz;
+}
+
 // what the handles export of a level's patches
 static inline std::vector<int64_t> patch_info(const DPatch &D) {
   return {D.np, D.big, D.mcode, D.tcode, D.on<double>(), D.on<float>()};
