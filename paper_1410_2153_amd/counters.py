@@ -52,18 +52,21 @@ def _srcs(*names):
 
 
 KERNEL_SRCS = _srcs("device.hip", "common.hpp", "patch.hpp")
+PATCH_SHAPE = "one block of 512 threads per patch, XCD-contiguous block order"
 
 # workload -> dominant kernel, the sources that define it, the bench selection of the counter runs
 WORKLOADS = {
-    "graded1M": dict(kernel=KERNEL, sources=("device.hip", "common.hpp", "patch.hpp"),
+    "graded1M": dict(kernel=KERNEL, shape=PATCH_SHAPE, sources=("device.hip", "common.hpp", "patch.hpp"),
                      bench="--only graded --no-extra", engine="single",
                      desc="graded 2-D Delaunay mesh, 1002722 vertices, FP64 and mixed solves"),
-    "cube2M": dict(kernel="asmg::k_sell<0, double, 0>", sources=("device.hip", "common.hpp"),
+    "cube2M": dict(kernel="asmg::k_sell<0, double, 0>",
+                   shape="256 threads per block, XCD-contiguous block order at every launch site", sources=("device.hip", "common.hpp"),
                    bench="--only cube3d", engine="single",
                    desc="Kuhn cube 128^3 x 6 tetrahedra, 2048383 unknowns, FP64 and mixed solves"),
     "batched256x4": dict(kernel=("asmg::k_patch_down<asmg::PatchGeom<8, 4, 4, 4, 12>, 2, double, double, true, true, 2>",
                                  "asmg::k_patch_up<asmg::PatchGeom<8, 4, 4, 4, 12>, 2, double, double, true, true, "
                                  "false, 2>"),
+                         shape=PATCH_SHAPE + ", two blocks of two right-hand sides per patch",
                          sources=("batch.hip", "common.hpp", "patch.hpp"),
                          bench="--only batched", engine="batch",
                          desc="256 jittered squares (sides 32..512) x 4 right-hand sides, FP64 and mixed solves"),
@@ -82,7 +85,7 @@ def source_key(paths=KERNEL_SRCS):
 
 
 def _name(kernel_name):
-    return kernel_name.split("(")[0].replace("void ", "")
+    return kernel_name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
 
 
 def _per_dispatch(path, counter, kernel):
@@ -173,7 +176,7 @@ def record(workload, fetch_csv, write_csv):
     return {
         "kernel": " and ".join(kernel) if isinstance(kernel, tuple) else kernel,
         "workload": wl["desc"],
-        "launch_shape": "256 threads per block, XCD-contiguous block order at every launch site",
+        "launch_shape": wl["shape"],
         "kernel_code_key": source_key(_srcs(*wl["sources"])),
         "kernel_sources": list(wl["sources"]),
         "dispatches": n,
