@@ -11,8 +11,8 @@
  *     the Scott-Zhang transfer Pi (Section 4.1);
  *   - solve: CG (Section 5.2) preconditioned by one multiplicative auxiliary
  *     space cycle (Algorithm 1): Gauss-Seidel on the original grid, transfer
- *     Pi^T, a V-cycle (Algorithm 2) down the auxiliary hierarchy with a dense
- *     Cholesky solve at the bottom, transfer Pi, Gauss-Seidel back.
+ *     Pi^T, a V-cycle (Algorithm 2) down the auxiliary hierarchy with an exact
+ *     dense solve at the bottom, transfer Pi, Gauss-Seidel back.
  *
  * Conventions
  *   - All functions return 0 on success or a negative ASMG_E* code; they never
@@ -104,7 +104,8 @@ typedef struct {
                           level meshes of general domains) stay on the host. Needs device >= 0;
                           single-mesh handles. 0 = host (default). */
   int red_blocks;      /* cap on the blocks of the PCG reduction kernels (dot products, residual
-                          norms, q = A p), 1..2048; 0 = 2048 (default). Beyond the cap the kernels
+                          norms, q = A p), 1..2048; 0 = no cap of its own (default). A grid holds
+                          1024 blocks at most, whatever the cap; beyond it the kernels
                           loop over their rows (grid-stride). Results do not depend on it beyond
                           the summation order of the dot products. Single-mesh handles. */
   int nb_layers;       /* near-boundary correction (Section 3.5, Algorithm 3): j > 0 = on every
@@ -197,8 +198,7 @@ int asmg_solve_device(asmg_handle h, const double *d_f, double tol, double *d_u,
  * allocation): the call allocates nothing, host or device, and calls no allocating routine.
  * The PCG control block and the reduction partials live in a static per-GPU scratch array of
  * 24832 bytes (256 for the control block, three times 8 per reduction block up to 1024) held by the library
- * until the process ends; every handle's reduction grid fits it (a larger one would be rejected
- * with ASMG_EINVAL). The iteration runs as eager kernel launches (no graph is built) and the
+ * until the process ends; every handle's reduction grid fits it. The iteration runs as eager kernel launches (no graph is built) and the
  * launch-shape autotuner never runs here: the shapes tuned by earlier asmg_solve_device calls on
  * the handle are used, or the defaults. Results equal asmg_solve_device's bit for bit. Calls on
  * one GPU share that GPU's scratch: calls that overlap on one GPU (from several threads, or on

@@ -1454,8 +1454,8 @@ BatchDevice *batch_device_create(std::vector<std::unique_ptr<Hierarchy>> &H, int
     patch_build(0, jobs);
     auto passes = [&](int i) { return jobs[i].cuts.empty() || !patch_fp32(dv->d); };
     // ---- sliced ELL images: the product of the original grids, and what some cycle does by passes. Tasks: 0-2 the
-    // original grids' smoothing, product and residual images, 3-4 Pi and Pi^T, 5..K+4 the auxiliary
-    // levels, K+5 the bottom inverses, then the prolongations
+    // original grids' smoothing, product and residual images, 3-4 Pi and Pi^T, 5..K+5 the auxiliary
+    // levels (nothing for the deepest, whose rows are bottom unknowns), then the prolongations
     host_parallel(0, 2 * K + 6, [&](int t) {
       if (t == 0) {
         if (!passes(0)) return;

@@ -558,9 +558,10 @@ static bool patch_range(const PatchSource<M> &S, int a, int b, PatchMarks &W, Pa
   return patch_range(S, a, m, W, out) && patch_range(S, m, b, W, out);
 }
 
-// Own rows per patch: enough patches for the chip where that is possible, no fewer own rows than
-// kPatchOwnMin (the halo grows against them: measured flat from 256 to 1024 within 4 %), no more than
-// kPatchOwnMax; where the halo outweighs the own rows (3-D levels), as many as fit.
+// Own rows per patch that a plan starts from: enough patches for the chip where that is possible, no fewer own rows
+// than kPatchOwnMin (the halo grows against them: measured flat from 256 to 1024 within 4 %), no more than
+// kPatchOwnMax. Where such patches do not fit, a fifth less at a time, down to 128; where the halo outweighs the own
+// rows (3-D levels), as many as fit.
 static constexpr int kPatchOwnMin = 256;
 static constexpr int kPatchOwnMax = 1536;
 

@@ -7,7 +7,7 @@
 //   build_levels      choice of the V-cycle bottom, A_l and P_l patterns (Section 4.1)
 //   build_transfer    Scott-Zhang transfer Pi (Section 4.1)
 //   build_colourings  multicolour orderings for Gauss-Seidel
-//   build_coarse      Cholesky factor and explicit inverse of the bottom matrix (Algorithm 2, B_0)
+//   build_coarse      host-only handles: Cholesky factor and explicit inverse of the bottom matrix (Algorithm 2, B_0)
 //
 // Index maps (keys, refined boxes, vertices, simplices, unknown numbering, patterns,
 // colourings) are exact integer computations. The floating-point steps that feed
@@ -1458,7 +1458,7 @@ void build_local_sets(Hierarchy &h) {
 }
 
 // ---------------------------------------------------------------------------
-// bottom of the V-cycle: Cholesky factor A_lc = L L^T and the explicit inverse
+// bottom of the V-cycle on host-only handles: Cholesky factor A_lc = L L^T and the explicit inverse
 // ---------------------------------------------------------------------------
 
 void build_coarse(Hierarchy &h) {
