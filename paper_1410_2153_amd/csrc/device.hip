@@ -1955,6 +1955,7 @@ Device *device_create(Hierarchy &h, int ordinal) {
     commit_transfer(dv, pit_st, dv->PiT);
     for (int i = 0; i <= naux; ++i) {
       level_of(i).pt.big = jobs[i].src.shape.waves == kPatchBig.waves;
+      if (i > 0) level_of(i).pt.cells_host.swap(jobs[i].all.cgidx);
       patch_commit(
           jobs[i].all, jobs[i].codes, level_of(i).pt, jobs[i].src.R != nullptr, [&](const auto &v) { return dupload(dv, v); },
           [&](int64_t n) { return dalloc<double>(dv, n); }, [&](int64_t n) { return dalloc<float>(dv, n); });
@@ -2055,7 +2056,12 @@ void device_update_values(Device *dv, Hierarchy &h) {
       const int *rp = level_of(i).A.rp, *ci = level_of(i).A.ci;  // on the device on the original grid only
       if (!rp) rp = (const int *)temp.copy(H.rp.data(), H.rp.size() * 4);
       if (!ci) ci = (const int *)temp.copy(H.ci.data(), H.ci.size() * 4);
+      if (i > 0) D.cgidx = (int *)temp.copy(D.cells_host.data(), D.cells_host.size() * 4);
       patch_map(D, rp, ci, m, nullptr);
+      if (i > 0) {
+        D.cgidx = nullptr;
+        D.cells_host = RawVector<int>();
+      }
       D.map = m;
     }
     vals[i] = (const double *)temp.copy(H.v.data(), H.v.size() * 8);

@@ -819,6 +819,7 @@ struct DPatch {
   double *dict64 = nullptr, *plain64 = nullptr, *uval64 = nullptr, *rval64 = nullptr;
   float *dict32 = nullptr, *plain32 = nullptr, *uval32 = nullptr, *rval32 = nullptr;
   int *map = nullptr;  // matrix entry of each stored value (patch_map), made when the values first change
+  RawVector<int> cells_host;  // cgidx where only a host update can make the map: most handles never need it
   int64_t npair = 0, nu = 0, nr = 0, rows = 0, nstart = 0, ncoarse = 0;  // stored pairs, entries, rows
   template <class T>
   PatchView<T> view() const {
